@@ -764,13 +764,13 @@ def main():
     one_step_bytes = B * (28 * cells + 16 * interior)
     per_step_us = rev_us / steps_r
     traffic = reverse_traffic(B, rev_shape, steps_r)
-    rev_kernel = (f"rev2d_t{steps_r}_kernel<{rev_shape[0]}> ({steps_r} reverse steps per launch: reconstruction + "
+    rev_kernel = (f"rev2d_multi_kernel<{rev_shape[0]}, {steps_r}> ({steps_r} reverse steps per launch: reconstruction + "
                   f"receiver field + imaging, {B} shots per launch)" if steps_r >= 2 else
                   f"rev2d_kernel<{rev_shape[0]},false,{rev_shape[1]}> (fused reconstruction + receiver field + "
                   f"imaging, {B} shots per launch)")
     # the reverse launches of the check plan: nt // steps multi-step launches
     # plus the nt % steps single steps
-    check_kernel = (f"rev2d_t{steps_r}_kernel<{rev_shape[0]}> at the timed shape, {B} shots"
+    check_kernel = (f"rev2d_multi_kernel<{rev_shape[0]}, {steps_r}> at the timed shape, {B} shots"
                     if check_launches == nt // steps_r + nt % steps_r else f"{check_launches} launches")
     fwd_ms, fwd_n = loops["model_forward"]
     rf_ms, rf_n = loops["rtm_forward"]

@@ -21,13 +21,14 @@
 #include "rtm.h"
 
 namespace rtm {
-// prop2d.hip
+// prop2d.hip (one step per launch, persistent passes)
 hipError_t launch_fwd2d(int vec, int tx, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                         const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
                         hipStream_t st);
 hipError_t launch_rev2d(int vec, int tx, bool grad, const ShotDev *shots, const Tile2D *tiles, int ntiles,
                         int nslots, const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj,
                         hipStream_t st);
+// prop2d_multi.hip
 hipError_t launch_fwd2d_t2(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
                            hipStream_t st);
@@ -38,6 +39,10 @@ hipError_t launch_fwd2d_t3(int vec, const ShotDev *shots, const Tile2D *tiles, i
                            hipStream_t st);
 hipError_t launch_rev2d_t3(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, int k, int reinject, hipStream_t st);
+hipError_t launch_rev2d_t3_grad(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+                                const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj,
+                                hipStream_t st);
+// prop2d.hip
 hipError_t launch_fwd2d_persist(int vec, const ShotDev *shots, const Tile2D *tiles, const PItem *items, int nitems,
                                 const int *shot_items, const InjEnt *ents, const Contrib *cont,
                                 const SampleTask *stasks, int n0, int nsteps, unsigned *cnt, unsigned *status,
@@ -658,35 +663,81 @@ int64_t count_tiles(const Job &J, Tune t)
 // shot of a modest grid) would leave most of the 256 CUs idle, so the shape
 // is narrowed (fewer rows per tile first, then fewer floats per lane) until
 // the job has at least kMinWaves wavefronts or the smallest shape is
-// reached.  Results do not depend on the shape.
-//
-// Three steps per launch keep their shape down to kT3Mid wavefronts, take
-// half-height tiles down to kT3Small, and below that (one or two shots of a
-// survey grid, latency-bound) give way to two steps and the narrowing
-// above.  Measured per shot on 2301 x 751 batches (modeling + RTM): 2 shots
-// 26-28 us per step with two steps against 33+ with three; 4 and 8 shots
-// 26 and 18 us with three steps and half-height tiles against 27-29 and
-// 24-31 otherwise; 16 shots and more best at the configured shape.
+// reached.  Results do not depend on the shape.  (One step per launch; the
+// 2-D multi-step shape is chosen by fit_multi.)
 constexpr int64_t kMinWaves = 256 * 16;
-constexpr int64_t kT3Mid = 2048, kT3Small = 600;
 
 Tune fit_tune(const Job &J, Tune t)
 {
     if (g_tune_exact.load()) return t;
-    if (t.steps > 2) {
-        const int64_t n = count_tiles(J, t);
-        if (n >= kT3Mid) return t;
-        if (n >= kT3Small) {
-            if (t.zseg >= 2 * kMinZseg) t.zseg = std::max(kMinZseg, t.zseg / 2 / kZUnroll * kZUnroll);
-            return t;
-        }
-        t.steps = 2;
-    }
     while (count_tiles(J, t) < kMinWaves) {
         if (t.zseg > kMinZseg) t.zseg = std::max(kMinZseg, t.zseg / 2 / kZUnroll * kZUnroll);
         else if (t.ty > 4) t.ty = 4;
         else if (t.vec > 1) t.vec /= 2;
         else break;
+    }
+    return t;
+}
+
+// Wavefronts of a 2-D launch of `steps` time steps.
+int64_t count_multi(const Job &J, int steps, int vec, int zseg)
+{
+    int64_t n = 0;
+    const int own = 64 * vec - 8 * (steps - 1);
+    for (const ShotIn &S : J.shots) n += (int64_t)((S.g.NX + own - 1) / own) * ((S.g.L.NZr + zseg - 1) / zseg);
+    return n;
+}
+
+// Rows per tile of a 2-D multi-step launch: the height, from the configured
+// one down, with the least march time.  A tile marches 9 (T - 1) rows beyond
+// its own; a SIMD with k wavefronts takes about 0.5 + k units per row and no
+// less than 2.2 (what its own latency costs a lone wavefront).  Up to three
+// wavefronts per SIMD all are resident and the fullest SIMD ends the launch,
+// so k lies half way to the whole number above.  Measured (us per step, forward, three steps, two floats per lane):
+// 4 shots of 2301 x 751 at 18, 27, 36, 54 rows 19.4, 15.1, 16.5, 17.0; 8
+// shots at 27, 36, 54, 108 rows 31.4, 31.3, 29.3, 33.0; 16 shots at 54, 108
+// rows 57.1, 52.7; 24 windows at 18, 27, 36 rows 15.7, 15.5, 14.5.
+int best_rows(const Job &J, int steps, int vec, int top, int least)
+{
+    int best = top;
+    double cost = 0.0;
+    for (int z : {top, 108, 54, 36, 27, 18, 9}) {
+        if (z != top && (z > top || z < least)) continue;
+        const double n = count_multi(J, steps, vec, z) / 1024.0;  // wavefronts per SIMD
+        const double k = n <= 3.0 ? 0.5 * (n + std::ceil(n)) : n;
+        const double c = (z + 9 * (steps - 1)) * std::max(2.2, 0.5 + k);
+        if (cost == 0.0 || c < cost) {
+            cost = c;
+            best = z;
+        }
+    }
+    return best;
+}
+
+// Shape of a 2-D multi-step launch: the configured steps and floats per lane
+// while their shortest useful tiles (18 rows forward, 27 reverse: shorter
+// ones march twice their rows) still give about two wavefronts per SIMD.
+// Below that three steps give way to two and the lanes are narrowed.
+// Measured (us per step, forward / reverse): 12 windows, three steps 9.4
+// against two 9.8; 2 shots, reverse, two steps at one float 20.6 against
+// three 26.4 and two at two floats 21.0; 1 shot, two steps, nine rows, two
+// floats 6.6 / 13.2 against one 7.4 / 14.5; 1574 x 534, one float 4.7 / 8.9
+// against two 4.8 / 10.0.
+Tune fit_multi(const Job &J, Tune t, bool reverse)
+{
+    if (g_tune_exact.load()) return t;
+    const int least = reverse && t.steps == 3 ? 27 : 18;
+    if (count_multi(J, t.steps, t.vec, std::min(t.zseg, least)) >= (reverse ? 2048 : 1900)) {
+        t.zseg = best_rows(J, t.steps, t.vec, t.zseg, least);
+        return t;
+    }
+    t.steps = 2;
+    if (reverse && count_multi(J, 2, 1, 18) >= 2300) {
+        t.vec = 1;
+        t.zseg = best_rows(J, 2, 1, 54, 18);
+    } else {
+        t.vec = count_multi(J, 2, 2, kMinZseg) >= 1800 ? 2 : 1;
+        t.zseg = best_rows(J, 2, t.vec, 18, kMinZseg);
     }
     return t;
 }
@@ -744,7 +795,8 @@ int build_job_tables(Job &J)
     const int ndim = J.shots[0].g.ndim;
     const bool persist = (J.flags & RTM_F_PERSISTENT) != 0;
     J.fw.ndim = J.rv.ndim = J.fw2.ndim = J.rv2.ndim = ndim;
-    J.fw.tune = fit_tune(J, get_tune(0, ndim));
+    const Tune conf_f = get_tune(0, ndim), conf_r = get_tune(J.op == RTM_OP_STORAGE ? 0 : 1, ndim);
+    J.fw.tune = fit_tune(J, conf_f);
     if (persist) {
         // one strip per workgroup, one step per item
         J.fw.tune.tx = 1;
@@ -754,7 +806,7 @@ int build_job_tables(Job &J)
     if (rc) return rc;
     if (J.op != RTM_OP_MODEL) {
         // the storage reverse pass steps one field, as the forward pass does
-        J.rv.tune = fit_tune(J, get_tune(J.op == RTM_OP_STORAGE ? 0 : 1, ndim));
+        J.rv.tune = fit_tune(J, conf_r);
         if (persist) {
             J.rv.tune.tx = 1;
             J.rv.tune.steps = 1;
@@ -783,20 +835,29 @@ int build_job_tables(Job &J)
         }
     }
     // Multi-step tilings (2-D): the forward one for every op, the reverse
-    // one for imaging (up to three steps) and the gradient (two).
-    // Three steps per launch store the middle level only on the receiver
-    // rows, so storage RTM (which copies whole stored levels) takes two.
+    // one for imaging and the gradient.  Three steps per launch store the
+    // middle level only on the receiver rows, so storage RTM (which copies
+    // whole stored levels) takes two.  The gradient pass takes three where
+    // the runtime chooses the shape and two of a configured one: at 209
+    // registers and two floats per lane its triple only pays with few
+    // wavefronts per SIMD (24 windows: 40.8 us per step with three, 46.6
+    // with two).
     J.fw2 = Tiling{};
     J.rv2 = Tiling{};
     J.fw2.ndim = J.rv2.ndim = ndim;
-    if (ndim == 2 && J.fw.tune.steps >= 2) {
-        J.fw2.tune = J.fw.tune;
-        J.fw2.steps = J.op == RTM_OP_STORAGE ? 2 : J.fw.tune.steps;
+    if (ndim != 2 || persist) return RTM_OK;
+    if (conf_f.steps >= 2) {
+        Tune t = conf_f;
+        if (J.op == RTM_OP_STORAGE) t.steps = 2;
+        J.fw2.tune = fit_multi(J, t, false);
+        J.fw2.steps = J.fw2.tune.steps;
         if ((rc = build_tiling(J, J.fw2, false))) return rc;
     }
-    if (ndim == 2 && (J.op == RTM_OP_RTM || J.op == RTM_OP_VJP) && J.rv.tune.steps >= 2) {
-        J.rv2.tune = J.rv.tune;
-        J.rv2.steps = J.op == RTM_OP_VJP ? 2 : J.rv.tune.steps;  // the gradient pass: two steps at most
+    if ((J.op == RTM_OP_RTM || J.op == RTM_OP_VJP) && conf_r.steps >= 2) {
+        Tune t = conf_r;
+        if (J.op == RTM_OP_VJP && g_tune_exact.load()) t.steps = 2;
+        J.rv2.tune = fit_multi(J, t, true);
+        J.rv2.steps = J.rv2.tune.steps;
         if ((rc = build_tiling(J, J.rv2, true))) return rc;
     }
     return RTM_OK;
@@ -1140,8 +1201,14 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
     }
     if (rs == 3) {
         for (; k >= 2; k -= 3) {
-            RTM_HIP(launch_rev2d_t3(J.rv2.tune.vec, SH(), D.at<Tile2D>(J.ws.tiles_r2), J.rv2.count(), J.rv2.nslots,
-                                    D.at<InjEnt>(J.ws.ents_r2), D.at<Contrib>(J.ws.cont_r2), k, reinject, st));
+            const Tile2D *t2 = D.at<Tile2D>(J.ws.tiles_r2);
+            const InjEnt *e2 = D.at<InjEnt>(J.ws.ents_r2);
+            const Contrib *c2 = D.at<Contrib>(J.ws.cont_r2);
+            if (grad)
+                RTM_HIP(launch_rev2d_t3_grad(J.rv2.tune.vec, SH(), t2, J.rv2.count(), J.rv2.nslots, e2, c2, k, reinject,
+                                             wadj, st));
+            else
+                RTM_HIP(launch_rev2d_t3(J.rv2.tune.vec, SH(), t2, J.rv2.count(), J.rv2.nslots, e2, c2, k, reinject, st));
             cur ^= 1;
         }
     } else if (two) {

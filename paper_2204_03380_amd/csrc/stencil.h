@@ -120,24 +120,8 @@ __device__ __forceinline__ void exchange_row(const float (&c)[VEC], const float 
     }
 }
 
-// Strip-end halo of one row: lane 0 loads the 4 cells left of the strip,
-// lane 63 the 4 cells right of it (zeros past the stored columns); one load
-// instruction for both.
-template <int VEC>
-__device__ __forceinline__ void load_halo(const gfloat *row, int x0, int NX, int lane, float (&hl)[4],
-                                          float (&hr)[4], bool enable = true)
-{
-    // enable = false (a row outside the stored grid): no load, zero halo.
-    const int xr = x0 + 64 * VEC;
-    const bool left = enable && lane == 0, right = enable && lane == 63 && xr < NX + kRadius;
-    f4v t = f4v{0.f, 0.f, 0.f, 0.f};
-    if (left || right) t = *(const gf4v *)(row + (left ? x0 - 4 : xr));
-    hl[0] = left ? t.x : 0.f; hl[1] = left ? t.y : 0.f; hl[2] = left ? t.z : 0.f; hl[3] = left ? t.w : 0.f;
-    hr[0] = right ? t.x : 0.f; hr[1] = right ? t.y : 0.f; hr[2] = right ? t.z : 0.f; hr[3] = right ? t.w : 0.f;
-}
-
-// The same halo in two parts, so that the load can be issued rows before
-// its use: halo_fetch loads the 4 cells beyond the strip's left end (lane 0)
+// Strip-end halo of one row in two parts, so that the load can be issued
+// rows before its use: halo_fetch loads the 4 cells beyond the strip's left end (lane 0)
 // or right end (lane 63) of a row; halo_split hands them out as hl / hr.
 template <int VEC>
 __device__ __forceinline__ f4v halo_fetch(const gfloat *row, int x0, int NX, int lane, bool enable)
@@ -255,45 +239,6 @@ __device__ __forceinline__ void inject_nodes(gfloat *f, const gfloat *Dp, const 
         const InjEnt E = ents[e];
         const int64_t o = (int64_t)E.z * plane + (int64_t)E.y * pitch + E.x;
         f[o] = fmaf(Dp[o], inj_sum(E, cont, sig), f[o]);
-    }
-}
-
-// Inside a wavefront's march: adds Dp * (weighted signal sum) into v at the
-// lane's VEC cells for every entry ents[e ..) of row r (entries sorted by
-// row, each column at most once per row; e advances past them).  The lanes
-// take up to 64 entries at a time and hand each sum to the owning lane
-// through LDS (sv, has: 64 * VEC slots, has zero on entry), instead of every
-// lane walking the list.  The workgroup is this one wavefront, and e and r
-// are uniform, so the barriers are reached by every lane.
-template <int VEC>
-__device__ __forceinline__ void row_inject(const InjEnt *ents, const Contrib *__restrict__ cont, const float *sig,
-                                           int r, int &e, int eend, int xs, int lane, const float (&d)[VEC],
-                                           float (&v)[VEC], float *sv, int *has)
-{
-    if (e >= eend || ents[e].z != r) return;
-    while (true) {
-        const int i = e + lane;
-        const bool mine = i < eend && ents[i].z == r;
-        const unsigned long long m = __ballot(mine);
-        if (mine) {
-            const InjEnt E = ents[i];
-            const int col = E.x - xs;
-            sv[col] = inj_sum(E, cont, sig);
-            has[col] = 1;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-            const int c = lane * VEC + j;
-            if (has[c]) {
-                v[j] = fmaf(d[j], sv[c], v[j]);
-                has[c] = 0;
-            }
-        }
-        __syncthreads();
-        const int n = __popcll(m);
-        e += n;
-        if (n < 64) break;
     }
 }
 

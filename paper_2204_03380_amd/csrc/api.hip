@@ -138,6 +138,8 @@ struct Tune {
     int tx;  // 2-D: wavefronts (adjacent strips) per workgroup
     int steps = 1;  // 2-D: time steps per launch (1, 2 or 3)
     int zin = 0;    // 3-D: tiles numbered with z innermost (else y innermost)
+    int block = 0;  // 2-D multi-step: index of kBlockShapes (0: marching strips)
+    int code() const { return vec | block << 8; }  // as the multi-step launchers take it
 };
 
 // 2-D shapes: ((steps - 1) << 28) | (tx << 24) | (vec << 16) | zseg;
@@ -723,9 +725,35 @@ int best_rows(const Job &J, int steps, int vec, int top, int least)
 // three 26.4 and two at two floats 21.0; 1 shot, two steps, nine rows, two
 // floats 6.6 / 13.2 against one 7.4 / 14.5; 1574 x 534, one float 4.7 / 8.9
 // against two 4.8 / 10.0.
+//
+// Before that, a job of few blocks takes the block kernels, the smallest
+// shape that keeps to its rounds of blocks: two per CU at 1/8/4 (52 and 102
+// registers), one at 2/12/3; 2/16/3 (two blocks per CU forward, one reverse)
+// as long as it beats the strips.  Measured (blocks, then blocks against
+// strips): 1/8/4 465 2.3 / 4.0 against 3.8 / 6.5, 646 2.7 / 5.2; 2/12/3 216
+// 2.5 / 4.9 against 4.0 / 6.9, 300 3.1 / 7.4; 2/16/3 255 2.95 / 6.1 against
+// 4.6 / 8.8, 418 4.1 / 9.9 against 6.4 / 11.9, 616 5.3 / 14.0 against 6.6 /
+// 13.0, 1232 7.9 / 23.3 against 10.8 / 20.8, 3696 20.3 against 22.8, 4928
+// 32.3 against 30.0.
+int fit_block(const Job &J, int steps, bool reverse)
+{
+    const int64_t most[] = {0, 512, 256, reverse ? 512 : 3700};
+    for (int i = 1; i < 4; ++i) {
+        const BlockShape &b = kBlockShapes[i];
+        if (count_multi(J, steps, b.vec, b.waves * b.rows - 8 * (steps - 1)) <= most[i]) return i;
+    }
+    return 0;
+}
+
 Tune fit_multi(const Job &J, Tune t, bool reverse)
 {
     if (g_tune_exact.load()) return t;
+    if ((t.block = fit_block(J, t.steps, reverse)) != 0) {
+        const BlockShape &b = kBlockShapes[t.block];
+        t.vec = b.vec;
+        t.zseg = b.waves * b.rows - 8 * (t.steps - 1);
+        return t;
+    }
     const int least = reverse && t.steps == 3 ? 27 : 18;
     if (count_multi(J, t.steps, t.vec, std::min(t.zseg, least)) >= (reverse ? 2048 : 1900)) {
         t.zseg = best_rows(J, t.steps, t.vec, t.zseg, least);
@@ -1102,7 +1130,7 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
             // steps n .. n + 2 per launch; each launch records d^{n-2},
             // d^{n-1}, d^n (no stored levels: not for storage RTM)
             for (; n + 3 <= nt; n += 3) {
-                RTM_HIP(launch_fwd2d_t3(J.fw2.tune.vec, SH(), D.at<Tile2D>(J.ws.tiles_f2), J.fw2.count(),
+                RTM_HIP(launch_fwd2d_t3(J.fw2.tune.code(), SH(), D.at<Tile2D>(J.ws.tiles_f2), J.fw2.count(),
                                         J.fw2.nslots, D.at<InjEnt>(J.ws.ents_f2), D.at<Contrib>(J.ws.cont_f2),
                                         sample ? stasks : nullptr, nsample, n, st));
                 cur ^= 1;
@@ -1117,7 +1145,7 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
             // steps n, n + 1 per launch; each launch records d^{n-1}, d^n
             for (; n + 2 <= nt; n += 2) {
                 if ((rc = keep(n))) return rc;
-                RTM_HIP(launch_fwd2d_t2(J.fw2.tune.vec, SH(), D.at<Tile2D>(J.ws.tiles_f2), J.fw2.count(),
+                RTM_HIP(launch_fwd2d_t2(J.fw2.tune.code(), SH(), D.at<Tile2D>(J.ws.tiles_f2), J.fw2.count(),
                                         J.fw2.nslots, D.at<InjEnt>(J.ws.ents_f2), D.at<Contrib>(J.ws.cont_f2),
                                         sample ? stasks : nullptr, nsample, n, st));
                 cur ^= 1;
@@ -1205,15 +1233,15 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
             const InjEnt *e2 = D.at<InjEnt>(J.ws.ents_r2);
             const Contrib *c2 = D.at<Contrib>(J.ws.cont_r2);
             if (grad)
-                RTM_HIP(launch_rev2d_t3_grad(J.rv2.tune.vec, SH(), t2, J.rv2.count(), J.rv2.nslots, e2, c2, k, reinject,
+                RTM_HIP(launch_rev2d_t3_grad(J.rv2.tune.code(), SH(), t2, J.rv2.count(), J.rv2.nslots, e2, c2, k, reinject,
                                              wadj, st));
             else
-                RTM_HIP(launch_rev2d_t3(J.rv2.tune.vec, SH(), t2, J.rv2.count(), J.rv2.nslots, e2, c2, k, reinject, st));
+                RTM_HIP(launch_rev2d_t3(J.rv2.tune.code(), SH(), t2, J.rv2.count(), J.rv2.nslots, e2, c2, k, reinject, st));
             cur ^= 1;
         }
     } else if (two) {
         for (; k >= 1; k -= 2) {
-            RTM_HIP(launch_rev2d_t2(J.rv2.tune.vec, grad, SH(), D.at<Tile2D>(J.ws.tiles_r2), J.rv2.count(),
+            RTM_HIP(launch_rev2d_t2(J.rv2.tune.code(), grad, SH(), D.at<Tile2D>(J.ws.tiles_r2), J.rv2.count(),
                                     J.rv2.nslots, D.at<InjEnt>(J.ws.ents_r2), D.at<Contrib>(J.ws.cont_r2), k, reinject,
                                     wadj, st));
             cur ^= 1;

@@ -81,6 +81,15 @@ struct ShotDev {
     Layout L;
 };
 
+// Shapes of the 2-D block kernels (several time steps per launch, small
+// jobs): floats per lane, wavefronts per block, rows per wavefront.  The
+// multi-step launchers take floats per lane | (index << 8); index 0 is the
+// marching strips.
+struct BlockShape {
+    int vec, waves, rows;
+};
+constexpr BlockShape kBlockShapes[] = {{0, 0, 0}, {1, 8, 4}, {2, 12, 3}, {2, 16, 3}};
+
 // A 2-D stencil tile: one wavefront marches down rows [z0, z1) of a strip
 // of 64 * VEC columns starting at x0; z1 - z0 is a multiple of kZUnroll
 // (rows at or below NZ are zero halo rows and stay zero).  Injection entries

@@ -28,12 +28,20 @@
 // (forward 156.7 -> 149.9 us per step, reverse 413.7 -> 413.4).  With fewer
 // than about four wavefronts per SIMD each row waits for its own loads, so
 // P = 3 loads them three march steps ahead into a ring of registers
-// (16 shots, forward: 64.3 -> 52.7 us per step, 55.3 without the ring;
-// 1574 x 534, one shot: forward 7.1 -> 4.7, reverse 11.0 -> 8.9; the
-// gradient of 12 windows: 24.8 -> 19.4).
+// (16 shots, forward: 64.3 -> 52.7 us per step, 55.3 without the ring; 2
+// shots, reverse: 25.9 -> 20.6; the gradient of 12 windows: 24.8 -> 19.4).
+// Jobs of few blocks take the block kernels (prop2d_block.hip) instead.
 #include "multi2d.h"
 
 namespace rtm {
+// prop2d_block.hip
+hipError_t launch_fwd2d_block(int shape, int steps, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+                              const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
+                              hipStream_t st);
+hipError_t launch_rev2d_block(int shape, int steps, bool grad, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+                              const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj,
+                              hipStream_t st);
+
 namespace {
 
 template <int VEC, int C>
@@ -728,6 +736,8 @@ hipError_t launch_fwd2d_t2(int vec, const ShotDev *shots, const Tile2D *tiles, i
                            const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
                            hipStream_t st)
 {
+    if (vec >> 8)
+        return launch_fwd2d_block(vec >> 8, 2, shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st);
 #define RTM_CALL(V) fwd_launch<V, 2>(shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
@@ -737,6 +747,8 @@ hipError_t launch_fwd2d_t3(int vec, const ShotDev *shots, const Tile2D *tiles, i
                            const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
                            hipStream_t st)
 {
+    if (vec >> 8)
+        return launch_fwd2d_block(vec >> 8, 3, shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st);
 #define RTM_CALL(V) fwd_launch<V, 3>(shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
@@ -745,6 +757,8 @@ hipError_t launch_fwd2d_t3(int vec, const ShotDev *shots, const Tile2D *tiles, i
 hipError_t launch_rev2d_t2(int vec, bool grad, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj, hipStream_t st)
 {
+    if (vec >> 8)
+        return launch_rev2d_block(vec >> 8, 2, grad, shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);
 #define RTM_CALL(V)                                                                                          \
     if (grad)                                                                                                \
         rev_launch<V, 2, true>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);              \
@@ -757,6 +771,8 @@ hipError_t launch_rev2d_t2(int vec, bool grad, const ShotDev *shots, const Tile2
 hipError_t launch_rev2d_t3(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, int k, int reinject, hipStream_t st)
 {
+    if (vec >> 8)
+        return launch_rev2d_block(vec >> 8, 3, false, shots, tiles, ntiles, nslots, ents, cont, k, reinject, nullptr, st);
 #define RTM_CALL(V) rev_launch<V, 3, false>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, nullptr, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
@@ -766,6 +782,8 @@ hipError_t launch_rev2d_t3_grad(int vec, const ShotDev *shots, const Tile2D *til
                                 const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj,
                                 hipStream_t st)
 {
+    if (vec >> 8)
+        return launch_rev2d_block(vec >> 8, 3, true, shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);
 #define RTM_CALL(V) rev_launch<V, 3, true>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL

@@ -99,3 +99,39 @@ def test_many_tiles(shots, steps):
     want = run()
     _shape(True, steps, 1, 9)
     _same(want, run())
+
+
+# the block kernels' three shapes (small jobs): edges of the 48 x 16, 112 x 20
+# and 112 x 32 cells a block of three steps owns (56 x 24, 120 x 28 and
+# 120 x 40 with two), more receiver nodes in a block than it has threads, all
+# wavefronts of the last block idle but one
+@pytest.mark.parametrize("nx,nz,nb,nt,rows", [(1, 1, 0, 3, 1), (48, 16, 0, 6, 3), (49, 17, 0, 7, 3), (57, 47, 4, 8, 24),
+                                              (800, 450, 40, 7, 2), (785, 460, 0, 9, 1), (1121, 512, 0, 6, 1),
+                                              (1100, 513, 10, 8, 3), (2000, 600, 50, 7, 1)])
+def test_block_kernels(nx, nz, nb, nt, rows):
+    shot, d = _shot(nx, nz, nb, nt, rows=rows)
+    _shape(True, 1)
+    want = _all(shot, d)
+    for steps in (2, 3):
+        _shape(False, steps)
+        _same(want, _all(shot, d))
+
+
+def test_block_kernels_uneven_batch():
+    """Blocks of several shots of different grids in one launch."""
+    shots = [_shot(nx, nz, 5, 8, rows=2, seed=i) for i, (nx, nz) in enumerate([(90, 61), (201, 30), (33, 140)])]
+
+    def run():
+        tr = [torch.zeros_like(d) for _, d in shots]
+        im = [torch.zeros(s["grid"].interior_shape, device=DEV) for s, _ in shots]
+        gv = [torch.zeros(s["grid"].padded_shape, device=DEV) for s, _ in shots]
+        keys = ("grid", "v_pad", "wavelet", "src", "rec")
+        for op, kw in ((rtm.RTM_OP_MODEL, lambda i: dict(traces_out=tr[i])),
+                       (rtm.RTM_OP_RTM, lambda i: dict(traces_in=shots[i][1], image=im[i])),
+                       (rtm.RTM_OP_VJP, lambda i: dict(traces_in=shots[i][1], grad_v_pad=gv[i]))):
+            rtm.BatchPlan(op, [rtm.BatchShot(*(s[k] for k in keys), **kw(i)) for i, (s, _) in enumerate(shots)], 1e-3, 8).run()
+        return {f"{n}{i}": t for n, ts in (("traces", tr), ("image", im), ("grad", gv)) for i, t in enumerate(ts)}
+    _shape(True, 1)
+    want = run()
+    _shape(False, 3)
+    _same(want, run())

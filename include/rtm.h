@@ -170,16 +170,17 @@ int rtm_set_steps_per_launch(int op, int steps);
 int rtm_get_steps_per_launch(int op, int *steps);
 
 /* Launch shape of the 3-D kernels: vec floats per lane (x strips of
- * 64 * vec cells), ty in {4, 8, 16} wavefronts per workgroup (rows in y),
- * zseg planes per tile (a multiple of 9).  ty 16 (1024-thread workgroups)
- * takes vec 1 or 2 for RTM_OP_MODEL and vec 1 for RTM_OP_RTM / RTM_OP_VJP.
- * Same rules as rtm_set_tuning. */
+ * 64 * vec cells), ty in {4, 8, 16} rows in y per workgroup, zseg planes per
+ * tile (a multiple of 9).  ty 16 takes vec 1 or 2 for RTM_OP_MODEL and vec 1
+ * for RTM_OP_RTM / RTM_OP_VJP.  A job takes tiles of at most this size, fewer
+ * planes (or rows, or floats) where that is faster, unless RTM_TUNE_EXACT is
+ * set.  Same rules as rtm_set_tuning. */
 int rtm_set_tuning3d(int op, int vec, int ty, int zseg);
 int rtm_get_tuning3d(int op, int *vec, int *ty, int *zseg);
 
 /* Numbering of the 3-D tiles, process-wide per operation (RTM_OP_MODEL: the
  * forward kernels; RTM_OP_RTM / RTM_OP_VJP: the reverse ones): z_inner 0
- * (default) numbers them z band by z band with the y tiles innermost,
+ * (default) numbers them z band by z band with the x strips innermost,
  * z_inner 1 x strip by x strip with the z bands innermost.  Workgroups are
  * dealt to the XCDs in that order, so it decides which tiles share an L2;
  * results do not depend on it (every cell's arithmetic is the same).  The

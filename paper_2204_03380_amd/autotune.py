@@ -29,7 +29,8 @@ DEFAULT_SHAPES = (tuple((3, v, 1, z) for v in (1, 2, 4) for z in (54, 108, 216))
                   tuple((2, v, 1, z) for v in (2, 4) for z in (36, 108)) +
                   tuple((1, v, x, z) for v in (1, 2, 4) for x in (1, 4) for z in (18, 36)))
 DEFAULT_SHAPES_3D = tuple((v, y, z, o) for v, y, z in ((1, 4, 18), (1, 8, 18), (2, 8, 18), (1, 4, 36), (2, 8, 36),
-                                                      (4, 8, 18), (1, 16, 18), (2, 16, 36))
+                                                      (4, 8, 18), (1, 16, 18), (2, 16, 36), (2, 8, 9), (2, 16, 72),
+                                                      (1, 8, 54))
                           for o in (0, 1))
 
 

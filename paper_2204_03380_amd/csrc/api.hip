@@ -134,12 +134,13 @@ namespace {
 struct Tune {
     int vec;
     int zseg;
-    int ty;  // 3-D: wavefronts (y rows) per workgroup
+    int ty;  // 3-D: y rows per workgroup
     int tx;  // 2-D: wavefronts (adjacent strips) per workgroup
     int steps = 1;  // 2-D: time steps per launch (1, 2 or 3)
-    int zin = 0;    // 3-D: tiles numbered with z innermost (else y innermost)
+    int zin = 0;    // 3-D: tiles numbered with z innermost (else x innermost)
     int block = 0;  // 2-D multi-step: index of kBlockShapes (0: marching strips)
-    int code() const { return vec | block << 8; }  // as the multi-step launchers take it
+    int once = 0;   // 3-D: kOnce3D, or 0
+    int code() const { return vec | block << 8 | once; }  // as the multi-step and 3-D launchers take it
 };
 
 // 2-D shapes: ((steps - 1) << 28) | (tx << 24) | (vec << 16) | zseg;
@@ -153,11 +154,13 @@ std::atomic<int> g_tune2d_rev{(2 << 28) | (1 << 24) | (2 << 16) | 108};
 std::atomic<int> g_tune_exact{0};  // 1: never narrow the configured shapes
 std::atomic<double> g_persist_wait_ms{4000.0};  // bounded wait of persistent passes
 
-// 3-D shapes: (vec << 24) | (ty << 16) | (z_inner << 15) | zseg; defaults from a sweep on
-// the 612 x 612 x 356 padded layered-salt grid (us per step: forward 556 at
-// vec 1, 4 rows, 18 planes against 575 at vec 2, 8 rows; reverse 1353).
-std::atomic<int> g_tune3d_fwd{(1 << 24) | (4 << 16) | 18};
-std::atomic<int> g_tune3d_rev{(1 << 24) | (4 << 16) | 18};
+// 3-D shapes: (vec << 24) | (ty << 16) | (z_inner << 15) | zseg: the largest
+// tiles that fit_tune3 chooses from; defaults from sweeps over 64^3 to 512 x
+// 512 x 256 grids (612 x 612 x 356 padded, us per step: forward, 2 floats x
+// 16 rows 442, 2 x 8 466, 1 x 8 485; reverse, 1 x 8 1096, 1 x 16 1108, 2 x 8
+// 1112, 1 x 4 1142).
+std::atomic<int> g_tune3d_fwd{(2 << 24) | (16 << 16) | 126};
+std::atomic<int> g_tune3d_rev{(1 << 24) | (8 << 16) | 54};
 
 Tune get_tune(int which, int ndim)
 {
@@ -492,20 +495,23 @@ int build_tiling(Job &J, Tiling &T, bool with_receivers)
         const int nys = T.ndim == 3 ? (g.NY + ty - 1) / ty : 1;
         const int nzs = (NZr + T.tune.zseg - 1) / T.tune.zseg;
         const int tbase = T.count();
-        // Tiles are numbered band by band in z, strip by strip within a band
-        // and (3-D) y tile by y tile within a strip, so that the workgroups
-        // that share lines run back to back on one XCD: adjacent 2-D strips
-        // share their strip-end columns (measured 3-7 % faster than strip by
-        // strip), adjacent 3-D y tiles the 4-row halos above and below.  A
-        // 3-D tuning may number them z innermost instead (x strip, then y
-        // tile, then z band), which some grids prefer (the better order
-        // depends on the grid: measured, not derived).
+        // Tiles are numbered band by band in z, row of tiles by row of tiles
+        // within a band (3-D) and strip by strip within a row, so that the
+        // workgroups that share lines run back to back on one XCD: adjacent
+        // strips share their strip-end columns (2-D: measured 3-7 % faster
+        // than strip by strip), adjacent 3-D y tiles the 4-row halos above
+        // and below.  In 3-D an XCD then works on whole rows of a few y tiles;
+        // with y innermost its neighbour strips were on other XCDs and every
+        // strip-end line came from memory twice (612 x 612 x 356 cells, us
+        // per step: forward 545 -> 520, reverse 1353 -> 1250).  A 3-D tuning
+        // may number them z innermost instead (x strip, then y tile, then z
+        // band).
         const bool zin = T.ndim == 3 && T.tune.zin;
-        const int nA = zin ? ns : nzs, nB = zin ? nys : ns, nC = zin ? nzs : nys;
+        const int nA = zin ? ns : nzs, nB = nys, nC = zin ? nzs : ns;
         for (int ia = 0; ia < nA; ++ia)
-            for (int ib = 0; ib < nB; ++ib)
+            for (int ys = 0; ys < nB; ++ys)
                 for (int ic = 0; ic < nC; ++ic) {
-                    const int zs = zin ? ic : ia, xs = zin ? ia : ib, ys = zin ? ib : ic;
+                    const int zs = zin ? ic : ia, xs = zin ? ia : ic;
                     const int z0 = zs * T.tune.zseg, z1 = std::min(z0 + T.tune.zseg, NZr);
                     if (T.ndim == 3) {
                         Tile3D t{};
@@ -527,7 +533,7 @@ int build_tiling(Job &J, Tiling &T, bool with_receivers)
         // (2-D multi-step: x is an owned column)
         auto tile_of = [&](int z, int y, int x) {
             if (zin) return tbase + ((x / strip) * nys + y / ty) * nzs + z / T.tune.zseg;
-            return tbase + ((z / T.tune.zseg) * ns + x / strip) * nys + (T.ndim == 3 ? y / ty : 0);
+            return tbase + ((z / T.tune.zseg) * nys + (T.ndim == 3 ? y / ty : 0)) * ns + x / strip;
         };
         PointOp sp;
         if (!make_point(g, S.src, &sp))
@@ -648,25 +654,99 @@ int build_tiling(Job &J, Tiling &T, bool with_receivers)
     return RTM_OK;
 }
 
-// Wavefronts a launch shape gives a job.
+// Wavefronts a 2-D shape of one step per launch gives a job.
 int64_t count_tiles(const Job &J, Tune t)
 {
     int64_t n = 0;
-    for (const ShotIn &S : J.shots) {
-        const int64_t ny = S.g.ndim == 3 ? (S.g.NY + t.ty - 1) / t.ty * t.ty : 1;  // wavefronts per column
-        const int64_t wx = S.g.ndim == 2 ? t.tx : 1;                                   // wavefronts per strip group
-        n += (int64_t)((S.g.NX + 64 * t.vec * wx - 1) / (64 * t.vec * wx)) * wx * ny *
+    for (const ShotIn &S : J.shots)
+        n += (int64_t)((S.g.NX + 64 * t.vec * t.tx - 1) / (64 * t.vec * t.tx)) * t.tx *
              ((S.g.L.NZr + t.zseg - 1) / t.zseg);
-    }
     return n;
 }
 
-// The configured shape is meant for large batches; a small job (a single
-// shot of a modest grid) would leave most of the 256 CUs idle, so the shape
-// is narrowed (fewer rows per tile first, then fewer floats per lane) until
-// the job has at least kMinWaves wavefronts or the smallest shape is
-// reached.  Results do not depend on the shape.  (One step per launch; the
-// 2-D multi-step shape is chosen by fit_multi.)
+// Workgroups a 3-D shape gives a job.
+int64_t count_tiles3(const Job &J, Tune t)
+{
+    int64_t n = 0;
+    for (const ShotIn &S : J.shots)
+        n += (int64_t)((S.g.NX + 64 * t.vec - 1) / (64 * t.vec)) * ((S.g.NY + t.ty - 1) / t.ty) *
+             ((S.g.L.NZr + t.zseg - 1) / t.zseg);
+    return n;
+}
+
+// Shape of a 3-D pass, no larger than the configured one.
+//
+// once: a step's arrays beyond 7/8 of the 256 MiB memory-side cache come from
+// HBM whatever is done, and then the L2 serves the shared halo rows better
+// without the arrays that are touched once; smaller ones live in that cache
+// (us per step with / without: 612 x 612 x 356 cells forward 442 / 527,
+// reverse 1096 / 1251; 252^3 reverse, 353 MB, 122 / 137; 220^3 reverse,
+// 245 MB, 91 / 94; 252^3 forward, 192 MB, 53 / 50; 188^3 reverse, 150 MB,
+// 55 / 53).
+//
+// Width and rows: the configured ones where the arrays exceed that cache
+// (fewer halo rows read); else a forward step is quicker in 8-row tiles
+// (156^3, 2 floats: 17.9 against 23.6 us; 188^3: 24.4 against 28.5), a
+// receiver step at one float (188 x 188 x 160: 26.7 against 30.6).
+//
+// Planes per tile, for the forward and receiver kernels: the least march
+// time.  A tile marches 8 planes beyond its own, and the fullest CU ends the
+// launch: one workgroup of 16 wavefronts fills a CU, smaller ones share it,
+// k of them taking about 1.2 + k units (501 x 501 x 235 cells, one / two /
+// 2.5 workgroups of 16 per CU: 203 / 208 / 241 us per step; 612 x 612 x 356
+// at 72 planes, 3.8 per CU, 442, at 90, 3.05, 508; 96^3 at 9 and 18 planes
+// 10.4 and 15.8).  The reverse kernel, at two rows per wavefront, stays near
+// its memory time at any height that leaves enough workgroups (316^3 at 9 to
+// 81 planes 264 to 292); on arrays that fit the cache the same march rule
+// holds, with a floor for what a lone workgroup takes per plane (188^3 at 9,
+// 18, 27, 36 planes 53.1, 58.5, 48.1, 56.2).
+enum Pass3 { kFwd3, kRecv3, kRev3 };
+constexpr int64_t kCacheBytes = (int64_t)224 << 20;
+
+Tune fit_tune3(const Job &J, Tune t, Pass3 pass)
+{
+    int64_t bytes = 0;
+    int NZr = 0, NX = 0;
+    for (const ShotIn &S : J.shots) {
+        const int64_t all = 4 * (int64_t)S.g.NX * S.g.NY * S.g.L.NZ, in = 4 * (int64_t)S.g.nx * S.g.ny * S.g.nz;
+        bytes += pass != kRev3 ? 3 * all : J.op == RTM_OP_VJP ? 6 * all : 5 * all + 2 * in;
+        NZr = std::max(NZr, S.g.L.NZr);
+        NX = std::max(NX, S.g.NX);
+    }
+    t.once = bytes > kCacheBytes ? kOnce3D : 0;
+    if (g_tune_exact.load()) return t;
+    if (NX <= 64) t.vec = 1;  // half the lanes would be idle
+    if (!t.once && t.ty == 16 && t.vec > 1) {
+        if (pass == kRecv3) t.vec = 1;
+        else t.ty = 8;
+    }
+    const bool full = t.ty * t.vec >= 32;  // workgroups that fill a CU
+    const int top = t.zseg;
+    double least = 0.0;
+    for (int seg = 1; seg <= NZr / kZUnroll; ++seg) {
+        Tune c = t;
+        c.zseg = (NZr / kZUnroll + seg - 1) / seg * kZUnroll;
+        if (c.zseg > top || (least != 0.0 && c.zseg == t.zseg)) continue;
+        const double n = (double)count_tiles3(J, c) / 256.0;  // workgroups per CU
+        double cost;
+        if (pass != kRev3) cost = full ? (c.zseg + 8) * std::ceil(n) : (c.zseg + 6) * (1.2 + (n > 4.0 ? n : std::ceil(n)));
+        else if (!t.once) cost = (c.zseg + 8) * std::max(1.13, 0.5 + 0.22 * (n + std::ceil(n)));
+        else cost = n >= 16.0 && c.zseg > kMinZseg ? 1.0 : 2.0 + c.zseg;  // the tallest that leaves 16 per CU
+        if (least == 0.0 || cost < least) {
+            least = cost;
+            t.zseg = c.zseg;
+        }
+    }
+    t.zseg = std::min(t.zseg, top);
+    return t;
+}
+
+// The configured 2-D shape of one step per launch is meant for large
+// batches; a small job (a single shot of a modest grid) would leave most of
+// the 256 CUs idle, so the shape is narrowed (fewer rows per tile first, then
+// fewer floats per lane) until the job has at least kMinWaves wavefronts or
+// the smallest shape is reached.  Results do not depend on the shape.  (The
+// multi-step shape is chosen by fit_multi.)
 constexpr int64_t kMinWaves = 256 * 16;
 
 Tune fit_tune(const Job &J, Tune t)
@@ -674,7 +754,6 @@ Tune fit_tune(const Job &J, Tune t)
     if (g_tune_exact.load()) return t;
     while (count_tiles(J, t) < kMinWaves) {
         if (t.zseg > kMinZseg) t.zseg = std::max(kMinZseg, t.zseg / 2 / kZUnroll * kZUnroll);
-        else if (t.ty > 4) t.ty = 4;
         else if (t.vec > 1) t.vec /= 2;
         else break;
     }
@@ -824,7 +903,7 @@ int build_job_tables(Job &J)
     const bool persist = (J.flags & RTM_F_PERSISTENT) != 0;
     J.fw.ndim = J.rv.ndim = J.fw2.ndim = J.rv2.ndim = ndim;
     const Tune conf_f = get_tune(0, ndim), conf_r = get_tune(J.op == RTM_OP_STORAGE ? 0 : 1, ndim);
-    J.fw.tune = fit_tune(J, conf_f);
+    J.fw.tune = ndim == 3 ? fit_tune3(J, conf_f, kFwd3) : fit_tune(J, conf_f);
     if (persist) {
         // one strip per workgroup, one step per item
         J.fw.tune.tx = 1;
@@ -834,7 +913,7 @@ int build_job_tables(Job &J)
     if (rc) return rc;
     if (J.op != RTM_OP_MODEL) {
         // the storage reverse pass steps one field, as the forward pass does
-        J.rv.tune = fit_tune(J, conf_r);
+        J.rv.tune = ndim == 3 ? fit_tune3(J, conf_r, J.op == RTM_OP_STORAGE ? kRecv3 : kRev3) : fit_tune(J, conf_r);
         if (persist) {
             J.rv.tune.tx = 1;
             J.rv.tune.steps = 1;
@@ -1157,7 +1236,7 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
         for (; n < nt; ++n) {
             if ((rc = keep(n))) return rc;
             if (J.fw.ndim == 3)
-                RTM_HIP(launch_fwd3d(J.fw.tune.vec, J.fw.tune.ty, SH(), (const Tile3D *)tiles, ntiles, J.fw.nslots,
+                RTM_HIP(launch_fwd3d(J.fw.tune.code(), J.fw.tune.ty, SH(), (const Tile3D *)tiles, ntiles, J.fw.nslots,
                                      ents, cont, sample ? stasks : nullptr, nsample, n, st));
             else
                 RTM_HIP(launch_fwd2d(J.fw.tune.vec, J.fw.tune.tx, SH(), tiles, ntiles, J.fw.nslots, ents, cont,
@@ -1197,7 +1276,7 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
             const bool stored = k >= S.phase && (k - S.phase) % S.stride == 0;
             const float *snap = stored ? S.snaps + (int64_t)((k - S.phase) / S.stride) * ncell : nullptr;
             if (J.rv.ndim == 3)
-                RTM_HIP(launch_recv3d(J.rv.tune.vec, J.rv.tune.ty, SH(), (const Tile3D *)tiles, ntiles, J.rv.nslots,
+                RTM_HIP(launch_recv3d(J.rv.tune.code(), J.rv.tune.ty, SH(), (const Tile3D *)tiles, ntiles, J.rv.nslots,
                                       ents, cont, k, snap, st));
             else
                 RTM_HIP(launch_recv2d(J.rv.tune.vec, J.rv.tune.tx, SH(), tiles, ntiles, J.rv.nslots, ents, cont, k,
@@ -1249,7 +1328,7 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
     }
     for (; k >= 0; --k) {
         if (J.rv.ndim == 3)
-            RTM_HIP(launch_rev3d(J.rv.tune.vec, J.rv.tune.ty, grad, SH(), (const Tile3D *)tiles, ntiles, J.rv.nslots,
+            RTM_HIP(launch_rev3d(J.rv.tune.code(), J.rv.tune.ty, grad, SH(), (const Tile3D *)tiles, ntiles, J.rv.nslots,
                                  ents, cont, k, reinject, wadj, st));
         else
             RTM_HIP(launch_rev2d(J.rv.tune.vec, J.rv.tune.tx, grad, SH(), tiles, ntiles, J.rv.nslots, ents, cont, k,

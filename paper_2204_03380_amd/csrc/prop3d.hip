@@ -1,226 +1,325 @@
 // 3-D propagation kernels for gfx950.
 //
-// A workgroup of TY wavefronts owns a tile of 64 * VEC x cells by TY rows in
-// y and marches down z over [z0, z1) (a multiple of the 9-plane register
-// queue).  Wavefront w holds row y0 + w:
-//  - z-neighbours come from its register queue of planes z-4 .. z+4;
-//  - x-neighbours from the adjacent lanes through DPP (plus the 4-cell strip
-//    halo from one extra load by lanes 0 and 63);
-//  - y-neighbours from an LDS copy of the centre plane z: every wavefront
-//    writes its row there and the first ones load the 4 + 4 halo rows of the
-//    tile.  The copy is double-buffered, so one barrier per plane suffices.
+// A workgroup of TY wavefronts owns a tile of 64 * VEC x cells by TY * RW rows
+// in y and marches down z over [z0, z1) (a multiple of the 9-plane register
+// queue).  Wavefront w holds the RW rows from y0 + w RW on:
+//  - z-neighbours come from its register queues of planes z-4 .. z+4;
+//  - x-neighbours from the adjacent lanes through DPP, with the 4 + 4 cells
+//    beyond the strip ends of all RW rows loaded by one instruction (8 RW
+//    lanes) and handed to lanes 0 and 63 through LDS;
+//  - y-neighbours from its own rows and, beyond them, from an LDS copy of the
+//    centre plane z: every wavefront writes its rows there and the tile's
+//    4 + 4 halo rows.  The copy is double-buffered, so one barrier per plane
+//    suffices.
+// Everything a plane needs from memory (queue rows of plane z + 4, older
+// level, D', halos, imaging sums) is loaded one plane ahead in one batch:
+// loads return in order, so a load issued and awaited inside the plane would
+// also wait for the whole batch behind it.
+//
+// Bound: memory traffic.  A forward step must move four arrays, a reverse one
+// seven and the imaging sums twice; 612 x 612 x 356 cells (533 MB an array)
+// took 581 us (5.6 TB/s with 4.9 arrays read for 3) and 1365 us, of which the
+// x-innermost tile order (whole rows of tiles on one XCD) took 25 and 103 us,
+// non-temporal access to what a step touches once 22 and 85, and wider and
+// taller tiles the rest: now 442 and 1096 us, 4.8 and 4.4 TB/s of what must be
+// moved.  501 x 501 x 235: forward 289 -> 203, receiver 325 -> 231; 188^3, in
+// the memory-side cache: 25.8 -> 24.4 and 61.1 -> 48.1 us.  Two rows per
+// wavefront share y-neighbours and halo loads in the reverse kernel, which is
+// short of registers for more wavefronts (188^3: 8 rows as 4 x 2 49.6, as
+// 8 x 1 57.6 us).
 // Stencil, update and injection follow the 2-D kernels (difference form that
 // is exactly zero on constant fields; source and receiver terms added after
 // the march by the lanes that stored the cells).
-#include "stencil.h"
+#include "multi2d.h"
 
 namespace rtm {
 namespace {
 
-template <int VEC, int TY>
-struct Lds {
-    float row[2][TY + 8][64 * VEC];
-};
+typedef __attribute__((address_space(4))) const Tile3D Tile3Entry;
+
+// Access to values that this launch touches once (older level, D', imaging
+// sums).  NT leaves them out of the way in the L2, whose lines then last
+// until the neighbouring tiles have read the halo rows they share.
+template <int VEC, bool NT>
+__device__ __forceinline__ void ld_once(const gfloat *p, float (&v)[VEC])
+{
+    if constexpr (!NT) {
+        ldv<VEC>(p, v);
+    } else if constexpr (VEC == 4) {
+        const f4v t = __builtin_nontemporal_load((const gf4v *)p);
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    } else if constexpr (VEC == 2) {
+        const f2v t = __builtin_nontemporal_load((const gf2v *)p);
+        v[0] = t.x; v[1] = t.y;
+    } else {
+        v[0] = __builtin_nontemporal_load(p);
+    }
+}
+
+template <int VEC, bool NT>
+__device__ __forceinline__ void st_once(gfloat *p, const float (&v)[VEC])
+{
+    if constexpr (!NT)
+        stv<VEC>(p, v);
+    else if constexpr (VEC == 4)
+        __builtin_nontemporal_store(f4v{v[0], v[1], v[2], v[3]}, (gf4v *)p);
+    else if constexpr (VEC == 2)
+        __builtin_nontemporal_store(f2v{v[0], v[1]}, (gf2v *)p);
+    else
+        __builtin_nontemporal_store(v[0], p);
+}
 
 // Number of y-halo rows a wave loads per plane (8 halo rows over TY waves).
 template <int TY>
 constexpr int halo_per_wave() { return (8 + TY - 1) / TY; }
 
-// Everything one field needs from memory for one plane of one row, loaded
-// one plane ahead (software pipelining across the per-plane barrier).
-template <int VEC, int TY>
-struct FieldNext {
-    float q[VEC];                         // row z + 4 of the register queue
-    float halo[halo_per_wave<TY>()][VEC];  // this wave's y-halo rows of plane z
-    f4v hv;                               // strip-end x-halo (lanes 0 and 63)
+template <int VEC, int TY, int RW>
+struct Lds {
+    float row[2][TY * RW + 8][64 * VEC];
+    __attribute__((aligned(16))) float ends[2][TY][RW * 8];  // strip-end cells of each row: 4 left, 4 right
 };
 
-template <int VEC>
-struct Ctx3 {
-    int64_t pitch, plane;
-    int x, x0, y, y0, NX, NY, lane, w;
-    bool liveX, live, own, rowlive;
-};
-
-// Issues the loads of field f for plane z (queue row z + 4, y-halo rows and
-// x-halo of plane z).
-template <int VEC, int TY>
-__device__ __forceinline__ void field_prefetch(const Ctx3<VEC> &C, const gfloat *f, int z, FieldNext<VEC, TY> &nx)
+// Per lane: bit i set where `lane_in` and row y + i lies in [lo, hi).  Kept in
+// a vector register: the compiler would otherwise copy the whole march for
+// either value of each (uniform) row test.
+template <int RW>
+__device__ __forceinline__ unsigned row_mask(int y, int lo, int hi, bool lane_in)
 {
-    const gfloat *pz = f + (int64_t)z * C.plane;
+    unsigned m = 0;
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) nx.q[j] = 0.f;
-    if (C.live) ldv<VEC>(pz + 4 * C.plane + (int64_t)C.y * C.pitch + C.x, nx.q);
-#pragma unroll
-    for (int i = 0; i < halo_per_wave<TY>(); ++i) {
-        const int h = C.w + i * TY;
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) nx.halo[i][j] = 0.f;
-        if (h < 8) {
-            const int yh = h < 4 ? C.y0 - 4 + h : C.y0 + TY + (h - 4);
-            if (C.liveX && yh < C.NY + kRadius) ldv<VEC>(pz + (int64_t)yh * C.pitch + C.x, nx.halo[i]);
-        }
-    }
-    const int xr = C.x0 + 64 * VEC;
-    const bool left = C.rowlive && C.lane == 0, right = C.rowlive && C.lane == 63 && xr < C.NX + kRadius;
-    nx.hv = f4v{0.f, 0.f, 0.f, 0.f};
-    if (left || right) nx.hv = *(const gf4v *)(pz + (int64_t)C.y * C.pitch + (left ? C.x0 - 4 : xr));
+    for (int i = 0; i < RW; ++i) m |= lane_in && y + i >= lo && y + i < hi ? 1u << i : 0u;
+    return here(m);
 }
 
-// Writes the centre row (queue slot of plane z) and the y-halo rows into
-// LDS buffer `buf`; returns the x-halo split into left / right.
-template <int VEC, int TY>
-__device__ __forceinline__ void field_publish(const Ctx3<VEC> &C, Lds<VEC, TY> &L, int buf, const float (&c)[VEC],
-                                              const FieldNext<VEC, TY> &nx, float (&hl)[4], float (&hr)[4])
+// What every march knows of its tile.  Field pointers point at cell (0, 0,
+// x0) of plane 0; rows and columns outside the stored ones are read from the
+// zero halo instead, so that no load needs a guard.
+template <int VEC, int TY, int RW>
+struct Ctx3 {
+    int64_t plane4;            // bytes per plane
+    unsigned row[RW];          // byte offset of each own row in its plane (clamped)
+    unsigned hrow[halo_per_wave<TY>()];  // of this wave's y-halo rows
+    unsigned erow;             // per lane: row offset and column of its strip-end cell, from x0 - 4
+    unsigned lx, cx;           // byte offsets of this lane's columns: stored, own
+    unsigned own;              // per lane: bit i - this lane stores cells of own row i
+    int pitch4, x, x0, y, y0, NX, NY, lane, w;
+};
+
+template <int VEC, int TY, int RW>
+__device__ __forceinline__ Ctx3<VEC, TY, RW> make_ctx3(ShotEntry &S, Tile3Entry &T)
 {
+    Ctx3<VEC, TY, RW> C;
+    C.pitch4 = (int)S.L.pitch * 4;
+    C.plane4 = S.L.plane * 4;
+    C.NX = S.L.NX;
+    C.NY = S.L.NY;
+    C.lane = threadIdx.x & 63;
+    C.w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    C.x0 = T.x0;
+    C.y0 = T.y0;
+    C.x = T.x0 + C.lane * VEC;
+    C.y = T.y0 + C.w * RW;
+    C.lx = (unsigned)(min(C.x, (C.NX + VEC - 1) / VEC * VEC) - T.x0) * 4u;
+    C.cx = (unsigned)(C.lane * VEC) * 4u;
+    C.own = row_mask<RW>(C.y, 0, C.NY, C.x < C.NX);
+    // rows from -4 on, so that the offsets are not negative
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) L.row[buf][4 + C.w][C.lane * VEC + j] = c[j];
+    for (int i = 0; i < RW; ++i) C.row[i] = (unsigned)(min(C.y + i, C.NY + kRadius - 1) + kRadius) * (unsigned)C.pitch4;
 #pragma unroll
     for (int i = 0; i < halo_per_wave<TY>(); ++i) {
         const int h = C.w + i * TY;
-        if (h < 8) {
-            const int slot = h < 4 ? h : TY + 4 + (h - 4);
+        const int yh = h < 4 ? C.y0 - 4 + h : C.y0 + TY * RW + (h - 4);
+        C.hrow[i] = (unsigned)(min(yh, C.NY + kRadius - 1) + kRadius) * (unsigned)C.pitch4;
+    }
+    // lane 8 i + e: cell e of row i's 4 left and 4 right strip-end cells
+    const int e = C.lane & 7, ye = min(C.y + min(C.lane >> 3, RW - 1), C.NY + kRadius - 1) + kRadius;
+    const int xe = e < 4 ? e : min(64 * VEC, C.NX + kRadius - C.x0) + e;  // from x0 - 4; past the grid: zero halo
+    C.erow = (unsigned)ye * (unsigned)C.pitch4 + (unsigned)xe * 4u;
+    return C;
+}
+
+// Everything one field needs from memory for one plane of the wave's rows.
+template <int VEC, int TY, int RW>
+struct FieldNext {
+    float q[RW][VEC];                      // queue rows of plane z + 4
+    float halo[halo_per_wave<TY>()][VEC];  // this wave's y-halo rows of plane z
+    float end;                             // this lane's strip-end cell of plane z
+};
+
+// Issues the loads of field f for plane z (zo: its byte offset).
+template <int VEC, int TY, int RW>
+__device__ __forceinline__ void field_prefetch(const Ctx3<VEC, TY, RW> &C, const gfloat *f, int64_t zo,
+                                               FieldNext<VEC, TY, RW> &nx)
+{
+#pragma unroll
+    for (int i = 0; i < RW; ++i) ldv<VEC>(at(at(f, zo + 4 * C.plane4 + C.row[i]), here(C.lx)), nx.q[i]);
+#pragma unroll
+    for (int i = 0; i < halo_per_wave<TY>(); ++i)
+        if (TY <= 8 || C.w + i * TY < 8) ldv<VEC>(at(at(f, zo + C.hrow[i]), here(C.lx)), nx.halo[i]);
+    if (C.lane < 8 * RW) nx.end = *at(at(f, zo) - 4, here(C.erow));
+}
+
+// Writes the centre rows (queue slot of plane z), the y-halo rows and the
+// strip-end cells into LDS buffer `buf`.
+template <int VEC, int TY, int RW>
+__device__ __forceinline__ void field_publish(const Ctx3<VEC, TY, RW> &C, Lds<VEC, TY, RW> &L, int buf,
+                                              const float (&c)[RW][VEC], const FieldNext<VEC, TY, RW> &nx)
+{
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) L.row[buf][4 + C.w * RW + i][C.lane * VEC + j] = c[i][j];
+#pragma unroll
+    for (int i = 0; i < halo_per_wave<TY>(); ++i) {
+        const int h = C.w + i * TY;
+        if (TY <= 8 || h < 8) {
+            const int slot = h < 4 ? h : TY * RW + 4 + (h - 4);
 #pragma unroll
             for (int j = 0; j < VEC; ++j) L.row[buf][slot][C.lane * VEC + j] = nx.halo[i][j];
         }
     }
-    const bool left = C.lane == 0, right = C.lane == 63;
-    hl[0] = left ? nx.hv.x : 0.f; hl[1] = left ? nx.hv.y : 0.f; hl[2] = left ? nx.hv.z : 0.f; hl[3] = left ? nx.hv.w : 0.f;
-    hr[0] = right ? nx.hv.x : 0.f; hr[1] = right ? nx.hv.y : 0.f; hr[2] = right ? nx.hv.z : 0.f; hr[3] = right ? nx.hv.w : 0.f;
+    if (C.lane < 8 * RW) L.ends[buf][C.w][C.lane] = nx.end;
 }
 
-// Unscaled 3-D Laplacian of the centre cells of this wave.
-template <int VEC, int TY>
-__device__ __forceinline__ void lap3(const Lds<VEC, TY> &L, int buf, int w, int lane, const float (&ext)[VEC + 8],
-                                     const float (&qa)[VEC], const float (&qb)[VEC], const float (&qc)[VEC],
-                                     const float (&qd)[VEC], const float (&qe)[VEC], const float (&qf)[VEC],
-                                     const float (&qg)[VEC], const float (&qh)[VEC], const float (&qi)[VEC],
-                                     float (&lap)[VEC])
-{
-    // qa..qi: planes z-4 .. z+4 (qe is the centre).
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-        const int col = lane * VEC + j;
-        const float c = qe[j], c2 = c + c;
-        float l = d2(c2, ext[3 + j], ext[5 + j], ext[2 + j], ext[6 + j], ext[1 + j], ext[7 + j], ext[j], ext[8 + j]);
-        l += d2(c2, L.row[buf][3 + w][col], L.row[buf][5 + w][col], L.row[buf][2 + w][col], L.row[buf][6 + w][col],
-                L.row[buf][1 + w][col], L.row[buf][7 + w][col], L.row[buf][w][col], L.row[buf][8 + w][col]);
-        l += d2(c2, qd[j], qf[j], qc[j], qg[j], qb[j], qh[j], qa[j], qi[j]);
-        lap[j] = l;
-    }
-}
-
-template <int VEC>
-__device__ __forceinline__ void plane_prefetch(const Ctx3<VEC> &C, const gfloat *f, int z, float (&v)[VEC])
-{
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) v[j] = 0.f;
-    if (C.live) ldv<VEC>(f + (int64_t)z * C.plane + (int64_t)C.y * C.pitch + C.x, v);
-}
-
-template <int VEC, int TY, int S>
-__device__ __forceinline__ void fwd3_plane(const Ctx3<VEC> &C, Lds<VEC, TY> &L, const gfloat *pc, gfloat *po,
-                                           const gfloat *Dp, float (&q)[9][VEC], FieldNext<VEC, TY> &nx,
-                                           float (&nold)[VEC], float (&nd)[VEC], int z, int z0, int z1)
+// Unscaled 3-D Laplacian of the wave's centre cells; q[k]: planes z - 4 + k
+// (rotated by S).
+template <int VEC, int TY, int RW, int S>
+__device__ __forceinline__ void lap3(const Ctx3<VEC, TY, RW> &C, const Lds<VEC, TY, RW> &L, int buf,
+                                     const float (&q)[9][RW][VEC], float (&lap)[RW][VEC])
 {
     constexpr int r0 = (S + 0) % 9, r1 = (S + 1) % 9, r2 = (S + 2) % 9, r3 = (S + 3) % 9, r4 = (S + 4) % 9,
                   r5 = (S + 5) % 9, r6 = (S + 6) % 9, r7 = (S + 7) % 9, r8 = (S + 8) % 9;
-    const int buf = (z - z0) & 1;
-    float old[VEC], d[VEC], hl[4], hr[4];
+    float yn[RW + 8][VEC];  // rows y - 4 .. y + RW + 3 of plane z
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-        q[r8][j] = nx.q[j];
-        old[j] = nold[j];
-        d[j] = nd[j];
-    }
-    field_publish<VEC, TY>(C, L, buf, q[r4], nx, hl, hr);
-    if (z + 1 < z1) {
-        field_prefetch<VEC, TY>(C, pc, z + 1, nx);
-        plane_prefetch<VEC>(C, po, z + 1, nold);
-        plane_prefetch<VEC>(C, Dp, z + 1, nd);
-    }
-    float ext[VEC + 8];
-    exchange_row<VEC>(q[r4], hl, hr, ext);
-    __syncthreads();
-    float lap[VEC], out[VEC];
-    lap3<VEC, TY>(L, buf, C.w, C.lane, ext, q[r0], q[r1], q[r2], q[r3], q[r4], q[r5], q[r6], q[r7], q[r8], lap);
+    for (int i = 0; i < RW + 8; ++i)
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-        const float c = q[r4][j];
-        out[j] = fmaf(d[j], lap[j], (c + c) - old[j]);
-    }
-    if (C.own) stv<VEC>(po + (int64_t)z * C.plane + (int64_t)C.y * C.pitch + C.x, out);
-}
-
-template <int VEC, int TY, bool GRAD, int S>
-__device__ __forceinline__ void rev3_plane(const Ctx3<VEC> &C, Lds<VEC, TY> &LP, Lds<VEC, TY> &LM,
-                                           const gfloat *P0, gfloat *P1, const gfloat *M0, gfloat *M1,
-                                           const gfloat *Dp, gfloat *A0, gfloat *A1, float (&qp)[9][VEC],
-                                           float (&qm)[9][VEC], FieldNext<VEC, TY> &np_, FieldNext<VEC, TY> &nm_,
-                                           float (&np1)[VEC], float (&nm1)[VEC], float (&nd)[VEC], int z, int z0,
-                                           int z1, bool img_row)
-{
-    constexpr int r0 = (S + 0) % 9, r1 = (S + 1) % 9, r2 = (S + 2) % 9, r3 = (S + 3) % 9, r4 = (S + 4) % 9,
-                  r5 = (S + 5) % 9, r6 = (S + 6) % 9, r7 = (S + 7) % 9, r8 = (S + 8) % 9;
-    const int buf = (z - z0) & 1;
-    float p1[VEC], m1[VEC], d[VEC], hlp[4], hrp[4], hlm[4], hrm[4];
+        for (int j = 0; j < VEC; ++j)
+            yn[i][j] = i >= 4 && i < RW + 4 ? q[r4][i - 4 < 0 ? 0 : (i - 4 >= RW ? 0 : i - 4)][j]
+                                            : L.row[buf][C.w * RW + i][C.lane * VEC + j];
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-        qp[r8][j] = np_.q[j];
-        qm[r8][j] = nm_.q[j];
-        p1[j] = np1[j];
-        m1[j] = nm1[j];
-        d[j] = nd[j];
-    }
-    field_publish<VEC, TY>(C, LP, buf, qp[r4], np_, hlp, hrp);
-    field_publish<VEC, TY>(C, LM, buf, qm[r4], nm_, hlm, hrm);
-    if (z + 1 < z1) {
-        field_prefetch<VEC, TY>(C, P0, z + 1, np_);
-        field_prefetch<VEC, TY>(C, M0, z + 1, nm_);
-        plane_prefetch<VEC>(C, P1, z + 1, np1);
-        plane_prefetch<VEC>(C, M1, z + 1, nm1);
-        plane_prefetch<VEC>(C, Dp, z + 1, nd);
-    }
-    float extp[VEC + 8], extm[VEC + 8];
-    exchange_row<VEC>(qp[r4], hlp, hrp, extp);
-    exchange_row<VEC>(qm[r4], hlm, hrm, extm);
-    __syncthreads();
-    float lp[VEC], lm[VEC];
-    lap3<VEC, TY>(LP, buf, C.w, C.lane, extp, qp[r0], qp[r1], qp[r2], qp[r3], qp[r4], qp[r5], qp[r6], qp[r7], qp[r8], lp);
-    lap3<VEC, TY>(LM, buf, C.w, C.lane, extm, qm[r0], qm[r1], qm[r2], qm[r3], qm[r4], qm[r5], qm[r6], qm[r7], qm[r8], lm);
-    float np[VEC], nm[VEC], inc[VEC];
+    for (int i = 0; i < RW; ++i) {
+        float hl[4], hr[4], ext[VEC + 8];
+        halo_split(*(const f4v *)&L.ends[buf][C.w][8 * i + (C.lane < 32 ? 0 : 4)], C.lane, hl, hr);
+        exchange_row<VEC>(q[r4][i], hl, hr, ext);
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-        const float cp = qp[r4][j], cm = qm[r4][j];
-        inc[j] = d[j] * lp[j];
-        np[j] = inc[j] + ((cp + cp) - p1[j]);
-        nm[j] = fmaf(d[j], lm[j], (cm + cm) - m1[j]);
-    }
-    if (C.own) {
-        const int64_t o = (int64_t)z * C.plane + (int64_t)C.y * C.pitch + C.x;
-        stv<VEC>(P1 + o, np);
-        stv<VEC>(M1 + o, nm);
-        if constexpr (GRAD) {
-            float g[VEC];
-            ldv<VEC>(A0 + o, g);
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) g[j] = fmaf(qm[r4][j], inc[j], g[j]);
-            stv<VEC>(A0 + o, g);
-        } else if (img_row) {
-            float a[VEC], b[VEC];
-            ldv<VEC>(A0 + o, a);
-            ldv<VEC>(A1 + o, b);
-#pragma unroll
-            for (int j = 0; j < VEC; ++j) {
-                a[j] = fmaf(qp[r4][j], qm[r4][j], a[j]);
-                b[j] = fmaf(qp[r4][j], qp[r4][j], b[j]);
-            }
-            stv<VEC>(A0 + o, a);
-            stv<VEC>(A1 + o, b);
+        for (int j = 0; j < VEC; ++j) {
+            const float c = q[r4][i][j], c2 = c + c;
+            float l = d2(c2, ext[3 + j], ext[5 + j], ext[2 + j], ext[6 + j], ext[1 + j], ext[7 + j], ext[j], ext[8 + j]);
+            l += d2(c2, yn[i + 3][j], yn[i + 5][j], yn[i + 2][j], yn[i + 6][j], yn[i + 1][j], yn[i + 7][j], yn[i][j],
+                    yn[i + 8][j]);
+            l += d2(c2, q[r3][i][j], q[r5][i][j], q[r2][i][j], q[r6][i][j], q[r1][i][j], q[r7][i][j], q[r0][i][j],
+                    q[r8][i][j]);
+            lap[i][j] = l;
         }
     }
 }
 
+// The wave's rows of plane z (zo) of a field.
+template <int VEC, int TY, int RW, bool NT>
+__device__ __forceinline__ void plane_load(const Ctx3<VEC, TY, RW> &C, const gfloat *f, int64_t zo, float (&v)[RW][VEC])
+{
+#pragma unroll
+    for (int i = 0; i < RW; ++i) ld_once<VEC, NT>(at(at(f, zo + C.row[i]), here(C.lx)), v[i]);
+}
+
+template <int VEC, int TY, int RW, bool NT>
+__device__ __forceinline__ void plane_store(const Ctx3<VEC, TY, RW> &C, gfloat *f, int64_t zo, const float (&v)[RW][VEC])
+{
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+        if (C.own >> i & 1) st_once<VEC, NT>(at(at(f, zo + C.row[i]), here(C.cx)), v[i]);
+}
+
+// One field's update (forward pass, receiver field of storage RTM).  IMG: at
+// a stored level, the imaging sums take p^k from the dense snapshot.
+template <int VEC, int TY, int RW, bool IMG>
+struct StepIn {
+    FieldNext<VEC, TY, RW> f;
+    float old[RW][VEC], d[RW][VEC];
+    float s[IMG ? RW : 1][VEC], a[IMG ? RW : 1][VEC], b[IMG ? RW : 1][VEC];
+};
+
+template <int VEC, int TY, int RW, bool IMG>
+struct Step3 {
+    const gfloat *pc, *Dp;
+    gfloat *po, *A0, *A1;
+    SnapImg I;
+    int z1;
+    unsigned izn;   // interior planes from I.iz0
+    unsigned mask;  // per lane: the own rows that hold interior cells
+};
+
+template <int VEC, int TY, int RW, bool IMG, bool NT>
+__device__ __forceinline__ void step_fetch(const Ctx3<VEC, TY, RW> &C, const Step3<VEC, TY, RW, IMG> &K, int z, int64_t zo,
+                                           StepIn<VEC, TY, RW, IMG> &in)
+{
+    field_prefetch<VEC, TY, RW>(C, K.pc, zo, in.f);
+    plane_load<VEC, TY, RW, NT>(C, K.po, zo, in.old);
+    plane_load<VEC, TY, RW, NT>(C, K.Dp, zo, in.d);
+    if constexpr (IMG)
+        if (in_rows(z, K.I.iz0, K.izn)) {
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+                if (K.mask >> i & 1) {
+                    const int64_t row = ((int64_t)(z - K.I.iz0) * K.I.nyi + (C.y + i - K.I.iy0)) * K.I.nxi - K.I.ix0;
+#pragma unroll
+                    for (int j = 0; j < VEC; ++j)
+                        in.s[i][j] = C.x + j >= K.I.ix0 && C.x + j < K.I.ix1 ? K.I.snap[row + C.x + j] : 0.f;
+                    ld_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.lx)), in.a[i]);
+                    ld_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.lx)), in.b[i]);
+                }
+        }
+}
+
+template <int VEC, int TY, int RW, bool NT, bool IMG, int S>
+__device__ __forceinline__ void step_plane(const Ctx3<VEC, TY, RW> &C, const Step3<VEC, TY, RW, IMG> &K, Lds<VEC, TY, RW> &L,
+                                           float (&q)[9][RW][VEC], StepIn<VEC, TY, RW, IMG> &in, int z, int64_t &zo)
+{
+    constexpr int r4 = (S + 4) % 9, r8 = (S + 8) % 9;
+    const int buf = z & 1;
+    float old[RW][VEC], d[RW][VEC], sn[RW][VEC], sa[RW][VEC], sb[RW][VEC];
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+            q[r8][i][j] = in.f.q[i][j];
+            old[i][j] = in.old[i][j];
+            d[i][j] = in.d[i][j];
+            if constexpr (IMG) {
+                sn[i][j] = in.s[i][j];
+                sa[i][j] = in.a[i][j];
+                sb[i][j] = in.b[i][j];
+            }
+        }
+    field_publish<VEC, TY, RW>(C, L, buf, q[r4], in.f);
+    if (z + 1 < K.z1) step_fetch<VEC, TY, RW, IMG, NT>(C, K, z + 1, zo + C.plane4, in);
+    __syncthreads();
+    float lap[RW][VEC];
+    lap3<VEC, TY, RW, S>(C, L, buf, q, lap);
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) lap[i][j] = fmaf(d[i][j], lap[i][j], (q[r4][i][j] + q[r4][i][j]) - old[i][j]);
+    plane_store<VEC, TY, RW, NT>(C, K.po, zo, lap);
+    if constexpr (IMG)
+        if (in_rows(z, K.I.iz0, K.izn)) {
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+                if (K.mask >> i & 1) {
+#pragma unroll
+                    for (int j = 0; j < VEC; ++j) {
+                        sa[i][j] = fmaf(sn[i][j], q[r4][i][j], sa[i][j]);
+                        sb[i][j] = fmaf(sn[i][j], sn[i][j], sb[i][j]);
+                    }
+                    st_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.cx)), sa[i]);
+                    st_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.cx)), sb[i]);
+                }
+        }
+    zo += C.plane4;
+}
+
+// Runs ROWCALL(S, z) over the tile's planes, nine per trip (z1 - z0 is a
+// multiple of nine), so that S = (z - z0) mod 9 is a compile-time constant.
 #define RTM_MARCH3(ROWCALL)                                                                    \
     for (int z = T.z0; z < T.z1; z += kZUnroll) {                                              \
         ROWCALL(0, z); ROWCALL(1, z + 1); ROWCALL(2, z + 2); ROWCALL(3, z + 3);                \
@@ -228,47 +327,136 @@ __device__ __forceinline__ void rev3_plane(const Ctx3<VEC> &C, Lds<VEC, TY> &LP,
         ROWCALL(8, z + 8);                                                                     \
     }
 
-template <int VEC>
-__device__ __forceinline__ Ctx3<VEC> make_ctx3(const ShotDev &S, const Tile3D &T)
+template <int VEC, int TY, int RW, bool NT, bool IMG>
+__device__ __forceinline__ void step_march(const Ctx3<VEC, TY, RW> &C, const Step3<VEC, TY, RW, IMG> &K, Lds<VEC, TY, RW> &L,
+                                           Tile3Entry &T)
 {
-    Ctx3<VEC> C;
-    C.pitch = S.L.pitch;
-    C.plane = S.L.plane;
-    C.NX = S.L.NX;
-    C.NY = S.L.NY;
-    C.lane = threadIdx.x & 63;
-    C.w = threadIdx.x >> 6;
-    C.x0 = T.x0;
-    C.y0 = T.y0;
-    C.x = T.x0 + C.lane * VEC;
-    C.y = T.y0 + C.w;
-    C.liveX = C.x < C.NX + kRadius;
-    C.rowlive = C.y < C.NY + kRadius;
-    C.live = C.liveX && C.rowlive;
-    C.own = C.x < C.NX && C.y < C.NY;
-    return C;
+    float q[9][RW][VEC];
+    StepIn<VEC, TY, RW, IMG> in;
+    int64_t zo = (int64_t)T.z0 * C.plane4;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) plane_load<VEC, TY, RW, false>(C, K.pc, zo + (i - 4) * C.plane4, q[i]);
+    step_fetch<VEC, TY, RW, IMG, NT>(C, K, T.z0, zo, in);
+#define RTM_STEP3(SS, ZZ) step_plane<VEC, TY, RW, NT, IMG, SS>(C, K, L, q, in, ZZ, zo)
+    RTM_MARCH3(RTM_STEP3)
+#undef RTM_STEP3
 }
 
 // Does this wave-lane own padded cell (y, x) of the tile?
-template <int VEC>
-__device__ __forceinline__ bool owns3(const Ctx3<VEC> &C, int y, int x)
+template <int VEC, int TY, int RW>
+__device__ __forceinline__ bool owns3(const Ctx3<VEC, TY, RW> &C, int y, int x)
 {
-    return y == C.y && x >= C.x && x < C.x + VEC;
+    return y >= C.y && y < C.y + RW && x >= C.x && x < C.x + VEC;
+}
+
+// The fused reverse pair of fields.
+template <int VEC, int TY, int RW, bool GRAD>
+struct RevIn3 {
+    FieldNext<VEC, TY, RW> p, m;
+    float p1[RW][VEC], m1[RW][VEC], d[RW][VEC], a[RW][VEC], b[GRAD ? 1 : RW][VEC];
+};
+
+template <int VEC, int TY, int RW, bool GRAD>
+struct Rev3 {
+    const gfloat *P0, *M0, *Dp;
+    gfloat *P1, *M1, *A0, *A1;
+    int z1, alo;    // the sums cover planes [alo, alo + an) ...
+    unsigned an;
+    unsigned mask;  // ... and, per lane, these of the own rows
+};
+
+template <int VEC, int TY, int RW, bool GRAD, bool NT>
+__device__ __forceinline__ void rev_fetch3(const Ctx3<VEC, TY, RW> &C, const Rev3<VEC, TY, RW, GRAD> &K, int z, int64_t zo,
+                                           RevIn3<VEC, TY, RW, GRAD> &in)
+{
+    field_prefetch<VEC, TY, RW>(C, K.P0, zo, in.p);
+    field_prefetch<VEC, TY, RW>(C, K.M0, zo, in.m);
+    plane_load<VEC, TY, RW, NT>(C, K.P1, zo, in.p1);
+    plane_load<VEC, TY, RW, NT>(C, K.M1, zo, in.m1);
+    plane_load<VEC, TY, RW, NT>(C, K.Dp, zo, in.d);
+    if (in_rows(z, K.alo, K.an)) {
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+            if (K.mask >> i & 1) {
+                ld_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.lx)), in.a[i]);
+                if constexpr (!GRAD) ld_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.lx)), in.b[i]);
+            }
+    }
+}
+
+template <int VEC, int TY, int RW, bool NT, bool GRAD, int S>
+__device__ __forceinline__ void rev_plane3(const Ctx3<VEC, TY, RW> &C, const Rev3<VEC, TY, RW, GRAD> &K,
+                                           Lds<VEC, TY, RW> &LP, Lds<VEC, TY, RW> &LM, float (&qp)[9][RW][VEC],
+                                           float (&qm)[9][RW][VEC], RevIn3<VEC, TY, RW, GRAD> &in, int z, int64_t &zo)
+{
+    constexpr int r4 = (S + 4) % 9, r8 = (S + 8) % 9;
+    const int buf = z & 1;
+    float p1[RW][VEC], m1[RW][VEC], d[RW][VEC], a[RW][VEC], b[RW][VEC];
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+            qp[r8][i][j] = in.p.q[i][j];
+            qm[r8][i][j] = in.m.q[i][j];
+            p1[i][j] = in.p1[i][j];
+            m1[i][j] = in.m1[i][j];
+            d[i][j] = in.d[i][j];
+            a[i][j] = in.a[i][j];
+            if constexpr (!GRAD) b[i][j] = in.b[i][j];
+        }
+    field_publish<VEC, TY, RW>(C, LP, buf, qp[r4], in.p);
+    field_publish<VEC, TY, RW>(C, LM, buf, qm[r4], in.m);
+    if (z + 1 < K.z1) rev_fetch3<VEC, TY, RW, GRAD, NT>(C, K, z + 1, zo + C.plane4, in);
+    __syncthreads();
+    float lp[RW][VEC], lm[RW][VEC];
+    lap3<VEC, TY, RW, S>(C, LP, buf, qp, lp);
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+            const float cp = qp[r4][i][j], inc = d[i][j] * lp[i][j];
+            if constexpr (GRAD) {
+                a[i][j] = fmaf(qm[r4][i][j], inc, a[i][j]);
+            } else {
+                a[i][j] = fmaf(cp, qm[r4][i][j], a[i][j]);
+                b[i][j] = fmaf(cp, cp, b[i][j]);
+            }
+            lp[i][j] = inc + ((cp + cp) - p1[i][j]);
+        }
+    plane_store<VEC, TY, RW, NT>(C, K.P1, zo, lp);
+    lap3<VEC, TY, RW, S>(C, LM, buf, qm, lm);
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) lm[i][j] = fmaf(d[i][j], lm[i][j], (qm[r4][i][j] + qm[r4][i][j]) - m1[i][j]);
+    plane_store<VEC, TY, RW, NT>(C, K.M1, zo, lm);
+    if (in_rows(z, K.alo, K.an)) {
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+            if (K.mask >> i & 1) {
+                st_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.cx)), a[i]);
+                if constexpr (!GRAD) st_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.cx)), b[i]);
+            }
+    }
+    zo += C.plane4;
 }
 
 }  // namespace
 
-// Forward step n (see the 2-D kernel): tiles of 64*VEC x TY x (z1 - z0).
+// Field pointer at (y = -4, x = x0) of plane 0, as Ctx3's row offsets count.
+#define RTM_AT3(f) (gp(f) + S.L.org - kRadius * S.L.pitch + T.x0)
+
+// Forward step n (see the 2-D kernel): tiles of 64*VEC x TY*RW x (z1 - z0).
 // Workgroups past the stencil slots record d^n = R p^n, one receiver task
 // of 64 per wavefront.
-template <int VEC, int TY>
+template <int VEC, int TY, int RW, bool NT>
 __global__ __launch_bounds__(64 * TY) void fwd3d_kernel(const ShotDev *__restrict__ shots,
                                                         const Tile3D *__restrict__ tiles, int ntiles, int nslots,
                                                         const InjEnt *__restrict__ ents,
                                                         const Contrib *__restrict__ cont,
                                                         const SampleTask *__restrict__ stasks, int nsample, int n)
 {
-    __shared__ Lds<VEC, TY> L;
+    __shared__ Lds<VEC, TY, RW> L;
     const int b = blockIdx.x;
     if (b >= nslots) {
         const int task = (b - nslots) * TY + (int)(threadIdx.x >> 6);
@@ -277,78 +465,72 @@ __global__ __launch_bounds__(64 * TY) void fwd3d_kernel(const ShotDev *__restric
     }
     const int t = xcd_tile(b, nslots);
     if (t >= ntiles) return;
-    const Tile3D T = tiles[t];
-    const ShotDev &S = shots[T.shot];
-    const Ctx3<VEC> C = make_ctx3<VEC>(S, T);
-    const gfloat *pc = gp(S.fld[n & 1] + S.L.org);
-    gfloat *po = gp(S.fld[(n + 1) & 1] + S.L.org);
-    const gfloat *Dp = gp(S.Dp + S.L.org);
-    float q[9][VEC];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) plane_prefetch<VEC>(C, pc, T.z0 - 4 + i, q[i]);
-    FieldNext<VEC, TY> nx;
-    float nold[VEC], nd[VEC];
-    field_prefetch<VEC, TY>(C, pc, T.z0, nx);
-    plane_prefetch<VEC>(C, po, T.z0, nold);
-    plane_prefetch<VEC>(C, Dp, T.z0, nd);
-#define RTM_FWD3(SS, ZZ) fwd3_plane<VEC, TY, SS>(C, L, pc, po, Dp, q, nx, nold, nd, ZZ, T.z0, T.z1)
-    RTM_MARCH3(RTM_FWD3)
-#undef RTM_FWD3
+    Tile3Entry &T = *(Tile3Entry *)(uintptr_t)(tiles + t);
+    ShotEntry &S = *(ShotEntry *)(uintptr_t)(shots + T.shot);
+    const Ctx3<VEC, TY, RW> C = make_ctx3<VEC, TY, RW>(S, T);
+    Step3<VEC, TY, RW, false> K{};
+    K.pc = RTM_AT3(S.fld[n & 1]);
+    K.po = RTM_AT3(S.fld[(n + 1) & 1]);
+    K.Dp = RTM_AT3(S.Dp);
+    K.z1 = T.z1;
+    step_march<VEC, TY, RW, NT, false>(C, K, L, T);
     const float *wav = S.wav + n;
     for (int e = T.sbeg; e < T.send; ++e) {
         const InjEnt E = ents[e];
-        if (owns3<VEC>(C, E.y, E.x)) {
-            const int64_t o = (int64_t)E.z * C.plane + (int64_t)E.y * C.pitch + E.x;
-            po[o] = fmaf(Dp[o], inj_sum(E, cont, wav), po[o]);
+        if (owns3(C, E.y, E.x)) {
+            const int64_t o = (int64_t)E.z * S.L.plane + (int64_t)E.y * S.L.pitch + E.x;
+            gfloat *po = gp(S.fld[(n + 1) & 1]) + S.L.org;
+            po[o] = fmaf((gp(S.Dp) + S.L.org)[o], inj_sum(E, cont, wav), po[o]);
         }
     }
 }
 
 // Reverse step k (see the 2-D kernel), with LDS copies of both fields.
-template <int VEC, int TY, bool GRAD>
+template <int VEC, int TY, int RW, bool NT, bool GRAD>
 __global__ __launch_bounds__(64 * TY) void rev3d_kernel(const ShotDev *__restrict__ shots,
                                                         const Tile3D *__restrict__ tiles, int ntiles, int nslots,
                                                         const InjEnt *__restrict__ ents,
                                                         const Contrib *__restrict__ cont, int k, int reinject,
                                                         float *__restrict__ wadj)
 {
-    __shared__ Lds<VEC, TY> LP, LM;
+    __shared__ Lds<VEC, TY, RW> LP, LM;
     const int t = xcd_tile(blockIdx.x, nslots);
     if (t >= ntiles) return;
-    const Tile3D T = tiles[t];
-    const ShotDev &S = shots[T.shot];
-    const Ctx3<VEC> C = make_ctx3<VEC>(S, T);
-    const gfloat *P0 = gp(S.fld[k & 1] + S.L.org);
-    gfloat *P1 = gp(S.fld[(k + 1) & 1] + S.L.org);
-    const gfloat *M0 = gp(S.fld[2 + ((k + 1) & 1)] + S.L.org);
-    gfloat *M1 = gp(S.fld[2 + (k & 1)] + S.L.org);
-    const gfloat *Dp = gp(S.Dp + S.L.org);
-    gfloat *A0 = gp(S.acc0 + S.L.org);
-    gfloat *A1 = GRAD ? nullptr : gp(S.acc1 + S.L.org);
-    const bool img_lane = C.x + VEC > S.ix0 && C.x < S.ix1 && C.y >= S.iy0 && C.y < S.iy1;
-    float qp[9][VEC], qm[9][VEC];
+    Tile3Entry &T = *(Tile3Entry *)(uintptr_t)(tiles + t);
+    ShotEntry &S = *(ShotEntry *)(uintptr_t)(shots + T.shot);
+    const Ctx3<VEC, TY, RW> C = make_ctx3<VEC, TY, RW>(S, T);
+    Rev3<VEC, TY, RW, GRAD> K;
+    K.P0 = RTM_AT3(S.fld[k & 1]);
+    K.P1 = RTM_AT3(S.fld[(k + 1) & 1]);
+    K.M0 = RTM_AT3(S.fld[2 + ((k + 1) & 1)]);
+    K.M1 = RTM_AT3(S.fld[2 + (k & 1)]);
+    K.Dp = RTM_AT3(S.Dp);
+    K.A0 = RTM_AT3(S.acc0);
+    K.A1 = GRAD ? nullptr : RTM_AT3(S.acc1);
+    K.z1 = T.z1;
+    // the gradient sum covers the whole padded grid, the imaging sums the interior
+    K.alo = GRAD ? T.z0 : max(T.z0, S.iz0);
+    K.an = (unsigned)max((GRAD ? T.z1 : min(T.z1, S.iz1)) - K.alo, 0);
+    K.mask = GRAD ? C.own : row_mask<RW>(C.y, S.iy0, S.iy1, C.x + VEC > S.ix0 && C.x < S.ix1);
+    float qp[9][RW][VEC], qm[9][RW][VEC];
+    RevIn3<VEC, TY, RW, GRAD> in;
+    int64_t zo = (int64_t)T.z0 * C.plane4;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        plane_prefetch<VEC>(C, P0, T.z0 - 4 + i, qp[i]);
-        plane_prefetch<VEC>(C, M0, T.z0 - 4 + i, qm[i]);
+        plane_load<VEC, TY, RW, false>(C, K.P0, zo + (i - 4) * C.plane4, qp[i]);
+        plane_load<VEC, TY, RW, false>(C, K.M0, zo + (i - 4) * C.plane4, qm[i]);
     }
-    FieldNext<VEC, TY> npf, nmf;
-    float np1[VEC], nm1[VEC], nd[VEC];
-    field_prefetch<VEC, TY>(C, P0, T.z0, npf);
-    field_prefetch<VEC, TY>(C, M0, T.z0, nmf);
-    plane_prefetch<VEC>(C, P1, T.z0, np1);
-    plane_prefetch<VEC>(C, M1, T.z0, nm1);
-    plane_prefetch<VEC>(C, Dp, T.z0, nd);
-#define RTM_REV3(SS, ZZ) \
-    rev3_plane<VEC, TY, GRAD, SS>(C, LP, LM, P0, P1, M0, M1, Dp, A0, A1, qp, qm, npf, nmf, np1, nm1, nd, ZZ, T.z0, \
-                                  T.z1, img_lane && (ZZ) >= S.iz0 && (ZZ) < S.iz1)
+    rev_fetch3<VEC, TY, RW, GRAD, NT>(C, K, T.z0, zo, in);
+#define RTM_REV3(SS, ZZ) rev_plane3<VEC, TY, RW, NT, GRAD, SS>(C, K, LP, LM, qp, qm, in, ZZ, zo)
     RTM_MARCH3(RTM_REV3)
 #undef RTM_REV3
+    const gfloat *Dp = gp(S.Dp) + S.L.org, *M0 = gp(S.fld[2 + ((k + 1) & 1)]) + S.L.org;
+    gfloat *P1 = gp(S.fld[(k + 1) & 1]) + S.L.org, *A0 = gp(S.acc0) + S.L.org;
     const float *wav = S.wav + k;
     for (int e = T.sbeg; e < T.send; ++e) {
         const InjEnt E = ents[e];
-        if (owns3<VEC>(C, E.y, E.x)) {
-            const int64_t o = (int64_t)E.z * C.plane + (int64_t)E.y * C.pitch + E.x;
+        if (owns3(C, E.y, E.x)) {
+            const int64_t o = (int64_t)E.z * S.L.plane + (int64_t)E.y * S.L.pitch + E.x;
             const float ds = Dp[o] * inj_sum(E, cont, wav);
             if (reinject) P1[o] = P1[o] + ds;
             if (GRAD) A0[o] = fmaf(M0[o], ds, A0[o]);
@@ -359,148 +541,121 @@ __global__ __launch_bounds__(64 * TY) void rev3d_kernel(const ShotDev *__restric
             }
         }
     }
-    inject_nodes(M1, Dp, ents, T.rbeg, T.rend, cont, S.sig + (int64_t)k * S.nrec, C.plane, C.pitch);
+    inject_nodes(gp(S.fld[2 + (k & 1)]) + S.L.org, Dp, ents, T.rbeg, T.rend, cont, S.sig + (int64_t)k * S.nrec, S.L.plane,
+                 S.L.pitch);
 }
 
 // Receiver wavefield alone, for migration with a stored source wavefield
 // (see the 2-D kernel): the forward plane update applied to mu, with the
 // imaging sums at a stored level taking p^k from the dense snapshot (IMG).
-template <int VEC, int TY, bool IMG>
+template <int VEC, int TY, int RW, bool NT, bool IMG>
 __global__ __launch_bounds__(64 * TY) void recv3d_kernel(const ShotDev *__restrict__ shots,
                                                          const Tile3D *__restrict__ tiles, int ntiles, int nslots,
                                                          const InjEnt *__restrict__ ents,
                                                          const Contrib *__restrict__ cont, int k,
                                                          const float *__restrict__ snap)
 {
-    __shared__ Lds<VEC, TY> L;
+    __shared__ Lds<VEC, TY, RW> L;
     const int t = xcd_tile(blockIdx.x, nslots);
     if (t >= ntiles) return;
-    const Tile3D T = tiles[t];
-    const ShotDev &S = shots[T.shot];
-    const Ctx3<VEC> C = make_ctx3<VEC>(S, T);
-    const gfloat *pc = gp(S.fld[2 + ((k + 1) & 1)] + S.L.org);  // mu^{k+1}
-    gfloat *po = gp(S.fld[2 + (k & 1)] + S.L.org);              // mu^{k+2} -> mu^k
-    const gfloat *Dp = gp(S.Dp + S.L.org);
-    gfloat *A0 = gp(S.acc0 + S.L.org), *A1 = gp(S.acc1 + S.L.org);
-    const bool img = IMG && C.own && C.x + VEC > S.ix0 && C.x < S.ix1 && C.y >= S.iy0 && C.y < S.iy1;
-    const SnapImg I{snap, S.ix1 - S.ix0, S.iy1 - S.iy0, S.ix0, S.ix1, S.iy0, S.iz0};
-    float q[9][VEC];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) plane_prefetch<VEC>(C, pc, T.z0 - 4 + i, q[i]);
-    FieldNext<VEC, TY> nx;
-    float nold[VEC], nd[VEC];
-    field_prefetch<VEC, TY>(C, pc, T.z0, nx);
-    plane_prefetch<VEC>(C, po, T.z0, nold);
-    plane_prefetch<VEC>(C, Dp, T.z0, nd);
-#define RTM_RECV3(SS, ZZ)                                                                                       \
-    fwd3_plane<VEC, TY, SS>(C, L, pc, po, Dp, q, nx, nold, nd, ZZ, T.z0, T.z1);                                  \
-    if constexpr (IMG)                                                                                           \
-        if (img && (ZZ) >= S.iz0 && (ZZ) < S.iz1)                                                                \
-            snap_image<VEC>(I, A0, A1, (int64_t)(ZZ) * C.plane + (int64_t)C.y * C.pitch + C.x, ZZ, C.y, C.x,     \
-                            q[((SS) + 4) % 9]);
-    RTM_MARCH3(RTM_RECV3)
-#undef RTM_RECV3
-    inject_nodes(po, Dp, ents, T.rbeg, T.rend, cont, S.sig + (int64_t)k * S.nrec, C.plane, C.pitch);
+    Tile3Entry &T = *(Tile3Entry *)(uintptr_t)(tiles + t);
+    ShotEntry &S = *(ShotEntry *)(uintptr_t)(shots + T.shot);
+    const Ctx3<VEC, TY, RW> C = make_ctx3<VEC, TY, RW>(S, T);
+    Step3<VEC, TY, RW, IMG> K{};
+    K.pc = RTM_AT3(S.fld[2 + ((k + 1) & 1)]);  // mu^{k+1}
+    K.po = RTM_AT3(S.fld[2 + (k & 1)]);        // mu^{k+2} -> mu^k
+    K.Dp = RTM_AT3(S.Dp);
+    K.z1 = T.z1;
+    if constexpr (IMG) {
+        K.A0 = RTM_AT3(S.acc0);
+        K.A1 = RTM_AT3(S.acc1);
+        K.I = SnapImg{snap, S.ix1 - S.ix0, S.iy1 - S.iy0, S.ix0, S.ix1, S.iy0, S.iz0};
+        K.izn = (unsigned)(S.iz1 - S.iz0);
+        K.mask = row_mask<RW>(C.y, S.iy0, S.iy1, C.x + VEC > S.ix0 && C.x < S.ix1);
+    }
+    step_march<VEC, TY, RW, NT, IMG>(C, K, L, T);
+    inject_nodes(gp(S.fld[2 + (k & 1)]) + S.L.org, gp(S.Dp) + S.L.org, ents, T.rbeg, T.rend, cont,
+                 S.sig + (int64_t)k * S.nrec, S.L.plane, S.L.pitch);
 }
 
-// ---------------------------------------------------------------------------
-// Host launchers
-// ---------------------------------------------------------------------------
+// `code` is floats per lane | kOnce3D where the arrays of a step exceed the
+// memory-side cache; `ty` rows per tile.  A tile's rows are split over
+// wavefronts by register need: one row each while a workgroup has at most
+// eight (forward) or four (reverse) of them, and at two floats per lane.
+#define RTM_ONCE3(CALL, V, Y, R) do { if (once) CALL(V, Y, R, true); else CALL(V, Y, R, false); } while (0)
+#define RTM_FWD_SHAPES(CALL)                        \
+    switch (vec << 8 | ty) {                        \
+    case 0x104: RTM_ONCE3(CALL, 1, 4, 1); break;    \
+    case 0x108: RTM_ONCE3(CALL, 1, 8, 1); break;    \
+    case 0x110: RTM_ONCE3(CALL, 1, 8, 2); break;    \
+    case 0x204: RTM_ONCE3(CALL, 2, 4, 1); break;    \
+    case 0x208: RTM_ONCE3(CALL, 2, 8, 1); break;    \
+    case 0x210: RTM_ONCE3(CALL, 2, 16, 1); break;   \
+    case 0x404: RTM_ONCE3(CALL, 4, 4, 1); break;    \
+    case 0x408: RTM_ONCE3(CALL, 4, 8, 1); break;    \
+    default: return hipErrorInvalidValue;           \
+    }
+#define RTM_REV_SHAPES(CALL)                        \
+    switch (vec << 8 | ty) {                        \
+    case 0x104: RTM_ONCE3(CALL, 1, 4, 1); break;    \
+    case 0x108: RTM_ONCE3(CALL, 1, 4, 2); break;    \
+    case 0x110: RTM_ONCE3(CALL, 1, 8, 2); break;    \
+    case 0x204: RTM_ONCE3(CALL, 2, 4, 1); break;    \
+    case 0x208: RTM_ONCE3(CALL, 2, 4, 2); break;    \
+    case 0x404: RTM_ONCE3(CALL, 4, 4, 1); break;    \
+    case 0x408: RTM_ONCE3(CALL, 4, 8, 1); break;    \
+    default: return hipErrorInvalidValue;           \
+    }
 
-hipError_t launch_fwd3d(int vec, int ty, const ShotDev *shots, const Tile3D *tiles, int ntiles, int nslots,
+hipError_t launch_fwd3d(int code, int ty, const ShotDev *shots, const Tile3D *tiles, int ntiles, int nslots,
                         const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
                         hipStream_t st)
 {
-    const int nsb = (nsample + ty - 1) / ty;
-    dim3 grid(nslots + nsb), block(64 * ty);
-#define RTM_F3(V, Y) \
-    hipLaunchKernelGGL((fwd3d_kernel<V, Y>), grid, block, 0, st, shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n)
-    if (ty == 4) {
-        switch (vec) {
-        case 1: RTM_F3(1, 4); break;
-        case 2: RTM_F3(2, 4); break;
-        case 4: RTM_F3(4, 4); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else if (ty == 8) {
-        switch (vec) {
-        case 1: RTM_F3(1, 8); break;
-        case 2: RTM_F3(2, 8); break;
-        case 4: RTM_F3(4, 8); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else if (ty == 16) {
-        switch (vec) {
-        case 1: RTM_F3(1, 16); break;
-        case 2: RTM_F3(2, 16); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        return hipErrorInvalidValue;
-    }
+    const int vec = code & 0xff;
+    const bool once = code & kOnce3D;
+    if (!stasks) nsample = 0;
+#define RTM_F3(V, Y, R, N)                                                                                          \
+    hipLaunchKernelGGL((fwd3d_kernel<V, Y, R, N>), dim3(nslots + (nsample + Y - 1) / Y), dim3(64 * Y), 0, st, shots, \
+                       tiles, ntiles, nslots, ents, cont, stasks, nsample, n)
+    RTM_FWD_SHAPES(RTM_F3)
 #undef RTM_F3
     return hipGetLastError();
 }
 
-hipError_t launch_rev3d(int vec, int ty, bool grad, const ShotDev *shots, const Tile3D *tiles, int ntiles, int nslots,
+hipError_t launch_rev3d(int code, int ty, bool grad, const ShotDev *shots, const Tile3D *tiles, int ntiles, int nslots,
                         const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj, hipStream_t st)
 {
-    dim3 grid(nslots), block(64 * ty);
-#define RTM_R3(V, Y, G) \
-    hipLaunchKernelGGL((rev3d_kernel<V, Y, G>), grid, block, 0, st, shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj)
-#define RTM_R3V(Y, G)                          \
-    switch (vec) {                             \
-    case 1: RTM_R3(1, Y, G); break;            \
-    case 2: RTM_R3(2, Y, G); break;            \
-    case 4: RTM_R3(4, Y, G); break;            \
-    default: return hipErrorInvalidValue;      \
-    }
-    if (ty == 4) {
-        if (grad) { RTM_R3V(4, true) } else { RTM_R3V(4, false) }
-    } else if (ty == 8) {
-        if (grad) { RTM_R3V(8, true) } else { RTM_R3V(8, false) }
-    } else if (ty == 16 && vec == 1) {
-        if (grad) { RTM_R3(1, 16, true); } else { RTM_R3(1, 16, false); }
-    } else {
-        return hipErrorInvalidValue;
-    }
-#undef RTM_R3V
+    const int vec = code & 0xff;
+    const bool once = code & kOnce3D;
+#define RTM_R3(V, Y, R, N)                                                                                         \
+    do {                                                                                                           \
+        if (grad)                                                                                                  \
+            hipLaunchKernelGGL((rev3d_kernel<V, Y, R, N, true>), dim3(nslots), dim3(64 * Y), 0, st, shots, tiles,  \
+                               ntiles, nslots, ents, cont, k, reinject, wadj);                                     \
+        else                                                                                                       \
+            hipLaunchKernelGGL((rev3d_kernel<V, Y, R, N, false>), dim3(nslots), dim3(64 * Y), 0, st, shots, tiles, \
+                               ntiles, nslots, ents, cont, k, reinject, wadj);                                     \
+    } while (0)
+    RTM_REV_SHAPES(RTM_R3)
 #undef RTM_R3
     return hipGetLastError();
 }
 
-hipError_t launch_recv3d(int vec, int ty, const ShotDev *shots, const Tile3D *tiles, int ntiles, int nslots,
+hipError_t launch_recv3d(int code, int ty, const ShotDev *shots, const Tile3D *tiles, int ntiles, int nslots,
                          const InjEnt *ents, const Contrib *cont, int k, const float *snap, hipStream_t st)
 {
-    dim3 grid(nslots), block(64 * ty);
-#define RTM_RC3(V, Y)                                                                                              \
-    if (snap)                                                                                                      \
-        hipLaunchKernelGGL((recv3d_kernel<V, Y, true>), grid, block, 0, st, shots, tiles, ntiles, nslots, ents, cont, k, \
-                           snap);                                                                                  \
-    else                                                                                                           \
-        hipLaunchKernelGGL((recv3d_kernel<V, Y, false>), grid, block, 0, st, shots, tiles, ntiles, nslots, ents, cont, \
-                           k, snap)
-#define RTM_RC3V(Y)                            \
-    switch (vec) {                             \
-    case 1: RTM_RC3(1, Y); break;              \
-    case 2: RTM_RC3(2, Y); break;              \
-    case 4: RTM_RC3(4, Y); break;              \
-    default: return hipErrorInvalidValue;      \
-    }
-    if (ty == 4) {
-        RTM_RC3V(4)
-    } else if (ty == 8) {
-        RTM_RC3V(8)
-    } else if (ty == 16) {
-        switch (vec) {
-        case 1: RTM_RC3(1, 16); break;
-        case 2: RTM_RC3(2, 16); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        return hipErrorInvalidValue;
-    }
-#undef RTM_RC3V
+    const int vec = code & 0xff;
+    const bool once = code & kOnce3D;
+#define RTM_RC3(V, Y, R, N)                                                                                         \
+    do {                                                                                                            \
+        if (snap)                                                                                                   \
+            hipLaunchKernelGGL((recv3d_kernel<V, Y, R, N, true>), dim3(nslots), dim3(64 * Y), 0, st, shots, tiles,  \
+                               ntiles, nslots, ents, cont, k, snap);                                                \
+        else                                                                                                        \
+            hipLaunchKernelGGL((recv3d_kernel<V, Y, R, N, false>), dim3(nslots), dim3(64 * Y), 0, st, shots, tiles, \
+                               ntiles, nslots, ents, cont, k, snap);                                                \
+    } while (0)
+    RTM_FWD_SHAPES(RTM_RC3)
 #undef RTM_RC3
     return hipGetLastError();
 }

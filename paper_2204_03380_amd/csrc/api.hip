@@ -139,7 +139,7 @@ struct Tune {
     int steps = 1;  // 2-D: time steps per launch (1, 2 or 3)
     int zin = 0;    // 3-D: tiles numbered with z innermost (else x innermost)
     int block = 0;  // 2-D multi-step: index of kBlockShapes (0: marching strips)
-    int once = 0;   // 3-D: kOnce3D, or 0
+    int once = 0;   // 3-D, 2-D multi-step: kOnce, or 0
     int code() const { return vec | block << 8 | once; }  // as the multi-step and 3-D launchers take it
 };
 
@@ -713,7 +713,7 @@ Tune fit_tune3(const Job &J, Tune t, Pass3 pass)
         NZr = std::max(NZr, S.g.L.NZr);
         NX = std::max(NX, S.g.NX);
     }
-    t.once = bytes > kCacheBytes ? kOnce3D : 0;
+    t.once = bytes > kCacheBytes ? kOnce : 0;
     if (g_tune_exact.load()) return t;
     if (NX <= 64) t.vec = 1;  // half the lanes would be idle
     if (!t.once && t.ty == 16 && t.vec > 1) {
@@ -824,8 +824,27 @@ int fit_block(const Job &J, int steps, bool reverse)
     return 0;
 }
 
+// once, as in fit_tune3: the arrays a multi-step launch moves (the fields read
+// and written, D' per model, imaging sums) beyond the 256 MiB memory-side
+// cache.  Measured (us per step with / without, reverse): 3 shots of 2301 x
+// 751, 246 MB, 35.2 / 31.8; 4 shots 38.3 / 39.3; 8 shots 69.1 / 72.2; 48
+// shots 378 / 413; forward: 8 shots, 272 MB, 29.6 / 29.6; 48 shots 143 / 150;
+// gradient: 24 windows 38.6 / 40.1.
+int once_multi(const Job &J, bool reverse)
+{
+    int64_t bytes = 0;
+    for (int s = 0; s < (int)J.shots.size(); ++s) {
+        const GridInfo &g = J.shots[s].g;
+        const int64_t all = 4 * (int64_t)g.NX * g.NZ, in = 4 * g.nx * g.nz;
+        bytes += (reverse ? 8 : 4) * all + (!reverse ? 0 : J.op == RTM_OP_VJP ? all : 2 * in);
+        if (J.slot_shot[J.dslot[s]] == s) bytes += all;
+    }
+    return bytes > ((int64_t)256 << 20) ? kOnce : 0;
+}
+
 Tune fit_multi(const Job &J, Tune t, bool reverse)
 {
+    if (t.vec < 4) t.once = once_multi(J, reverse);
     if (g_tune_exact.load()) return t;
     if ((t.block = fit_block(J, t.steps, reverse)) != 0) {
         const BlockShape &b = kBlockShapes[t.block];

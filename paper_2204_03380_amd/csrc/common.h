@@ -90,9 +90,9 @@ struct BlockShape {
 };
 constexpr BlockShape kBlockShapes[] = {{0, 0, 0}, {1, 8, 4}, {2, 12, 3}, {2, 16, 3}};
 
-// 3-D launchers take floats per lane | kOnce3D where what a step touches once
-// is better kept out of the caches.
-constexpr int kOnce3D = 0x100;
+// The 3-D and the multi-step launchers also take kOnce in that code: what a
+// launch touches once is better kept out of the caches.
+constexpr int kOnce = 0x10000;
 
 // A 2-D stencil tile: one wavefront marches down rows [z0, z1) of a strip
 // of 64 * VEC columns starting at x0; z1 - z0 is a multiple of kZUnroll

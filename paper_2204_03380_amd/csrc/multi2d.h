@@ -1,6 +1,7 @@
-// Device helpers of the 2-D kernels that take several time steps per launch:
-// addressing without guards, table access through the scalar cache, lane
-// shifts with zero ends, source nodes held in lanes.
+// Device helpers of the 2-D kernels that take several time steps per launch
+// (and, where they apply, of the 3-D kernels): addressing without guards,
+// table access through the scalar cache, cache-bypassing access, lane shifts
+// with zero ends, source nodes held in lanes.
 #pragma once
 
 #include "stencil.h"
@@ -77,6 +78,39 @@ __device__ __forceinline__ bool in_rows(int r, int lo, unsigned n) { return (uns
 // them stays in scalar registers.
 typedef __attribute__((address_space(4))) const ShotDev ShotEntry;
 typedef __attribute__((address_space(4))) const Tile2D TileEntry;
+
+// Access to values that a launch touches once (new levels, imaging sums; in
+// the 3-D kernels also the older level and D').  NT leaves them out of the way
+// in the L2, whose lines then last until the neighbouring tiles have read the
+// halo rows they share.
+template <int VEC, bool NT>
+__device__ __forceinline__ void ld_once(const gfloat *p, float (&v)[VEC])
+{
+    if constexpr (!NT) {
+        ldv<VEC>(p, v);
+    } else if constexpr (VEC == 4) {
+        const f4v t = __builtin_nontemporal_load((const gf4v *)p);
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+    } else if constexpr (VEC == 2) {
+        const f2v t = __builtin_nontemporal_load((const gf2v *)p);
+        v[0] = t.x; v[1] = t.y;
+    } else {
+        v[0] = __builtin_nontemporal_load(p);
+    }
+}
+
+template <int VEC, bool NT>
+__device__ __forceinline__ void st_once(gfloat *p, const float (&v)[VEC])
+{
+    if constexpr (!NT)
+        stv<VEC>(p, v);
+    else if constexpr (VEC == 4)
+        __builtin_nontemporal_store(f4v{v[0], v[1], v[2], v[3]}, (gf4v *)p);
+    else if constexpr (VEC == 2)
+        __builtin_nontemporal_store(f2v{v[0], v[1]}, (gf2v *)p);
+    else
+        __builtin_nontemporal_store(v[0], p);
+}
 
 // The value again, opaque to the compiler: the 64-bit extension of a byte
 // offset then stays next to its use, where it folds into the access (a

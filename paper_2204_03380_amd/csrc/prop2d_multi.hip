@@ -25,7 +25,11 @@
 // 88 % busy; hence the zero-guard addressing below (scalar row addresses, a
 // 32-bit lane offset, clamped rows): 4442 vector instructions for 27 rows of
 // fwd2d_multi<2, 3> against 2581 for 9 with guards and 64-bit lane addresses
-// (forward 156.7 -> 149.9 us per step, reverse 413.7 -> 413.4).  With fewer
+// (forward 156.7 -> 149.9 us per step, reverse 413.7 -> 413.4).  Stores of new
+// levels and the imaging sums that bypass the caches where the arrays exceed
+// them (NT) leave the L2 to the columns and rows that neighbouring tiles share
+// (forward 150 -> 143, reverse 413 -> 378; bypassing on the loads too, 146 and
+// 391: strips overlap, and D' is shared by the shots).  With fewer
 // than about four wavefronts per SIMD each row waits for its own loads, so
 // P = 3 loads them three march steps ahead into a ring of registers
 // (16 shots, forward: 64.3 -> 52.7 us per step, 55.3 without the ring; 2
@@ -144,7 +148,7 @@ __device__ __forceinline__ void fwd_fetch(const FwdMulti<VEC, T> &K, RowAt &ra, 
 
 // March step s = 9 i + S (PH = min(i, 2)): step one of row r1 = r0 + s, step
 // two of row r1 - 4 from s = 8 on, step three of row r1 - 8 from s = 16 on.
-template <int VEC, int T, int P, int PH, int S>
+template <int VEC, int T, int P, bool NT, int PH, int S>
 __device__ __forceinline__ void fwd_row(const FwdMulti<VEC, T> &K, float (&q1)[9][VEC], float (&q2)[9][VEC],
                                            float (&q3)[9][VEC], float (&qd)[9][VEC], FwdIn<VEC> (&in)[P > 0 ? P : 1],
                                            const SrcLane &src, RowAt &ra, RowAt &rq, int64_t &o1, int r1)
@@ -175,9 +179,9 @@ __device__ __forceinline__ void fwd_row(const FwdMulti<VEC, T> &K, float (&q1)[9
         qd[a4][j] = d[j];
     }
     if constexpr (T == 3) {
-        if (in_rows(r1, K.m0, K.mn) && C.own) stv<VEC>(at(at(K.mid, o1), here(C.cx)), v);
+        if (in_rows(r1, K.m0, K.mn) && C.own) st_once<VEC, NT>(at(at(K.mid, o1), here(C.cx)), v);
     } else {
-        if (in_rows(r1, C.z0, C.zn) && C.own) stv<VEC>(at(at(K.wa, o1), here(C.cx)), v);
+        if (in_rows(r1, C.z0, C.zn) && C.own) st_once<VEC, NT>(at(at(K.wa, o1), here(C.cx)), v);
     }
     if constexpr (PH > 0 || S == 8) {
         exchange_row0<VEC>(q2[a0], ext);
@@ -188,7 +192,7 @@ __device__ __forceinline__ void fwd_row(const FwdMulti<VEC, T> &K, float (&q1)[9
         if constexpr (T == 3)
 #pragma unroll
             for (int j = 0; j < VEC; ++j) q3[a0][j] = v[j];
-        if (in_rows(r2, C.z0, C.zn) && C.own) stv<VEC>(at(at(T == 3 ? K.wa : K.wb, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), v);
+        if (in_rows(r2, C.z0, C.zn) && C.own) st_once<VEC, NT>(at(at(T == 3 ? K.wa : K.wb, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), v);
     }
     if constexpr (T == 3 && (PH > 1 || (PH == 1 && S >= 7))) {
         exchange_row0<VEC>(q3[a5], ext);
@@ -196,7 +200,7 @@ __device__ __forceinline__ void fwd_row(const FwdMulti<VEC, T> &K, float (&q1)[9
 #pragma unroll
         for (int j = 0; j < VEC; ++j) v[j] = fmaf(qd[a5][j], lap[j], (q3[a5][j] + q3[a5][j]) - q2[a5][j]);
         if (in_rows(r3, K.s0, K.sn)) src_row<VEC>(src, 3, r3, C.x, [&](int j, float s, int) __attribute__((always_inline)) { v[j] = fmaf(qd[a5][j], s, v[j]); });
-        if (r3 < C.z1 && C.own) stv<VEC>(at(at(K.wb, o1 - 8 * (int64_t)C.pitch4), here(C.cx)), v);
+        if (r3 < C.z1 && C.own) st_once<VEC, NT>(at(at(K.wb, o1 - 8 * (int64_t)C.pitch4), here(C.cx)), v);
     }
     o1 += C.pitch4;
 }
@@ -362,7 +366,7 @@ __device__ __forceinline__ void rev_src(const RevMulti<VEC, T, GRAD> &K, const S
 // three steps, the new p^{k-2}, mu^{k-1} are in registers.  Gradient: the
 // row's sum travels through the queue qg, taking each step's term where
 // that step is computed.
-template <int VEC, int T, int P, bool GRAD, int PH, int S>
+template <int VEC, int T, int P, bool NT, bool GRAD, int PH, int S>
 __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (&q1p)[9][VEC], float (&q1m)[9][VEC],
                                            float (&q2p)[9][VEC], float (&q2m)[9][VEC], float (&q3p)[9][VEC],
                                            float (&q3m)[9][VEC], float (&qd)[9][VEC], float (&qg)[9][VEC],
@@ -388,8 +392,8 @@ __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (
     }
     if constexpr (!GRAD && P == 0) {
         if (in_rows(r2, K.alo, K.an) && K.alane) {
-            ldv<VEC>(at(at(K.A0, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), ia);
-            ldv<VEC>(at(at(K.A1, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), ib);
+            ld_once<VEC, NT>(at(at(K.A0, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), ia);
+            ld_once<VEC, NT>(at(at(K.A1, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), ib);
         }
     }
     if constexpr (P > 0) rev_fetch<VEC, T, GRAD, true>(K, ra, rq, I);
@@ -418,8 +422,8 @@ __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (
     }
     if constexpr (T == 2)
         if (in_rows(r1, C.z0, C.zn) && C.own) {
-            stv<VEC>(at(at(K.WPa, o1), here(C.cx)), vp);
-            stv<VEC>(at(at(K.WMa, o1), here(C.cx)), vm);
+            st_once<VEC, NT>(at(at(K.WPa, o1), here(C.cx)), vp);
+            st_once<VEC, NT>(at(at(K.WMa, o1), here(C.cx)), vm);
         }
     if constexpr (PH > 0 || S == 8) {
         exchange_row0<VEC>(q2p[a0], ext);
@@ -439,9 +443,9 @@ __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (
         const bool mine = in_rows(r2, C.z0, C.zn);
         if (mine && C.own) {
             const int64_t o2 = o1 - 4 * (int64_t)C.pitch4;
-            stv<VEC>(at(at(T == 3 ? K.WPa : K.WPb, o2), here(C.cx)), vp);
-            stv<VEC>(at(at(T == 3 ? K.WMa : K.WMb, o2), here(C.cx)), vm);
-            if constexpr (GRAD && T == 2) stv<VEC>(at(at(K.A0, o2), here(C.cx)), qg[a0]);
+            st_once<VEC, NT>(at(at(T == 3 ? K.WPa : K.WPb, o2), here(C.cx)), vp);
+            st_once<VEC, NT>(at(at(T == 3 ? K.WMa : K.WMb, o2), here(C.cx)), vm);
+            if constexpr (GRAD && T == 2) st_once<VEC, NT>(at(at(K.A0, o2), here(C.cx)), qg[a0]);
         }
         if constexpr (!GRAD) {
             if (in_rows(r2, K.alo, K.an) && K.alane) {
@@ -455,8 +459,8 @@ __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (
                         sb[j] = fmaf(vp[j], vp[j], sb[j]);
                     }
                 }
-                stv<VEC>(at(at(K.A0, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), sa);
-                stv<VEC>(at(at(K.A1, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), sb);
+                st_once<VEC, NT>(at(at(K.A0, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), sa);
+                st_once<VEC, NT>(at(at(K.A1, o1 - 4 * (int64_t)C.pitch4), here(C.cx)), sb);
             }
         }
         if constexpr (T == 3)
@@ -469,8 +473,8 @@ __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (
     if constexpr (!GRAD && P > 0) {
         // the next row's sums
         if (in_rows(r2 + 1, K.alo, K.an) && K.alane) {
-            ldv<VEC>(at(at(K.A0, o1 - 3 * (int64_t)C.pitch4), here(C.cx)), ia);
-            ldv<VEC>(at(at(K.A1, o1 - 3 * (int64_t)C.pitch4), here(C.cx)), ib);
+            ld_once<VEC, NT>(at(at(K.A0, o1 - 3 * (int64_t)C.pitch4), here(C.cx)), ia);
+            ld_once<VEC, NT>(at(at(K.A1, o1 - 3 * (int64_t)C.pitch4), here(C.cx)), ib);
         }
     }
     if constexpr (T == 3 && (PH > 1 || (PH == 1 && S >= 7))) {
@@ -491,9 +495,9 @@ __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (
                          K.has);
         if (r3 < C.z1 && C.own) {
             const int64_t o3 = o1 - 8 * (int64_t)C.pitch4;
-            stv<VEC>(at(at(K.WPb, o3), here(C.cx)), vp);
-            stv<VEC>(at(at(K.WMb, o3), here(C.cx)), vm);
-            if constexpr (GRAD) stv<VEC>(at(at(K.A0, o3), here(C.cx)), qg[a5]);
+            st_once<VEC, NT>(at(at(K.WPb, o3), here(C.cx)), vp);
+            st_once<VEC, NT>(at(at(K.WMb, o3), here(C.cx)), vm);
+            if constexpr (GRAD) st_once<VEC, NT>(at(at(K.A0, o3), here(C.cx)), qg[a5]);
         }
     }
     o1 += C.pitch4;
@@ -503,7 +507,7 @@ __device__ __forceinline__ void rev_row(const RevMulti<VEC, T, GRAD> &K, float (
 
 // Steps n .. n + T - 1 of every tile; workgroups past the stencil slots
 // record receivers from the read set.
-template <int VEC, int T, int P>
+template <int VEC, int T, int P, bool NT>
 __global__ __launch_bounds__(64) void fwd2d_multi_kernel(const ShotDev *__restrict__ shots,
                                                       const Tile2D *__restrict__ tiles, int ntiles, int nslots,
                                                       const InjEnt *__restrict__ ents,
@@ -565,7 +569,7 @@ __global__ __launch_bounds__(64) void fwd2d_multi_kernel(const ShotDev *__restri
         for (int j = 0; j < VEC; ++j) q2[i][j] = q3[i][j] = qd[i][j] = 0.f;
     int64_t o1 = (int64_t)K.C.r0 * (int64_t)K.C.pitch4;
     const int nstep = tile.z1 - tile.z0 + (T - 1) * kZUnroll;
-#define RTM_ROW(PH, SS, ZZ) fwd_row<VEC, T, P, PH, SS>(K, q1, q2, q3, qd, in, src, ra, rq, o1, K.C.r0 + (ZZ))
+#define RTM_ROW(PH, SS, ZZ) fwd_row<VEC, T, P, NT, PH, SS>(K, q1, q2, q3, qd, in, src, ra, rq, o1, K.C.r0 + (ZZ))
     RTM_NINE(RTM_ROW, 0, 0)
     if constexpr (T == 3) {
         RTM_NINE(RTM_ROW, 1, 9)
@@ -576,7 +580,7 @@ __global__ __launch_bounds__(64) void fwd2d_multi_kernel(const ShotDev *__restri
 #undef RTM_ROW
 }
 
-template <int VEC, int T, int P, bool GRAD>
+template <int VEC, int T, int P, bool NT, bool GRAD>
 __global__ __launch_bounds__(64) void rev2d_multi_kernel(const ShotDev *__restrict__ shots, const Tile2D *__restrict__ tiles,
                                                       int ntiles, int nslots, const InjEnt *__restrict__ ents,
                                                       const Contrib *__restrict__ cont, int k, int reinject,
@@ -666,7 +670,7 @@ __global__ __launch_bounds__(64) void rev2d_multi_kernel(const ShotDev *__restri
     int64_t o1 = (int64_t)K.C.r0 * (int64_t)K.C.pitch4;
     const int nstep = tile.z1 - tile.z0 + (T - 1) * kZUnroll;
 #define RTM_ROW(PH, SS, ZZ) \
-    rev_row<VEC, T, P, GRAD, PH, SS>(K, q1p, q1m, q2p, q2m, q3p, q3m, qd, qg, in, ia, ib, src, R, ra, rq, o1, K.C.r0 + (ZZ))
+    rev_row<VEC, T, P, NT, GRAD, PH, SS>(K, q1p, q1m, q2p, q2m, q3p, q3m, qd, qg, in, ia, ib, src, R, ra, rq, o1, K.C.r0 + (ZZ))
     RTM_NINE(RTM_ROW, 0, 0)
     if constexpr (T == 3) {
         RTM_NINE(RTM_ROW, 1, 9)
@@ -689,102 +693,106 @@ namespace {
 // (4752): 83.0 and 80.9; 48 shots (9504): 152.8 and 149.9.
 constexpr int kAheadTiles = 4 * 1024;
 
-template <int V, int T>
+template <int V, int T, bool N>
 void fwd_launch(const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots, const InjEnt *ents,
                 const Contrib *cont, const SampleTask *stasks, int nsample, int n, hipStream_t st)
 {
     const dim3 grid(nslots + T * nsample), block(64);
     if constexpr (V < 4)  // four floats per lane leave no registers for the ring
         if (ntiles < kAheadTiles) {
-            hipLaunchKernelGGL((fwd2d_multi_kernel<V, T, 3>), grid, block, 0, st, shots, tiles, ntiles, nslots, ents,
-                               cont, stasks, nsample, n);
+            hipLaunchKernelGGL((fwd2d_multi_kernel<V, T, 3, N>), grid, block, 0, st, shots, tiles, ntiles, nslots,
+                               ents, cont, stasks, nsample, n);
             return;
         }
-    hipLaunchKernelGGL((fwd2d_multi_kernel<V, T, 0>), grid, block, 0, st, shots, tiles, ntiles, nslots, ents, cont,
+    hipLaunchKernelGGL((fwd2d_multi_kernel<V, T, 0, N>), grid, block, 0, st, shots, tiles, ntiles, nslots, ents, cont,
                        stasks, nsample, n);
 }
 
 // The reverse triple holds six field queues (167 registers at two floats per
 // lane): the ring would cost it a wavefront per SIMD (4 shots: 39.5 us per
 // step without, 44.7 with it).
-template <int V, int T, bool G>
+template <int V, int T, bool N, bool G>
 void rev_launch(const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots, const InjEnt *ents,
                 const Contrib *cont, int k, int reinject, float *wadj, hipStream_t st)
 {
     if constexpr (V < 4 && T == 2)
         if (ntiles < kAheadTiles) {
-            hipLaunchKernelGGL((rev2d_multi_kernel<V, T, 3, G>), dim3(nslots), dim3(64), 0, st, shots, tiles, ntiles,
+            hipLaunchKernelGGL((rev2d_multi_kernel<V, T, 3, N, G>), dim3(nslots), dim3(64), 0, st, shots, tiles, ntiles,
                                nslots, ents, cont, k, reinject, wadj);
             return;
         }
-    hipLaunchKernelGGL((rev2d_multi_kernel<V, T, 0, G>), dim3(nslots), dim3(64), 0, st, shots, tiles, ntiles, nslots,
+    hipLaunchKernelGGL((rev2d_multi_kernel<V, T, 0, N, G>), dim3(nslots), dim3(64), 0, st, shots, tiles, ntiles, nslots,
                        ents, cont, k, reinject, wadj);
 }
 
 }  // namespace
 
+// `code`: floats per lane | block shape << 8 | kOnce (strips of up to two
+// floats per lane).
 #define RTM_VECS(CALL)                          \
-    switch (vec) {                              \
-    case 1: CALL(1); break;                     \
-    case 2: CALL(2); break;                     \
-    case 4: CALL(4); break;                     \
+    switch (code) {                             \
+    case 1: CALL(1, false); break;              \
+    case 2: CALL(2, false); break;              \
+    case 4: CALL(4, false); break;              \
+    case 1 | kOnce: CALL(1, true); break;       \
+    case 2 | kOnce: CALL(2, true); break;       \
     default: return hipErrorInvalidValue;       \
     }                                           \
     return hipGetLastError();
 
-hipError_t launch_fwd2d_t2(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+hipError_t launch_fwd2d_t2(int code, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
                            hipStream_t st)
 {
-    if (vec >> 8)
-        return launch_fwd2d_block(vec >> 8, 2, shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st);
-#define RTM_CALL(V) fwd_launch<V, 2>(shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st)
+    if (const int shape = code >> 8 & 0xff)
+        return launch_fwd2d_block(shape, 2, shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st);
+#define RTM_CALL(V, N) fwd_launch<V, 2, N>(shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
 }
 
-hipError_t launch_fwd2d_t3(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+hipError_t launch_fwd2d_t3(int code, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, const SampleTask *stasks, int nsample, int n,
                            hipStream_t st)
 {
-    if (vec >> 8)
-        return launch_fwd2d_block(vec >> 8, 3, shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st);
-#define RTM_CALL(V) fwd_launch<V, 3>(shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st)
+    if (const int shape = code >> 8 & 0xff)
+        return launch_fwd2d_block(shape, 3, shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st);
+#define RTM_CALL(V, N) fwd_launch<V, 3, N>(shots, tiles, ntiles, nslots, ents, cont, stasks, nsample, n, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
 }
 
-hipError_t launch_rev2d_t2(int vec, bool grad, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+hipError_t launch_rev2d_t2(int code, bool grad, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj, hipStream_t st)
 {
-    if (vec >> 8)
-        return launch_rev2d_block(vec >> 8, 2, grad, shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);
-#define RTM_CALL(V)                                                                                          \
+    if (const int shape = code >> 8 & 0xff)
+        return launch_rev2d_block(shape, 2, grad, shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);
+#define RTM_CALL(V, N)                                                                                          \
     if (grad)                                                                                                \
-        rev_launch<V, 2, true>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);              \
+        rev_launch<V, 2, N, true>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);              \
     else                                                                                                     \
-        rev_launch<V, 2, false>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st)
+        rev_launch<V, 2, N, false>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
 }
 
-hipError_t launch_rev2d_t3(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+hipError_t launch_rev2d_t3(int code, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                            const InjEnt *ents, const Contrib *cont, int k, int reinject, hipStream_t st)
 {
-    if (vec >> 8)
-        return launch_rev2d_block(vec >> 8, 3, false, shots, tiles, ntiles, nslots, ents, cont, k, reinject, nullptr, st);
-#define RTM_CALL(V) rev_launch<V, 3, false>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, nullptr, st)
+    if (const int shape = code >> 8 & 0xff)
+        return launch_rev2d_block(shape, 3, false, shots, tiles, ntiles, nslots, ents, cont, k, reinject, nullptr, st);
+#define RTM_CALL(V, N) rev_launch<V, 3, N, false>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, nullptr, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
 }
 
-hipError_t launch_rev2d_t3_grad(int vec, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
+hipError_t launch_rev2d_t3_grad(int code, const ShotDev *shots, const Tile2D *tiles, int ntiles, int nslots,
                                 const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj,
                                 hipStream_t st)
 {
-    if (vec >> 8)
-        return launch_rev2d_block(vec >> 8, 3, true, shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);
-#define RTM_CALL(V) rev_launch<V, 3, true>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st)
+    if (const int shape = code >> 8 & 0xff)
+        return launch_rev2d_block(shape, 3, true, shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st);
+#define RTM_CALL(V, N) rev_launch<V, 3, N, true>(shots, tiles, ntiles, nslots, ents, cont, k, reinject, wadj, st)
     RTM_VECS(RTM_CALL)
 #undef RTM_CALL
 }

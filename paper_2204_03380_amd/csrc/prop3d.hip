@@ -37,38 +37,6 @@ namespace {
 
 typedef __attribute__((address_space(4))) const Tile3D Tile3Entry;
 
-// Access to values that this launch touches once (older level, D', imaging
-// sums).  NT leaves them out of the way in the L2, whose lines then last
-// until the neighbouring tiles have read the halo rows they share.
-template <int VEC, bool NT>
-__device__ __forceinline__ void ld_once(const gfloat *p, float (&v)[VEC])
-{
-    if constexpr (!NT) {
-        ldv<VEC>(p, v);
-    } else if constexpr (VEC == 4) {
-        const f4v t = __builtin_nontemporal_load((const gf4v *)p);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    } else if constexpr (VEC == 2) {
-        const f2v t = __builtin_nontemporal_load((const gf2v *)p);
-        v[0] = t.x; v[1] = t.y;
-    } else {
-        v[0] = __builtin_nontemporal_load(p);
-    }
-}
-
-template <int VEC, bool NT>
-__device__ __forceinline__ void st_once(gfloat *p, const float (&v)[VEC])
-{
-    if constexpr (!NT)
-        stv<VEC>(p, v);
-    else if constexpr (VEC == 4)
-        __builtin_nontemporal_store(f4v{v[0], v[1], v[2], v[3]}, (gf4v *)p);
-    else if constexpr (VEC == 2)
-        __builtin_nontemporal_store(f2v{v[0], v[1]}, (gf2v *)p);
-    else
-        __builtin_nontemporal_store(v[0], p);
-}
-
 // Number of y-halo rows a wave loads per plane (8 halo rows over TY waves).
 template <int TY>
 constexpr int halo_per_wave() { return (8 + TY - 1) / TY; }
@@ -578,7 +546,7 @@ __global__ __launch_bounds__(64 * TY) void recv3d_kernel(const ShotDev *__restri
                  S.sig + (int64_t)k * S.nrec, S.L.plane, S.L.pitch);
 }
 
-// `code` is floats per lane | kOnce3D where the arrays of a step exceed the
+// `code` is floats per lane | kOnce where the arrays of a step exceed the
 // memory-side cache; `ty` rows per tile.  A tile's rows are split over
 // wavefronts by register need: one row each while a workgroup has at most
 // eight (forward) or four (reverse) of them, and at two floats per lane.
@@ -612,7 +580,7 @@ hipError_t launch_fwd3d(int code, int ty, const ShotDev *shots, const Tile3D *ti
                         hipStream_t st)
 {
     const int vec = code & 0xff;
-    const bool once = code & kOnce3D;
+    const bool once = code & kOnce;
     if (!stasks) nsample = 0;
 #define RTM_F3(V, Y, R, N)                                                                                          \
     hipLaunchKernelGGL((fwd3d_kernel<V, Y, R, N>), dim3(nslots + (nsample + Y - 1) / Y), dim3(64 * Y), 0, st, shots, \
@@ -626,7 +594,7 @@ hipError_t launch_rev3d(int code, int ty, bool grad, const ShotDev *shots, const
                         const InjEnt *ents, const Contrib *cont, int k, int reinject, float *wadj, hipStream_t st)
 {
     const int vec = code & 0xff;
-    const bool once = code & kOnce3D;
+    const bool once = code & kOnce;
 #define RTM_R3(V, Y, R, N)                                                                                         \
     do {                                                                                                           \
         if (grad)                                                                                                  \
@@ -645,7 +613,7 @@ hipError_t launch_recv3d(int code, int ty, const ShotDev *shots, const Tile3D *t
                          const InjEnt *ents, const Contrib *cont, int k, const float *snap, hipStream_t st)
 {
     const int vec = code & 0xff;
-    const bool once = code & kOnce3D;
+    const bool once = code & kOnce;
 #define RTM_RC3(V, Y, R, N)                                                                                         \
     do {                                                                                                            \
         if (snap)                                                                                                   \

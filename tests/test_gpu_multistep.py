@@ -135,3 +135,35 @@ def test_block_kernels_uneven_batch():
     want = run()
     _shape(False, 3)
     _same(want, run())
+
+
+# Ten shots of 2401 x 851 padded cells exceed the memory-side cache (335 MB
+# forward, 790 reverse), one does not: the kernels that keep what they touch
+# once out of the caches give the bits of the others.
+@pytest.mark.parametrize("op", [rtm.RTM_OP_MODEL, rtm.RTM_OP_RTM, rtm.RTM_OP_VJP])
+@pytest.mark.parametrize("steps", [2, 3])
+def test_large_batch_equals_single(op, steps):
+    nt = 7
+    shot, d = _shot(2301, 751, 50, nt, rows=1)
+    _shape(False, steps)
+
+    def run(n):
+        g = shot["grid"]
+        shape = {rtm.RTM_OP_MODEL: (len(d), nt + 1), rtm.RTM_OP_RTM: g.interior_shape, rtm.RTM_OP_VJP: g.padded_shape}[op]
+        key = {rtm.RTM_OP_MODEL: "traces_out", rtm.RTM_OP_RTM: "image", rtm.RTM_OP_VJP: "grad_v_pad"}[op]
+        outs = [torch.zeros(shape, device=DEV) for _ in range(n)]
+        plan = rtm.BatchPlan(op, [rtm.BatchShot(g, shot["v_pad"], shot["wavelet"], shot["src"], shot["rec"],
+                                                traces_in=None if op == rtm.RTM_OP_MODEL else d, **{key: o})
+                                  for o in outs], shot["dt"], nt)
+        plan.run()
+        torch.cuda.synchronize()
+        plan.free()
+        return outs
+
+    try:
+        one, many = run(1)[0], run(10)
+    finally:
+        _shape(False, 3)
+    assert torch.isfinite(one).all() and one.any()
+    for o in many:
+        assert torch.equal(o, one)

@@ -71,14 +71,17 @@ hipError_t launch_pad_adjoint(int ndim, int nb, int64_t nx, int64_t ny, int64_t 
                               uint64_t seed, float v_cap, const unsigned *cap_bits, const BandOpts &o,
                               const float *g_pad, float *g_int, hipStream_t st);
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t st);
+hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
 hipError_t launch_build_dp(const Layout &L, const float *v_pad, float dt_over_h, float *Dp, hipStream_t st);
 hipError_t launch_unpack(const Layout &L, const float *f, float *out, hipStream_t st);
-hipError_t launch_transpose(const float *in, float *out, int64_t R, int64_t C, hipStream_t st);
+hipError_t launch_traces(const ShotDev *shots, int nsh, int maxrec, int64_t nt1, bool in, hipStream_t st);
 hipError_t launch_inj_set(const ShotDev *shots, const InjEnt *ents, int ebeg, int eend, const Contrib *cont, int step,
                           hipStream_t st);
 hipError_t launch_sample(const ShotDev *shots, const SampleTask *stasks, int ntask, int n, int slot, hipStream_t st);
-hipError_t launch_image(const ShotDev *shots, int shot, int64_t ninterior, unsigned *dmax_bits, float eps_rel,
-                        float *image, int accumulate, float *num, float *den, hipStream_t st);
+hipError_t launch_den_max(const ShotDev *shots, int nsh, int64_t rows, int64_t len, unsigned *dmax_bits, hipStream_t st);
+hipError_t launch_image(const ShotDev *shots, int first, int count, int64_t rows, int64_t len,
+                        const unsigned *dmax_bits, float eps_rel, float *image, int accumulate, float *num, float *den,
+                        hipStream_t st);
 hipError_t launch_grad(const ShotDev *shots, int shot, int64_t npad, const float *v_pad, float dt, float *grad,
                        hipStream_t st);
 hipError_t launch_snap_store(const ShotDev *shots, int shot, int lev, int64_t ninterior, float *out, hipStream_t st);
@@ -358,6 +361,7 @@ struct WsLayout {
     std::vector<size_t> dp;                  // per D' slot
     std::vector<std::array<size_t, 8>> fld;  // per shot
     std::vector<size_t> acc0, acc1, trint, wadj;
+    size_t zero_end = 0;  // fields and sums, from the first shot's first field on, end here
     size_t bytes = 0;
 };
 
@@ -442,6 +446,7 @@ WsLayout make_ws_layout(const Job &J, const Counts &c)
     for (int i = 0; i < nsh; ++i) {
         const ShotIn &S = J.shots[i];
         const int64_t F = S.g.L.total;
+        // one region of everything that starts at zero;
         // fields 0..3: first set (p, p, mu, mu), 4..7: second set; a
         // modeling job has the two p levels of each set (and in 2-D the
         // middle-level slot 2)
@@ -451,7 +456,10 @@ WsLayout make_ws_layout(const Job &J, const Counts &c)
         w.fld.push_back(f);
         w.acc0.push_back(J.op == RTM_OP_MODEL ? 0 : take(sizeof(float) * F));
         w.acc1.push_back(has_den(J.op) ? take(sizeof(float) * F) : 0);
-        w.trint.push_back(take(sizeof(float) * (size_t)(J.nt + 1) * S.nrec));
+    }
+    w.zero_end = align256(off);
+    for (int i = 0; i < nsh; ++i) {
+        w.trint.push_back(take(sizeof(float) * (size_t)(J.nt + 1) * J.shots[i].nrec));
         w.wadj.push_back(J.op == RTM_OP_VJP ? take(sizeof(float) * (size_t)J.nt * kMaxNodes) : 0);
     }
     w.bytes = align256(off);
@@ -1064,6 +1072,8 @@ void fill_shot_devs(const Job &J, const Dev &D, std::vector<ShotDev> &out)
         float *trint = D.at<float>(J.ws.trint[i]);
         d.sig = J.op == RTM_OP_MODEL ? nullptr : trint;
         d.rec_out = J.op == RTM_OP_MODEL ? trint : nullptr;
+        d.traces_in = S.traces_in;
+        d.traces_out = S.traces_out;
         d.rnode = D.at<int>(J.ws.rnode) + J.rbase[i] * kMaxNodes;
         d.rw = D.at<float>(J.ws.rw) + J.rbase[i] * kMaxNodes;
         d.nrec = S.nrec;
@@ -1176,17 +1186,17 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
         const ShotIn &S = J.shots[J.slot_shot[d]];
         RTM_HIP(launch_build_dp(S.g.L, S.v_pad, (float)(J.dt / S.g.h), D.at<float>(J.ws.dp[d]), st));
     }
+    // Fields and sums of every shot, one region: a launch per field and shot
+    // left the GPU idle between them (48 shots, imaging: 480 launches, 2.3 ms
+    // and as much again in gaps).
+    RTM_HIP(launch_zero(D.at<char>(J.ws.fld[0][0]), J.ws.zero_end - J.ws.fld[0][0], st));
+    int maxrec = 0;
     for (int i = 0; i < nsh; ++i) {
-        const int64_t F = J.shots[i].g.L.total;
-        for (int k = 0; k < 8; ++k)
-            if (J.ws.fld[i][k]) RTM_HIP(launch_fill(D.at<float>(J.ws.fld[i][k]), F, 0.f, st));
-        if (J.op != RTM_OP_MODEL) RTM_HIP(launch_fill(D.at<float>(J.ws.acc0[i]), F, 0.f, st));
-        if (has_den(J.op)) RTM_HIP(launch_fill(D.at<float>(J.ws.acc1[i]), F, 0.f, st));
+        maxrec = std::max(maxrec, J.shots[i].nrec);
         if (J.op == RTM_OP_VJP && J.shots[i].grad_wavelet)
             RTM_HIP(launch_fill(D.at<float>(J.ws.wadj[i]), (int64_t)nt * kMaxNodes, 0.f, st));
-        if (J.op != RTM_OP_MODEL)
-            RTM_HIP(launch_transpose(J.shots[i].traces_in, D.at<float>(J.ws.trint[i]), J.shots[i].nrec, nt + 1, st));
     }
+    if (J.op != RTM_OP_MODEL) RTM_HIP(launch_traces(table, nsh, maxrec, nt + 1, true, st));
     // Forward pass (Algorithm 1; in RTM only the last two panels are kept).
     {
         const PassRange pass("rtm:forward");
@@ -1269,9 +1279,9 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
         }
     }
     if (J.op == RTM_OP_MODEL) {
+        RTM_HIP(launch_traces(table, nsh, maxrec, nt + 1, false, st));
         for (int i = 0; i < nsh; ++i) {
             const ShotIn &S = J.shots[i];
-            RTM_HIP(launch_transpose(D.at<float>(J.ws.trint[i]), S.traces_out, nt + 1, S.nrec, st));
             if (S.p_last) RTM_HIP(launch_unpack(S.g.L, fld_of(i, nt & 1), S.p_last, st));
             if (S.p_prev) RTM_HIP(launch_unpack(S.g.L, fld_of(i, (nt + 1) & 1), S.p_prev, st));
         }
@@ -1302,8 +1312,9 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
                                       snap, st));
         }
         timer.finish();
-        RTM_HIP(launch_image(SH(), 0, ncell, scal + 64 + 2 * J.slot_shot.size(), J.eps, S.image, 0, S.num, S.den,
-                             st));
+        unsigned *dmax = scal + 64 + 2 * J.slot_shot.size();
+        RTM_HIP(launch_den_max(SH(), 1, S.g.ny * S.g.nz, S.g.nx, dmax, st));
+        RTM_HIP(launch_image(SH(), 0, 1, S.g.ny * S.g.nz, S.g.nx, dmax, J.eps, S.image, 0, S.num, S.den, st));
         return RTM_OK;
     }
     const int reinject = (J.flags & RTM_F_NO_REINJECT) ? 0 : 1;
@@ -1361,18 +1372,32 @@ int job_launch(const Job &J, const Dev &D, hipStream_t st, const rtm_probe_t *pr
         }
     }
     timer.finish();
-    // Finalisation, shot by shot (stream-ordered, so shots may share an
-    // accumulated image buffer).
-    for (int i = 0; i < nsh; ++i) {
-        const ShotIn &S = J.shots[i];
-        if (grad) {
+    // Finalisation: stream-ordered, so shots may share an image buffer; shots
+    // in a row that do are added in one launch, in their order.
+    if (grad) {
+        for (int i = 0; i < nsh; ++i) {
+            const ShotIn &S = J.shots[i];
             RTM_HIP(launch_grad(SH(), i, (int64_t)S.g.NX * S.g.NY * S.g.NZ, S.v_pad, (float)J.dt, S.grad_v_pad, st));
             if (S.grad_wavelet && nsh == 1)
                 RTM_HIP(launch_wadj(D.at<float>(J.ws.wadj[i]), nt, (float)(1.0 / (S.g.h * S.g.h)), S.grad_wavelet, st));
-        } else {
-            RTM_HIP(launch_image(SH(), i, S.g.nx * S.g.ny * S.g.nz, scal + 64 + 2 * J.slot_shot.size() + i, J.eps,
-                                 S.image, (J.flags & RTM_F_ACCUMULATE) ? 1 : 0, S.num, S.den, st));
         }
+        return RTM_OK;
+    }
+    unsigned *dmax = scal + 64 + 2 * J.slot_shot.size();
+    int64_t rows = 0, len = 0;
+    for (const ShotIn &S : J.shots) {
+        rows = std::max(rows, S.g.ny * S.g.nz);
+        len = std::max(len, S.g.nx);
+    }
+    RTM_HIP(launch_den_max(SH(), nsh, rows, len, dmax, st));
+    for (int i = 0, m; i < nsh; i += m) {
+        const ShotIn &S = J.shots[i];
+        auto joins = [&](const ShotIn &o) {
+            return o.image == S.image && !o.num && !o.den && o.g.nx == S.g.nx && o.g.ny == S.g.ny && o.g.nz == S.g.nz;
+        };
+        for (m = 1; S.image && !S.num && !S.den && i + m < nsh && joins(J.shots[i + m]);) ++m;
+        RTM_HIP(launch_image(SH(), i, m, S.g.ny * S.g.nz, S.g.nx, dmax, J.eps, S.image,
+                             (J.flags & RTM_F_ACCUMULATE) ? 1 : 0, S.num, S.den, st));
     }
     return RTM_OK;
 }

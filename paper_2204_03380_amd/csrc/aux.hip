@@ -22,13 +22,41 @@ inline unsigned grid_for(int64_t n)
     return (unsigned)b;
 }
 
-// Grid for reductions: a few blocks per CU, each striding over the data.
+// Grid for reductions: kPer elements per thread and round, at most four
+// blocks per CU.  Each block ends in one atomic on the same word, which cost
+// more than the reading on small arrays (1.2 MB: 13 us with one element per
+// thread and up to 1024 blocks, 4.7 with sixteen).
+constexpr int kPer = 8;
+
 inline unsigned grid_reduce(int64_t n)
 {
-    int64_t b = (n + kBlock - 1) / kBlock;
-    if (b < 1) b = 1;
-    if (b > 1024) b = 1024;
-    return (unsigned)b;
+    const int64_t b = (n + 2 * kPer * kBlock - 1) / (2 * kPer * kBlock);
+    return (unsigned)std::min<int64_t>(std::max<int64_t>(b, 1), 1024);
+}
+
+// Wavefronts over rows (612 x 612 x 356 cells, us: image 232 -> 140, den_max 212
+// -> 91, build_dp 416 -> 297; 401 x 401 x 135 snapshot 82 -> 47, with one cell
+// per thread and its divisions before): wavefront w of the grid takes chunks of 256 columns,
+// F(row, x0) with x0 the chunk's first column, four columns per lane at x0 +
+// lane + 64 u.  Row and chunk are uniform, so their divisions cost nothing
+// per cell.  rows * chunks fits 32 bits (grids hold fewer than 2^31 cells).
+constexpr int kChunk = 256;
+
+template <class F>
+__device__ __forceinline__ void chunks_do(unsigned rows, unsigned len, F f)
+{
+    const unsigned per = (len + kChunk - 1) / kChunk, n = rows * per;
+    const unsigned w = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6));
+    for (unsigned i = w; i < n; i += gridDim.x * (kBlock / 64)) {
+        const unsigned row = i / per;
+        f(row, (i - row * per) * kChunk + (threadIdx.x & 63));
+    }
+}
+
+inline unsigned grid_chunks(int64_t rows, int64_t len)
+{
+    const int64_t n = (rows * ((len + kChunk - 1) / kChunk) + kBlock / 64 - 1) / (kBlock / 64);
+    return (unsigned)std::min<int64_t>(std::max<int64_t>(n, 1), 16384);
 }
 
 // SplitMix64 (Steele, Lea & Flood 2014): output number k + 1 of the stream
@@ -90,28 +118,35 @@ __device__ __forceinline__ void block_reduce_atomic(unsigned m, unsigned *out)
     }
 }
 
-__global__ __launch_bounds__(kBlock) void vmax_bits_kernel(const float *__restrict__ v, int64_t n,
-                                                           unsigned *__restrict__ out)
+// Largest and (MIN) smallest IEEE bit pattern into out[0], out[1]: for positive
+// finite data these are the maximum and the minimum; a NaN, infinity or
+// negative value compares above +inf's pattern.  One pass over the data, eight
+// loads in flight per thread (1.2 MB: 4.7 us, two passes with one took 27; 533 MB:
+// 121 and 458).
+template <bool MIN>
+__global__ __launch_bounds__(kBlock) void vrange_kernel(const float *__restrict__ v, int64_t n,
+                                                        unsigned *__restrict__ out)
 {
-    // Largest IEEE bit pattern: for positive finite data it is the maximum;
-    // a NaN, infinity or negative value compares above +inf's pattern.
-    unsigned m = 0u;
-    for (int64_t i = gid(); i < n; i += gstride()) m = max(m, __float_as_uint(v[i]));
-    block_reduce_atomic<true>(m, out);
+    unsigned hi = 0u, lo = 0xffffffffu;
+    for (int64_t i = gid(); i < n; i += kPer * gstride()) {
+        unsigned x[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) x[u] = __float_as_uint(v[min(i + u * gstride(), n - 1)]);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            hi = max(hi, x[u]);
+            lo = min(lo, x[u]);
+        }
+    }
+    block_reduce_atomic<true>(hi, out);
+    if (MIN) block_reduce_atomic<false>(lo, out + 1);
 }
 
-__global__ __launch_bounds__(kBlock) void vmin_bits_kernel(const float *__restrict__ v, int64_t n,
-                                                           unsigned *__restrict__ out)
+// out[i] = i odd ? odd : even.
+__global__ void set_u32_kernel(unsigned *__restrict__ p, int n, unsigned even, unsigned odd)
 {
-    unsigned m = 0xffffffffu;
-    for (int64_t i = gid(); i < n; i += gstride()) m = min(m, __float_as_uint(v[i]));
-    block_reduce_atomic<false>(m, out);
-}
-
-__global__ void set_u32_kernel(unsigned *__restrict__ p, int n, unsigned v)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = i & 1 ? odd : even;
 }
 
 // Band cell value: min(f_j v_edge, cap); with the taper min(c_i (f_j v_edge),
@@ -145,45 +180,121 @@ __global__ void rbc_pad_kernel(PadDims d, const float *__restrict__ v_int, uint6
 // Gather form of the padding adjoint: each interior cell collects its own
 // gradient and (c_i) f_j times the gradient of every uncapped band cell j
 // whose clamped coordinates are this cell (free-surface cells are constant).
-__global__ void pad_adjoint_kernel(PadDims d, const float *__restrict__ v_int, uint64_t seed, float v_cap,
-                                   const unsigned *__restrict__ cap_bits, BandOpts o,
-                                   const float *__restrict__ g_pad, float *__restrict__ g_int)
+// An interior cell has one such term, one on a face nb + 1, on an edge (nb +
+// 1)^2, at a corner (2-D: (nb + 1)^2, 3-D: (nb + 1)^3): a thread that walked a
+// corner by itself, one gather and one factor after the other, set the whole
+// launch's time (401 .. 1201 x 300 cells, nb 40: 371 us; now 27).  A thread
+// still walks its own cell, four gathers ahead, but cells of many terms that
+// stand alone in their wavefront, or of very many, are shared by its lanes:
+// partial sums over every 64th term, added up in a fixed order.
+struct AdjCell {
+    float ve;
+    int64_t x0, y0, z0, cx, cy, cz;  // first padded cell of the box; the cell itself
+    int mx, my;                      // box extents
+    int m;                           // cells in the box
+};
+
+__device__ __forceinline__ AdjCell adj_cell(const PadDims &d, const float *__restrict__ v_int, int64_t i)
+{
+    AdjCell c;
+    const int64_t ix = i % d.nx;
+    const int64_t iy = (i / d.nx) % d.ny;
+    const int64_t iz = i / (d.nx * d.ny);
+    c.ve = v_int[i];
+    c.cx = ix + d.nb;
+    c.cz = iz + d.nb;
+    c.cy = d.ndim == 3 ? iy + d.nb : 0;
+    // Padded coordinate ranges that clamp onto (iz, iy, ix).
+    c.x0 = ix == 0 ? 0 : c.cx;
+    c.z0 = iz == 0 ? 0 : c.cz;
+    c.y0 = iy == 0 ? 0 : c.cy;
+    c.mx = (int)((ix == d.nx - 1 ? d.NX - 1 : c.cx) - c.x0) + 1;
+    c.my = (int)((iy == d.ny - 1 ? d.NY - 1 : c.cy) - c.y0) + 1;
+    c.m = c.mx * c.my * ((int)((iz == d.nz - 1 ? d.NZ - 1 : c.cz) - c.z0) + 1);
+    return c;
+}
+
+// Adds terms beg, beg + step, ... of a cell, in that order.  LINE: the box is
+// one cell wide along all axes but one, so that a term's cell takes no
+// division (the 2-D case above: 27 us, 40 without).
+template <bool LINE>
+__device__ __forceinline__ float adj_sum(const PadDims &d, const AdjCell &c, uint64_t seed, float cap,
+                                         const BandOpts &o, const float *__restrict__ g_pad, int beg, int step)
+{
+    constexpr int U = 4;
+    const int lx = c.mx > 1, ly = !lx && c.my > 1, lz = !lx && !ly;
+    auto cell = [&](int t, int64_t &x, int64_t &y, int64_t &z) {
+        if (LINE) {
+            x = c.x0 + (lx ? t : 0);
+            y = c.y0 + (ly ? t : 0);
+            z = c.z0 + (lz ? t : 0);
+        } else {
+            const int yz = t / c.mx, zz = yz / c.my;
+            x = c.x0 + (t - yz * c.mx);
+            y = c.y0 + (yz - zz * c.my);
+            z = c.z0 + zz;
+        }
+    };
+    float acc = 0.f;
+    for (int t0 = beg; t0 < c.m; t0 += U * step) {
+        float g[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int64_t x, y, z;
+            cell(min(t0 + u * step, c.m - 1), x, y, z);
+            g[u] = g_pad[(z * d.NY + y) * d.NX + x];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + u * step;
+            if (t >= c.m) break;
+            int64_t x, y, z;
+            cell(t, x, y, z);
+            if (z == c.cz && y == c.cy && x == c.cx) {
+                acc += g[u];
+            } else if (!((o.flags & kBandFreeSurface) && z < d.nb)) {
+                float f = rbc_factor(seed, (uint64_t)((z * d.NY + y) * d.NX + x));
+                float v = __fmul_rn(f, c.ve);
+                if (o.flags & kBandTaper) {
+                    const float k = o.c[cell_depth(d, x - d.nb, (d.ndim == 3) ? y - d.nb : 0, z - d.nb) - 1];
+                    v = __fmul_rn(k, v);
+                    f = __fmul_rn(k, f);
+                }
+                if (v < cap) acc = fmaf(f, g[u], acc);
+            }
+        }
+    }
+    return acc;
+}
+
+constexpr int kAdjLong = 16, kAdjShare = 1024;  // terms; a wavefront with at most 8 long cells shares them too
+
+__global__ __launch_bounds__(kBlock) void pad_adjoint_kernel(PadDims d, const float *__restrict__ v_int, uint64_t seed,
+                                                             float v_cap, const unsigned *__restrict__ cap_bits,
+                                                             BandOpts o, const float *__restrict__ g_pad,
+                                                             float *__restrict__ g_int)
 {
     const float cap = cap_bits ? __uint_as_float(*cap_bits) : v_cap;
     const int64_t n = d.nx * d.ny * d.nz;
-    for (int64_t i = gid(); i < n; i += gstride()) {
-        const int64_t ix = i % d.nx;
-        const int64_t iy = (i / d.nx) % d.ny;
-        const int64_t iz = i / (d.nx * d.ny);
-        const float ve = v_int[i];
-        // Padded coordinate ranges that clamp onto (iz, iy, ix).
-        const int64_t xlo = (ix == 0) ? 0 : ix + d.nb, xhi = (ix == d.nx - 1) ? d.NX - 1 : ix + d.nb;
-        const int64_t zlo = (iz == 0) ? 0 : iz + d.nb, zhi = (iz == d.nz - 1) ? d.NZ - 1 : iz + d.nb;
-        int64_t ylo = 0, yhi = 0;
-        if (d.ndim == 3) {
-            ylo = (iy == 0) ? 0 : iy + d.nb;
-            yhi = (iy == d.ny - 1) ? d.NY - 1 : iy + d.nb;
+    const int lane = threadIdx.x & 63;
+    // whole wavefronts: lanes past the end hold no cell but help with the shared ones
+    for (int64_t i = gid(); i - lane < n; i += gstride()) {
+        const bool in = i < n;
+        AdjCell c = adj_cell(d, v_int, min(i, n - 1));
+        if (!in) c.m = 0;
+        const bool few = __popcll(__ballot(c.m >= kAdjLong)) <= 8;
+        const bool share = c.m >= kAdjShare || (few && c.m >= kAdjLong);
+        if (in && !share) {
+            const int mz = c.m / (c.mx * c.my);
+            if (__all((c.mx > 1) + (c.my > 1) + (mz > 1) <= 1)) g_int[i] = adj_sum<true>(d, c, seed, cap, o, g_pad, 0, 1);
+            else g_int[i] = adj_sum<false>(d, c, seed, cap, o, g_pad, 0, 1);
         }
-        const int64_t cx = ix + d.nb, cz = iz + d.nb, cy = (d.ndim == 3) ? iy + d.nb : 0;
-        float acc = 0.f;
-        for (int64_t z = zlo; z <= zhi; ++z)
-            for (int64_t y = ylo; y <= yhi; ++y)
-                for (int64_t x = xlo; x <= xhi; ++x) {
-                    const int64_t j = (z * d.NY + y) * d.NX + x;
-                    if (z == cz && y == cy && x == cx) {
-                        acc += g_pad[j];
-                    } else if (!((o.flags & kBandFreeSurface) && z < d.nb)) {
-                        float f = rbc_factor(seed, (uint64_t)j);
-                        float v = __fmul_rn(f, ve);
-                        if (o.flags & kBandTaper) {
-                            const float c = o.c[cell_depth(d, x - d.nb, (d.ndim == 3) ? y - d.nb : 0, z - d.nb) - 1];
-                            v = __fmul_rn(c, v);
-                            f = __fmul_rn(c, f);
-                        }
-                        if (v < cap) acc = fmaf(f, g_pad[j], acc);
-                    }
-                }
-        g_int[i] = acc;
+        for (uint64_t todo = __ballot(share); todo != 0; todo &= todo - 1) {
+            const int64_t j = i - lane + (__ffsll((unsigned long long)todo) - 1);
+            float s = adj_sum<false>(d, adj_cell(d, v_int, j), seed, cap, o, g_pad, lane, 64);
+            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+            if (lane == 0) g_int[j] = s;
+        }
     }
 }
 
@@ -192,21 +303,37 @@ __global__ void fill_kernel(float *__restrict__ p, int64_t n, float v)
     for (int64_t i = gid(); i < n; i += gstride()) p[i] = v;
 }
 
-// D'[cell] = (v dt / h)^2 on the padded grid, zero in the halo.
-__global__ void build_dp_kernel(Layout L, const float *__restrict__ v_pad, float dt_over_h, float *__restrict__ Dp)
+typedef float fill4 __attribute__((ext_vector_type(4)));
+
+// Zeros n 16-byte units; NT: past the caches.
+template <bool NT>
+__global__ __launch_bounds__(kBlock) void zero_kernel(fill4 *__restrict__ p, int64_t n)
 {
-    for (int64_t i = gid(); i < L.total; i += gstride()) {
-        const int64_t zz = i / L.plane - kRadius;
-        const int64_t rem = i % L.plane;
-        const int64_t yy = (L.ndim == 3) ? rem / L.pitch - kRadius : 0;
-        const int64_t xx = rem % L.pitch - kXOff;
-        float val = 0.f;
-        if (zz >= 0 && zz < L.NZ && yy >= 0 && yy < L.NY && xx >= 0 && xx < L.NX) {
-            const float c = v_pad[(zz * L.NY + yy) * L.NX + xx] * dt_over_h;
-            val = c * c;
-        }
-        Dp[i] = val;
+    const fill4 z = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t i = gid(); i < n; i += gstride()) {
+        if (NT) __builtin_nontemporal_store(z, p + i);
+        else p[i] = z;
     }
+}
+
+// D'[cell] = (v dt / h)^2 on the padded grid, zero in the halo.
+__global__ __launch_bounds__(kBlock) void build_dp_kernel(Layout L, const float *__restrict__ v_pad, float dt_over_h,
+                                                          float *__restrict__ Dp)
+{
+    const unsigned py = (unsigned)(L.plane / L.pitch), rows = (unsigned)(L.total / L.pitch);
+    chunks_do(rows, (unsigned)L.pitch, [&](unsigned row, unsigned x0) {
+        const int zz = (int)(row / py) - kRadius, yy = L.ndim == 3 ? (int)(row % py) - kRadius : 0;
+        const bool in = zz >= 0 && zz < L.NZ && yy >= 0 && yy < L.NY;
+        const float *v = v_pad + ((int64_t)min(max(zz, 0), L.NZ - 1) * L.NY + min(max(yy, 0), L.NY - 1)) * L.NX;
+        float c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = in ? v[min(max((int)(x0 + 64 * u) - kXOff, 0), L.NX - 1)] * dt_over_h : 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int x = (int)(x0 + 64 * u), xx = x - kXOff;
+            if (x < L.pitch) Dp[(int64_t)row * L.pitch + x] = xx >= 0 && xx < L.NX ? c[u] * c[u] : 0.f;
+        }
+    });
 }
 
 // Dense [NZ][NY][NX] copy of a halo-layout field.
@@ -221,20 +348,33 @@ __global__ void unpack_kernel(Layout L, const float *__restrict__ f, float *__re
     }
 }
 
-// out[c][r] = in[r][c] for an R x C matrix, through a 32 x 33 LDS tile.
-__global__ void transpose_kernel(const float *__restrict__ in, float *__restrict__ out, int64_t R, int64_t C)
+// Traces of every shot between the caller's [nrec][nt1] and the [nt1][nrec]
+// that the passes read (IN) or write, through a 32 x 33 LDS tile; blockIdx.x:
+// 32 receivers, y: 32 samples, z: shot.
+template <bool IN>
+__global__ __launch_bounds__(256) void traces_kernel(const ShotDev *__restrict__ shots, int nsh, int64_t nt1)
 {
     __shared__ float tile[32][33];
-    const int64_t c0 = (int64_t)blockIdx.x * 32, r0 = (int64_t)blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8 threads
-    for (int i = ty; i < 32; i += 8) {
-        int64_t r = r0 + i, c = c0 + tx;
-        if (r < R && c < C) tile[i][tx] = in[r * C + c];
-    }
-    __syncthreads();
-    for (int i = ty; i < 32; i += 8) {
-        int64_t c = c0 + i, r = r0 + tx;
-        if (r < R && c < C) out[c * R + r] = tile[tx][i];
+    const int64_t r0 = (int64_t)blockIdx.x * 32;
+    for (int s = blockIdx.z; s < nsh; s += gridDim.z) {
+        const int64_t R = shots[s].nrec;
+        if (r0 >= R) continue;
+        // in: R x nt1 -> nt1 x R; out: nt1 x R -> R x nt1
+        const float *from = IN ? shots[s].traces_in : shots[s].rec_out;
+        float *to = IN ? const_cast<float *>(shots[s].sig) : shots[s].traces_out;
+        for (int64_t t0 = (int64_t)blockIdx.y * 32; t0 < nt1; t0 += (int64_t)gridDim.y * 32) {
+            for (int i = ty; i < 32; i += 8) {
+                const int64_t r = r0 + (IN ? i : tx), t = t0 + (IN ? tx : i);
+                if (r < R && t < nt1) tile[i][tx] = from[IN ? r * nt1 + t : t * R + r];
+            }
+            __syncthreads();
+            for (int i = ty; i < 32; i += 8) {
+                const int64_t r = r0 + (IN ? tx : i), t = t0 + (IN ? i : tx);
+                if (r < R && t < nt1) to[IN ? t * R + r : r * nt1 + t] = tile[tx][i];
+            }
+            __syncthreads();
+        }
     }
 }
 
@@ -268,56 +408,102 @@ __global__ void sample_kernel(const ShotDev *__restrict__ shots, const SampleTas
     S.rec_out[(int64_t)n * S.nrec + r] = s;
 }
 
-// max of den over the interior box, as float bits (den >= 0).
-__global__ __launch_bounds__(kBlock) void den_max_kernel(const ShotDev *__restrict__ shots, int shot, unsigned *__restrict__ out)
+// Index of interior row `row` (z ny + y) of a shot, x = 0.
+__device__ __forceinline__ int64_t interior_row(const ShotDev &S, unsigned row)
 {
-    const ShotDev &S = shots[shot];
-    const int64_t nx = S.ix1 - S.ix0, ny = S.iy1 - S.iy0, nz = S.iz1 - S.iz0;
-    const int64_t n = nx * ny * nz;
-    unsigned m = 0u;
-    for (int64_t i = gid(); i < n; i += gstride()) {
-        const int64_t x = i % nx, y = (i / nx) % ny, z = i / (nx * ny);
-        const int64_t off = S.L.org + (z + S.iz0) * S.L.plane + (y + S.iy0) * S.L.pitch + (x + S.ix0);
-        m = max(m, __float_as_uint(fmaxf(S.acc1[off], 0.f)));
-    }
-    block_reduce_atomic<true>(m, out);
+    const unsigned ny = (unsigned)(S.iy1 - S.iy0), z = row / ny;
+    return S.L.org + (int64_t)(z + S.iz0) * S.L.plane + (int64_t)(row - z * ny + S.iy0) * S.L.pitch + S.ix0;
 }
 
-// image = num / (den + eps max(den)) on the interior crop (Eq. (3)).
-__global__ void image_kernel(const ShotDev *__restrict__ shots, int shot, const unsigned *__restrict__ dmax_bits,
-                             float eps_rel, float *__restrict__ image, int accumulate, float *__restrict__ num_out,
-                             float *__restrict__ den_out)
+__device__ __forceinline__ unsigned interior_rows(const ShotDev &S)
 {
-    const ShotDev &S = shots[shot];
-    const float stab = eps_rel * __uint_as_float(*dmax_bits);
-    const int64_t nx = S.ix1 - S.ix0, ny = S.iy1 - S.iy0, nz = S.iz1 - S.iz0;
-    const int64_t n = nx * ny * nz;
-    for (int64_t i = gid(); i < n; i += gstride()) {
-        const int64_t x = i % nx, y = (i / nx) % ny, z = i / (nx * ny);
-        const int64_t off = S.L.org + (z + S.iz0) * S.L.plane + (y + S.iy0) * S.L.pitch + (x + S.ix0);
-        const float a = S.acc0[off], b = S.acc1[off];
-        if (image) {
-            const float v = a / (b + stab);
-            image[i] = accumulate ? image[i] + v : v;
-        }
-        if (num_out) num_out[i] = a;
-        if (den_out) den_out[i] = b;
+    return (unsigned)(S.iy1 - S.iy0) * (unsigned)(S.iz1 - S.iz0);
+}
+
+// max of den over the interior box of each shot, as float bits (den >= 0), to
+// out[shot]; blockIdx.y: shot.
+__global__ __launch_bounds__(kBlock) void den_max_kernel(const ShotDev *__restrict__ shots, int nsh,
+                                                         unsigned *__restrict__ out)
+{
+    for (int s = blockIdx.y; s < nsh; s += gridDim.y) {
+        const ShotDev &S = shots[s];
+        const unsigned nx = (unsigned)(S.ix1 - S.ix0);
+        unsigned m = 0u;
+        chunks_do(interior_rows(S), nx, [&](unsigned row, unsigned x0) {
+            const float *b = S.acc1 + interior_row(S, row);
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = b[min(x0 + 64 * u, nx - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m = max(m, __float_as_uint(fmaxf(v[u], 0.f)));
+        });
+        block_reduce_atomic<true>(m, out + s);
+        __syncthreads();
     }
+}
+
+// image = num / (den + eps max(den)) on the interior crop (Eq. (3)) of shots
+// [first, first + count), which share the image buffer and its extents: the
+// shots' values are added (accumulate) or replace each other in their order.
+__global__ __launch_bounds__(kBlock) void image_kernel(const ShotDev *__restrict__ shots, int first, int count,
+                                                       const unsigned *__restrict__ dmax_bits, float eps_rel,
+                                                       float *__restrict__ image, int accumulate,
+                                                       float *__restrict__ num_out, float *__restrict__ den_out)
+{
+    const ShotDev &F = shots[first];
+    const unsigned nx = (unsigned)(F.ix1 - F.ix0);
+    chunks_do(interior_rows(F), nx, [&](unsigned row, unsigned x0) {
+        const int64_t o = (int64_t)row * nx;
+        float v[4] = {};
+        if (image && accumulate)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = image[o + min(x0 + 64 * u, nx - 1)];
+        for (int s = accumulate ? 0 : count - 1; s < count; ++s) {
+#pragma clang fp contract(off)
+            const ShotDev &S = shots[first + s];
+            const float stab = eps_rel * __uint_as_float(dmax_bits[first + s]);
+            const int64_t r = interior_row(S, row);
+            float a[4], b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a[u] = S.acc0[r + min(x0 + 64 * u, nx - 1)];
+                b[u] = S.acc1[r + min(x0 + 64 * u, nx - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float w = a[u] / (b[u] + stab);
+                v[u] = accumulate ? v[u] + w : w;
+                if (x0 + 64 * u < nx) {
+                    if (num_out) num_out[o + x0 + 64 * u] = a[u];
+                    if (den_out) den_out[o + x0 + 64 * u] = b[u];
+                }
+            }
+        }
+        if (image)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (x0 + 64 * u < nx) image[o + x0 + 64 * u] = v[u];
+    });
 }
 
 // Dense interior copy of p^m (field fld[lev] of the shot table) for the
 // migration with a stored source wavefield: out[(z ny + y) nx + x] = p at
 // interior cell (x, y, z).
-__global__ void snap_store_kernel(const ShotDev *__restrict__ shots, int shot, int lev, float *__restrict__ out)
+__global__ __launch_bounds__(kBlock) void snap_store_kernel(const ShotDev *__restrict__ shots, int shot, int lev,
+                                                            float *__restrict__ out)
 {
     const ShotDev &S = shots[shot];
-    const int64_t nx = S.ix1 - S.ix0, ny = S.iy1 - S.iy0, nz = S.iz1 - S.iz0;
-    const int64_t n = nx * ny * nz;
     const float *f = S.fld[lev];
-    for (int64_t i = gid(); i < n; i += gstride()) {
-        const int64_t x = i % nx, y = (i / nx) % ny, z = i / (nx * ny);
-        out[i] = f[S.L.org + (z + S.iz0) * S.L.plane + (y + S.iy0) * S.L.pitch + (x + S.ix0)];
-    }
+    const unsigned nx = (unsigned)(S.ix1 - S.ix0);
+    chunks_do(interior_rows(S), nx, [&](unsigned row, unsigned x0) {
+        const int64_t r = interior_row(S, row);
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = f[r + min(x0 + 64 * u, nx - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (x0 + 64 * u < nx) __builtin_nontemporal_store(v[u], out + (int64_t)row * nx + x0 + 64 * u);
+    });
 }
 
 // flag |= 1 if any of x[0 .. n) is NaN or infinite (one atomic per block).
@@ -459,10 +645,8 @@ __global__ __launch_bounds__(kBlock) void stream_copy_kernel(const copy4 *__rest
 
 hipError_t launch_vrange(const float *v, int64_t n, unsigned *maxmin2, hipStream_t st)
 {
-    hipLaunchKernelGGL(set_u32_kernel, dim3(1), dim3(64), 0, st, maxmin2, 1, 0u);
-    hipLaunchKernelGGL(set_u32_kernel, dim3(1), dim3(64), 0, st, maxmin2 + 1, 1, 0xffffffffu);
-    hipLaunchKernelGGL(vmax_bits_kernel, dim3(grid_reduce(n)), dim3(kBlock), 0, st, v, n, maxmin2);
-    hipLaunchKernelGGL(vmin_bits_kernel, dim3(grid_reduce(n)), dim3(kBlock), 0, st, v, n, maxmin2 + 1);
+    hipLaunchKernelGGL(set_u32_kernel, dim3(1), dim3(64), 0, st, maxmin2, 2, 0u, 0xffffffffu);
+    hipLaunchKernelGGL((vrange_kernel<true>), dim3(grid_reduce(n)), dim3(kBlock), 0, st, v, n, maxmin2);
     return hipGetLastError();
 }
 
@@ -480,8 +664,8 @@ hipError_t launch_stream_copy(const void *src, void *dst, int64_t units, int blo
 
 hipError_t launch_vmax(const float *v, int64_t n, unsigned *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(set_u32_kernel, dim3(1), dim3(64), 0, st, out, 1, 0u);
-    hipLaunchKernelGGL(vmax_bits_kernel, dim3(grid_reduce(n)), dim3(kBlock), 0, st, v, n, out);
+    hipLaunchKernelGGL(set_u32_kernel, dim3(1), dim3(64), 0, st, out, 1, 0u, 0u);
+    hipLaunchKernelGGL((vrange_kernel<false>), dim3(grid_reduce(n)), dim3(kBlock), 0, st, v, n, out);
     return hipGetLastError();
 }
 
@@ -511,9 +695,22 @@ hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t st)
     return hipGetLastError();
 }
 
+// Zeros `bytes` (a multiple of 16) from a 16-byte-aligned address; beyond the
+// memory-side cache, past the caches.
+hipError_t launch_zero(void *p, size_t bytes, hipStream_t st)
+{
+    const int64_t n = (int64_t)(bytes / 16);
+    if (n <= 0) return hipSuccess;
+    if (bytes > ((size_t)256 << 20))
+        hipLaunchKernelGGL((zero_kernel<true>), dim3(grid_for(n)), dim3(kBlock), 0, st, (fill4 *)p, n);
+    else
+        hipLaunchKernelGGL((zero_kernel<false>), dim3(grid_for(n)), dim3(kBlock), 0, st, (fill4 *)p, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_build_dp(const Layout &L, const float *v_pad, float dt_over_h, float *Dp, hipStream_t st)
 {
-    hipLaunchKernelGGL(build_dp_kernel, dim3(grid_for(L.total)), dim3(kBlock), 0, st, L, v_pad, dt_over_h, Dp);
+    hipLaunchKernelGGL(build_dp_kernel, dim3(grid_chunks(L.total / L.pitch, L.pitch)), dim3(kBlock), 0, st, L, v_pad, dt_over_h, Dp);
     return hipGetLastError();
 }
 
@@ -523,10 +720,15 @@ hipError_t launch_unpack(const Layout &L, const float *f, float *out, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_transpose(const float *in, float *out, int64_t R, int64_t C, hipStream_t st)
+// Traces of every shot into (in) or out of the workspace.
+hipError_t launch_traces(const ShotDev *shots, int nsh, int maxrec, int64_t nt1, bool in, hipStream_t st)
 {
-    dim3 grid((unsigned)((C + 31) / 32), (unsigned)((R + 31) / 32));
-    hipLaunchKernelGGL(transpose_kernel, grid, dim3(256), 0, st, in, out, R, C);
+    const dim3 grid((unsigned)((maxrec + 31) / 32), (unsigned)std::min<int64_t>((nt1 + 31) / 32, 65535),
+                    (unsigned)std::min(nsh, 65535));
+    if (in)
+        hipLaunchKernelGGL((traces_kernel<true>), grid, dim3(256), 0, st, shots, nsh, nt1);
+    else
+        hipLaunchKernelGGL((traces_kernel<false>), grid, dim3(256), 0, st, shots, nsh, nt1);
     return hipGetLastError();
 }
 
@@ -547,19 +749,31 @@ hipError_t launch_sample(const ShotDev *shots, const SampleTask *stasks, int nta
     return hipGetLastError();
 }
 
-hipError_t launch_image(const ShotDev *shots, int shot, int64_t ninterior, unsigned *dmax_bits, float eps_rel,
-                        float *image, int accumulate, float *num, float *den, hipStream_t st)
+// max(den) of every shot to dmax_bits[shot].
+hipError_t launch_den_max(const ShotDev *shots, int nsh, int64_t rows, int64_t len, unsigned *dmax_bits, hipStream_t st)
 {
-    hipLaunchKernelGGL(set_u32_kernel, dim3(1), dim3(64), 0, st, dmax_bits, 1, 0u);
-    hipLaunchKernelGGL(den_max_kernel, dim3(grid_reduce(ninterior)), dim3(kBlock), 0, st, shots, shot, dmax_bits);
-    hipLaunchKernelGGL(image_kernel, dim3(grid_for(ninterior)), dim3(kBlock), 0, st, shots, shot,
-                       (const unsigned *)dmax_bits, eps_rel, image, accumulate, num, den);
+    hipLaunchKernelGGL(set_u32_kernel, dim3((nsh + kBlock - 1) / kBlock), dim3(kBlock), 0, st, dmax_bits, nsh, 0u, 0u);
+    // one atomic per block: at most 512 of them on a shot's word
+    const unsigned bx = std::min(grid_chunks((rows + 3) / 4, len), 512u);
+    hipLaunchKernelGGL(den_max_kernel, dim3(bx, (unsigned)std::min(nsh, 65535)), dim3(kBlock), 0, st, shots, nsh,
+                       dmax_bits);
+    return hipGetLastError();
+}
+
+hipError_t launch_image(const ShotDev *shots, int first, int count, int64_t rows, int64_t len,
+                        const unsigned *dmax_bits, float eps_rel, float *image, int accumulate, float *num, float *den,
+                        hipStream_t st)
+{
+    hipLaunchKernelGGL(image_kernel, dim3(grid_chunks(rows, len)), dim3(kBlock), 0, st, shots, first, count, dmax_bits,
+                       eps_rel, image, accumulate, num, den);
     return hipGetLastError();
 }
 
 hipError_t launch_snap_store(const ShotDev *shots, int shot, int lev, int64_t ninterior, float *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(snap_store_kernel, dim3(grid_for(ninterior)), dim3(kBlock), 0, st, shots, shot, lev, out);
+    // blocks of four chunks; the kernel strides over what is left
+    hipLaunchKernelGGL(snap_store_kernel, dim3(grid_chunks((ninterior + kChunk - 1) / kChunk, kChunk)), dim3(kBlock), 0,
+                       st, shots, shot, lev, out);
     return hipGetLastError();
 }
 

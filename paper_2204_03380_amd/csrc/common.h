@@ -73,6 +73,8 @@ struct ShotDev {
     const float *wav;   // wavelet [nt]
     const float *sig;   // receiver signal [nt + 1][nrec] (reverse passes)
     float *rec_out;     // recorded samples [nt + 1][nrec] (forward pass)
+    const float *traces_in;  // the caller's traces [nrec][nt + 1]
+    float *traces_out;
     const int *rnode;   // [nrec][kMaxNodes] node offsets from cell (0,0,0)
     const float *rw;    // [nrec][kMaxNodes] interpolation weights (0 = unused)
     int nrec;

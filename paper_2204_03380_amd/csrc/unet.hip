@@ -80,60 +80,96 @@ struct ConvArgs {
 // blocks share each weight fragment and each activation fragment feeds CBW
 // MFMAs.  Every output element is the same sequence of MFMAs whatever CBW.
 // ---------------------------------------------------------------------------
-// The fused epilogue of a convolution for channels c0 .. c0 + 7 of voxel v
-// (val: the sums before bias): bias, ReLU, the float output y, the stored
-// bfloat16 value r, and out (plus the skip input), as 16-byte accesses.
-template <int COUT>
-__device__ __forceinline__ void epi_store8(const ConvArgs &a, int64_t v, int c0, float (&val)[8])
+// N bfloat16 values as one access (N = 4: 8 bytes, N = 8: 16 bytes).
+template <int N>
+struct Bf16Vec {
+    uint32_t w[N / 2];
+    __device__ __forceinline__ float get(int j) const { return __uint_as_float(j & 1 ? w[j >> 1] & 0xffff0000u : w[j >> 1] << 16); }
+};
+
+template <int N>
+__device__ __forceinline__ Bf16Vec<N> bf_load(const uint16_t *p)
+{
+    Bf16Vec<N> v;
+    if constexpr (N == 8) {
+        const uint4 t = *reinterpret_cast<const uint4 *>(p);
+        v.w[0] = t.x; v.w[1] = t.y; v.w[2] = t.z; v.w[3] = t.w;
+    } else {
+        const uint2 t = *reinterpret_cast<const uint2 *>(p);
+        v.w[0] = t.x; v.w[1] = t.y;
+    }
+    return v;
+}
+
+template <int N>
+__device__ __forceinline__ void bf_store(uint16_t *p, const float (&f)[N])
+{
+    uint32_t w[N / 2];
+#pragma unroll
+    for (int q = 0; q < N / 2; ++q) w[q] = (uint32_t)f2bf(f[2 * q]) | ((uint32_t)f2bf(f[2 * q + 1]) << 16);
+    if constexpr (N == 8) *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    else *reinterpret_cast<uint2 *>(p) = make_uint2(w[0], w[1]);
+}
+
+// The bfloat16 input of the epilogue, if it has one (a call has a mask or a
+// skip input, not both).
+__device__ __forceinline__ const uint16_t *epi_aux(const ConvArgs &a)
+{
+    return a.gout ? a.mask : a.out ? a.skip : nullptr;
+}
+
+// The fused epilogue of a convolution for channels c0 .. c0 + N - 1 of voxel
+// v (val: the sums before bias): bias, ReLU, the float output y, the stored
+// bfloat16 value r, and out (plus the skip input), as 8- or 16-byte accesses.
+// aux: those channels of a.mask (with a.gout) or of a.skip.
+template <int COUT, int N>
+__device__ __forceinline__ void epi_store(const ConvArgs &a, int64_t v, int c0, const float (&bias)[N],
+                                          const Bf16Vec<N> &aux, float (&val)[N])
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        val[j] += a.bias ? a.bias[c0 + j] : 0.f;
+    for (int j = 0; j < N; ++j) {
+        val[j] += bias[j];
         if (a.relu) val[j] = fmaxf(val[j], 0.f);
     }
     if (a.y) {
         if (a.ych == COUT) {
             float4 *py = reinterpret_cast<float4 *>(a.y + v * COUT + c0);
-            py[0] = make_float4(val[0], val[1], val[2], val[3]);
-            py[1] = make_float4(val[4], val[5], val[6], val[7]);
+#pragma unroll
+            for (int q = 0; q < N / 4; ++q) py[q] = make_float4(val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]);
         } else {
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
+            for (int j = 0; j < N; ++j)
                 if (c0 + j < a.ych) a.y[v * a.ych + c0 + j] = val[j];
         }
     }
     const int64_t o = v * COUT + c0;
     if (a.gout) {  // the next layer's ReLU gradient (a.ych == COUT)
-        const uint4 mk = *reinterpret_cast<const uint4 *>(a.mask + o);
-        const uint16_t *me = reinterpret_cast<const uint16_t *>(&mk);
-        uint32_t w[4];
+        float gv[N];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            w[q] = (uint32_t)(bf2f(me[2 * q]) > 0.f ? f2bf(val[2 * q]) : (uint16_t)0) |
-                   ((uint32_t)(bf2f(me[2 * q + 1]) > 0.f ? f2bf(val[2 * q + 1]) : (uint16_t)0) << 16);
-        *reinterpret_cast<uint4 *>(a.gout + o) = make_uint4(w[0], w[1], w[2], w[3]);
+        for (int j = 0; j < N; ++j) gv[j] = aux.get(j) > 0.f ? val[j] : 0.f;
+        bf_store<N>(a.gout + o, gv);
     }
-    if (a.r) {
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[q] = (uint32_t)f2bf(val[2 * q]) | ((uint32_t)f2bf(val[2 * q + 1]) << 16);
-        *reinterpret_cast<uint4 *>(a.r + o) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
+    if (a.r) bf_store<N>(a.r + o, val);
     if (a.out) {
-        float ov[8];
+        float ov[N];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) ov[j] = val[j];
-        if (a.skip) {
-            const uint4 sk = *reinterpret_cast<const uint4 *>(a.skip + o);
-            const uint16_t *se = reinterpret_cast<const uint16_t *>(&sk);
+        for (int j = 0; j < N; ++j) ov[j] = val[j];
+        if (a.skip)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) ov[j] = val[j] + bf2f(se[j]);
-        }
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[q] = (uint32_t)f2bf(ov[2 * q]) | ((uint32_t)f2bf(ov[2 * q + 1]) << 16);
-        *reinterpret_cast<uint4 *>(a.out + o) = make_uint4(w[0], w[1], w[2], w[3]);
+            for (int j = 0; j < N; ++j) ov[j] = val[j] + aux.get(j);
+        bf_store<N>(a.out + o, ov);
     }
+}
+
+template <int COUT>
+__device__ __forceinline__ void epi_store8(const ConvArgs &a, int64_t v, int c0, float (&val)[8])
+{
+    float bias[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) bias[j] = a.bias ? a.bias[c0 + j] : 0.f;
+    Bf16Vec<8> aux = {};
+    if (const uint16_t *p = epi_aux(a)) aux = bf_load<8>(p + v * COUT + c0);
+    epi_store<COUT, 8>(a, v, c0, bias, aux, val);
 }
 
 // Stages rows 2*half, 2*half + 1 of a wavefront's MFMA accumulators for one
@@ -283,81 +319,96 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvArgs a)
 
 // ---------------------------------------------------------------------------
 // Forward convolution with the input staged in LDS (layers of at most 32
-// input and 32 output channels on grids that give enough workgroups: the
-// full-resolution level).  A workgroup of four
-// wavefronts owns an x-segment of 64 voxels of four consecutive y rows (one
-// row per wavefront) and marches z over lz planes.  The input planes z - 1,
-// z, z + 1 of the segment's halo (6 rows of 66 voxels, all channels) sit in
-// a three-plane LDS ring, so every activation fragment of the 27 taps is
-// read from LDS instead of L1/L2.  The next plane is fetched into registers
-// while the current one is computed, then written to the ring slot that the
-// previous plane left.  Each output element is the same MFMA sequence as in
-// conv_fwd_kernel (same K order, same fragments), so results are equal bit
-// for bit.
+// input and 32 output channels, and 64 -> 32, on grids that give enough
+// workgroups).  A workgroup of four wavefronts owns an x-segment of 64 voxels
+// of four consecutive y rows (one row per wavefront) and marches z over lz
+// planes.  The input planes z - 1, z, z + 1 of the segment's halo (6 rows of
+// 66 voxels, all channels) sit in a three-plane LDS ring, so every activation
+// fragment of the 27 taps is read from LDS instead of L1/L2.  The next plane
+// is fetched into registers while the current one is computed, then written
+// to the ring slot that the previous plane left.  Each output element is the
+// same MFMA sequence as in conv_fwd_kernel (same K order, same products), so
+// results are equal bit for bit.
+//
+// What bounds it: with few wavefronts per SIMD (two workgroups per CU, one at
+// 64 channels) each chunk's LDS reads, its weights and the epilogue's trip
+// through LDS were waited for in turn, and the matrix cores ran 17 % (32 ->
+// 16) and 28 % (64 -> 32) of the time.  Hence:
+//  - a chunk's activations are read one chunk ahead;
+//  - all weights stay in registers where they fit, else run PD chunks ahead;
+//  - 16-byte vectors are swizzled over the banks by voxel (45 % of the LDS
+//    cycles of the 32-channel layer were conflicts, 70 % at 64);
+//  - the weights are the MFMA's A operand and the voxels its B operand, so
+//    that a lane ends up with 4 (COUT 16) or, with the rows of the two
+//    weight fragments dealt out accordingly, 8 consecutive channels of one
+//    voxel and stores them as they are;
+//  - halo cells outside the grid are buffer loads past the plane's end,
+//    which return zero without a branch;
+//  - the epilogue's input (skip or mask) is loaded before the plane's MFMAs,
+//    and the next plane goes to LDS before the epilogue, so that no wait
+//    includes the epilogue's stores.
+// Measured before and now (us): 32 -> 16 at 128 x 256 x 256 523 and 414 (of
+// which 270 are its traffic at the copy rate), 64 -> 32 at 64 x 128 x 128 360
+// and 284, at 2 x 45 x 52 x 70 223 and 181, 16 -> 32 at 64 x 128 x 128 70 and
+// 55.
 // ---------------------------------------------------------------------------
 constexpr int kLdsX = 64, kLdsY = 4;
 
 template <int CIN>
 struct LdsTile {
     static constexpr int XW = kLdsX + 2, YW = kLdsY + 2;
-    static constexpr int PLANE = YW * XW * CIN;       // bf16 elements per plane
     static constexpr int VPR = CIN / 8;               // 16-byte vectors per voxel
     static constexpr int NV = YW * XW * VPR;          // vectors per plane
     static constexpr int PER = (NV + 255) / 256;      // vectors per thread
+    static constexpr int PLANE = NV * 16;             // bytes per plane
+
+    // Vector c of voxel vox is stored in place c ^ swz(vox): 16 voxels in a
+    // row put a channel vector into different banks.  Period 16 in vox, so
+    // that a wavefront's four 16-voxel blocks lie at constant distances.
+    static __device__ __forceinline__ int swz(int vox)
+    {
+        if (CIN == 64) return (vox + (vox >> 3 & 1)) & 7;
+        if (CIN == 32) return ((vox >> 1) + (vox >> 3 & 1)) & 3;
+        return 0;
+    }
 };
 
-// Plane z of the halo tile into registers (zeros outside the grid).
-template <int CIN>
-__device__ __forceinline__ void lds_fetch(const ConvArgs &a, uint4 (&v)[LdsTile<CIN>::PER], int64_t nbase, int z,
-                                          int y0, int x0)
+// The plane's bytes as a buffer (no bytes outside the sample's planes): loads
+// beyond its end return zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const ConvArgs &a, int64_t nbase, int z, int cin)
 {
-    using T = LdsTile<CIN>;
-    const bool zin = (unsigned)z < (unsigned)a.d;
-#pragma unroll
-    for (int k = 0; k < T::PER; ++k) {
-        const int i = threadIdx.x + 256 * k;
-        const int c8 = i % T::VPR, vox = i / T::VPR;
-        const int xx = vox % T::XW, yy = vox / T::XW;
-        const int gx = x0 - 1 + xx, gy = y0 - 1 + yy;
-        v[k] = uint4{0u, 0u, 0u, 0u};
-        if (i < T::NV && zin && (unsigned)gx < (unsigned)a.w && (unsigned)gy < (unsigned)a.h)
-            v[k] = *reinterpret_cast<const uint4 *>(a.x + (((nbase + z) * a.h + gy) * a.w + gx) * CIN + c8 * 8);
-    }
+    const bool in = (unsigned)z < (unsigned)a.d;
+    const int64_t elems = (int64_t)a.h * a.w * cin;
+    const uint16_t *p = a.x + (nbase + (in ? z : 0)) * elems;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p), 0, in ? (int)(elems * 2) : 0, 0x00027000);
 }
 
-template <int CIN>
-__device__ __forceinline__ void lds_store(uint16_t *dst, const uint4 (&v)[LdsTile<CIN>::PER])
+// Depth of the weight ring in chunks: the largest divisor of the chunk count
+// whose fragments fit the registers that the layer leaves: all of 32 -> 16
+// (27 chunks; ring of 9: 445 us at 128 x 256 x 256, all 414), nine chunks of
+// 64 -> 32 (3: 296, 9: 284, 13 and more: 289), seven of 16 -> 32 (56; all 14
+// spill: 64).
+constexpr int lds_weight_depth(int cin, int nch, int cb)
 {
-    using T = LdsTile<CIN>;
-#pragma unroll
-    for (int k = 0; k < T::PER; ++k) {
-        const int i = threadIdx.x + 256 * k;
-        if (i < T::NV) *reinterpret_cast<uint4 *>(dst + (int64_t)(i / T::VPR) * CIN + (i % T::VPR) * 8) = v[k];
-    }
-}
-
-// Depth of conv_fwd_lds_kernel's weight ring: the largest divisor of the
-// chunk count whose fragments fit in 40 registers; 1 (no ring: each chunk
-// loads its own fragments) for two output blocks over 27 chunks, where the
-// unrolled march would need more registers than two waves per SIMD allow.
-constexpr int lds_weight_depth(int nch, int cb)
-{
-    if (cb > 1 && nch > 14) return 1;
+    const int regs = cb == 1 ? 112 : cin == 64 ? 72 : cin == 16 ? 56 : 40;
     int best = 1;
     for (int d = 1; d <= nch; ++d)
-        if (nch % d == 0 && d * cb * 4 <= 40) best = d;
+        if (nch % d == 0 && d * cb * 4 <= regs) best = d;
     return best;
 }
 
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void conv_fwd_lds_kernel(ConvArgs a, int tiles_x, int tiles_y, int tiles_z, int lz,
-                                                           int64_t ntiles)
+__global__ __launch_bounds__(256, CIN == 64 ? 1 : 2) void conv_fwd_lds_kernel(ConvArgs a, int tiles_x, int tiles_y,
+                                                                              int tiles_z, int lz, int64_t ntiles)
 {
     using T = LdsTile<CIN>;
     constexpr int K = 27 * CIN;
-    constexpr int KP = (K + 31) / 32 * 32;  // chunks past tap 26 are zero, as in conv_fwd_kernel
-    constexpr int CB = COUT / 16;
-    __shared__ __attribute__((aligned(16))) uint16_t ring[3 * T::PLANE];
+    constexpr int NCH = (K + 31) / 32;  // chunks past tap 26 are zero, as in conv_fwd_kernel
+    constexpr int CB = COUT / 16, N = 4 * CB;
+    constexpr int PD = lds_weight_depth(CIN, NCH, CB);
+    constexpr int VB = CIN * 2;         // bytes per voxel
+    static_assert(CB <= 2, "a lane holds up to eight consecutive channels");
+    __shared__ __attribute__((aligned(16))) char ring[3 * T::PLANE];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, g = lane >> 4;
     int64_t b = xcd_block(blockIdx.x, a.nblocks);
@@ -372,106 +423,135 @@ __global__ __launch_bounds__(256) void conv_fwd_lds_kernel(ConvArgs a, int tiles
     const int z1 = min(z0 + lz, a.d);
     const int64_t nbase = n * a.d;               // first plane of this sample
     const int yw = y0 + wave;                    // this wavefront's output row
-    const bool row_ok = yw < a.h;
     const uint4 zero = {0u, 0u, 0u, 0u};
 
-    // Weight fragments run PD chunks ahead of their MFMAs through a ring of
-    // registers (PD divides the chunk count, so chunk c of every plane uses
-    // slot c mod PD and the ring carries on from one plane to the next:
-    // the weights are the same for every plane).  One load per chunk
-    // waited on right away would leave each chunk waiting a full memory
-    // latency.
-    constexpr int NCH = KP / 32;
-    constexpr int PD = lds_weight_depth(NCH, CB);
-    auto load_b = [&](int c, uint4(&B)[CB]) {
+    // Weights: fragment row r16 of block cb is channel row(cb).
+    uint4 Bq[PD][CB];
+    auto load_b = [&](int c, uint4(&B)[CB]) __attribute__((always_inline)) {
         const int kk = c * 32 + 8 * g;
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-            B[cb] = kk / CIN < 27 ? *reinterpret_cast<const uint4 *>(a.wt + (int64_t)(cb * 16 + r16) * K + kk) : zero;
+        for (int cb = 0; cb < CB; ++cb) {
+            const int row = CB == 1 ? r16 : 8 * (r16 >> 2) + 4 * cb + (r16 & 3);
+            B[cb] = kk / CIN < 27 ? *reinterpret_cast<const uint4 *>(a.wt + (int64_t)row * K + kk) : zero;
+        }
     };
-    uint4 Bq[PD][CB];
-    if constexpr (PD > 1) {
 #pragma unroll
-        for (int i = 0; i < PD; ++i) load_b(i, Bq[i]);
+    for (int i = 0; i < PD; ++i) load_b(i, Bq[i]);
+    float bias[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) bias[j] = a.bias ? a.bias[N * g + j] : 0.f;
+
+    // This thread's vectors of a plane: where they come from and go to.
+    unsigned from[T::PER];
+    int to[T::PER];
+#pragma unroll
+    for (int k = 0; k < T::PER; ++k) {
+        const int i = min((int)threadIdx.x + 256 * k, T::NV - 1);
+        const int c8 = i % T::VPR, vox = i / T::VPR;
+        const int gx = x0 - 1 + vox % T::XW, gy = y0 - 1 + vox / T::XW;
+        const bool in = (unsigned)gx < (unsigned)a.w && (unsigned)gy < (unsigned)a.h;
+        from[k] = in ? (unsigned)((gy * a.w + gx) * VB + c8 * 16) : 0x80000000u;
+        to[k] = (vox * T::VPR + (c8 ^ T::swz(vox))) * 16;
     }
     uint4 next[T::PER];
-    lds_fetch<CIN>(a, next, nbase, z0 - 1, y0, x0);
-    lds_store<CIN>(ring + ((z0 + 2) % 3) * T::PLANE, next);
-    lds_fetch<CIN>(a, next, nbase, z0, y0, x0);
-    lds_store<CIN>(ring + (z0 % 3) * T::PLANE, next);
-    lds_fetch<CIN>(a, next, nbase, z0 + 1, y0, x0);
+    auto fetch = [&](int z) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rs = plane_rsrc(a, nbase, z, CIN);
+#pragma unroll
+        for (int k = 0; k < T::PER; ++k)
+            next[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, from[k], 0, 0));
+    };
+    auto put = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < T::PER; ++k)
+            if ((k + 1) * 256 <= T::NV || (int)threadIdx.x + 256 * k < T::NV)
+                *reinterpret_cast<uint4 *>(ring + slot + to[k]) = next[k];
+    };
+
+    // Byte offsets of this lane's voxel of row wave + dy, column r16 + dx.
+    int tapo[CIN == 16 ? 1 : 9];
+    const int vox0 = (wave + 1) * T::XW + 1 + r16;
+    if constexpr (CIN == 16) {
+        tapo[0] = vox0 * VB + (g & 1) * 16;
+    } else {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const int vox = vox0 + (t / 3 - 1) * T::XW + t % 3 - 1;
+            tapo[t] = (vox * T::VPR + (g ^ T::swz(vox))) * 16;
+        }
+    }
+    int sm = 0, s0 = T::PLANE, sp = 2 * T::PLANE;  // slots of planes z - 1, z, z + 1
+    auto load_a = [&](int c, uint4(&A)[4]) __attribute__((always_inline)) {
+        int o;
+        bool tv = true;
+        if constexpr (CIN == 16) {  // a chunk is two taps of 16 channels
+            auto tap = [&](int t) {
+                return (t / 9 == 0 ? sm : t / 9 == 1 ? s0 : sp) + ((t / 3 % 3 - 1) * T::XW + t % 3 - 1) * VB;
+            };
+            o = tapo[0] + (g >> 1 ? tap(min(2 * c + 1, 26)) : tap(2 * c));
+            tv = 2 * c + 1 < 27 || g < 2;
+        } else {
+            const int t = c * 32 / CIN, half = c * 32 % CIN / 32;
+            o = (t / 9 == 0 ? sm : t / 9 == 1 ? s0 : sp) + (half ? tapo[t % 9] ^ 64 : tapo[t % 9]);
+        }
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) {
+            A[rb] = *reinterpret_cast<const uint4 *>(ring + o + rb * 16 * VB);
+            if (!tv) A[rb] = zero;
+        }
+    };
+
+    fetch(z0 - 1);
+    put(sm);
+    fetch(z0);
+    put(s0);
+    fetch(z0 + 1);
+    put(sp);
+    const uint16_t *auxp = epi_aux(a);
+    const bool row_ok = yw < a.h;
     for (int z = z0; z < z1; ++z) {
-        lds_store<CIN>(ring + ((z + 1) % 3) * T::PLANE, next);  // the slot plane z - 2 left
         __syncthreads();
-        if (z + 1 < z1) lds_fetch<CIN>(a, next, nbase, z + 2, y0, x0);  // in flight during this plane
+        // in flight during this plane: plane z + 2, the epilogue's input
+        const bool more = z + 1 < z1;
+        if (more) fetch(z + 2);
+        const int64_t vrow = ((nbase + z) * a.h + yw) * (int64_t)a.w + x0 + r16;
+        Bf16Vec<N> aux[4] = {};
+        if (auxp)
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb)
+                if (row_ok && x0 + rb * 16 + r16 < a.w) aux[rb] = bf_load<N>(auxp + (vrow + rb * 16) * COUT + N * g);
         f32x4 acc[4][CB];
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto chunk = [&](int c, const uint4(&B)[CB]) {
-            const int kk = c * 32 + 8 * g;
-            const int tap = kk / CIN;
-            const int ci0 = kk - tap * CIN;
-            const bool tv = tap < 27;
-            const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-            const uint16_t *pl = ring + ((z + dz + 3) % 3) * T::PLANE + ((wave + 1 + dy) * T::XW + 1 + dx) * CIN + ci0;
-            uint4 A[4];
+        uint4 A[2][4];
+        load_a(0, A[0]);
 #pragma unroll
-            for (int rb = 0; rb < 4; ++rb) A[rb] = tv ? *reinterpret_cast<const uint4 *>(pl + (rb * 16 + r16) * CIN) : zero;
+        for (int c = 0; c < NCH; ++c) {
+            if (c + 1 < NCH) load_a(c + 1, A[(c + 1) & 1]);
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = mfma16(A[rb], B[cb], acc[rb][cb]);
-        };
-        if constexpr (PD > 1) {
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                chunk(c, Bq[c % PD]);
-                load_b((c + PD) % NCH, Bq[c % PD]);  // chunk c + PD, of this plane or the next
-                // the scheduler would otherwise sink each load to its use
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll 4
-            for (int kc = 0; kc < KP; kc += 32) {
-                const int kk = kc + 8 * g;
-                const int tap = kk / CIN;
-                const int ci0 = kk - tap * CIN;
-                const bool tv = tap < 27;
-                const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-                const uint16_t *pl =
-                    ring + ((z + dz + 3) % 3) * T::PLANE + ((wave + 1 + dy) * T::XW + 1 + dx) * CIN + ci0;
-                uint4 A[4];
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb)
-                    A[rb] = tv ? *reinterpret_cast<const uint4 *>(pl + (rb * 16 + r16) * CIN) : zero;
-                uint4 B[CB];
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    B[cb] = tv ? *reinterpret_cast<const uint4 *>(a.wt + (int64_t)(cb * 16 + r16) * K + kk) : zero;
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = mfma16(A[rb], B[cb], acc[rb][cb]);
-            }
+                for (int cb = 0; cb < CB; ++cb) acc[rb][cb] = mfma16(Bq[c % PD][cb], A[c & 1][rb], acc[rb][cb]);
+            if constexpr (PD < NCH) load_b((c + PD) % NCH, Bq[c % PD]);  // of this plane or the next
+            // the scheduler would otherwise sink each load to its use
+            __builtin_amdgcn_sched_barrier(0);
         }
-        // Epilogue through LDS (the slot of plane z - 1, free once every wave
-        // is past its MFMAs): 8 channels of one voxel per lane.
         __syncthreads();  // every wave is done with plane z - 1's slot
-        float *scr = reinterpret_cast<float *>(ring + ((z + 2) % 3) * T::PLANE) + wave * (32 * kEpiStride);
-        const int64_t vrow = ((nbase + z) * a.h + yw) * (int64_t)a.w;
+        // before the epilogue: the wait for the plane then does not wait for its stores
+        if (more) put(sm);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
+        for (int rb = 0; rb < 4; ++rb) {
+            float val[N];
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const f32x4 acc2[2] = {acc[2 * half][cb], acc[2 * half + 1][cb]};
-                float val[8];
-                epi_transpose(scr, acc2, lane, val);
-                const int xo = x0 + half * 32 + (lane & 31);
-                if (row_ok && xo < a.w) epi_store8<COUT>(a, vrow + xo, cb * 16 + 8 * (lane >> 5), val);
-            }
-        __syncthreads();  // every wave is done with its scratch before the slot is refilled
+            for (int j = 0; j < N; ++j) val[j] = acc[rb][j / 4][j % 4];
+            if (row_ok && x0 + rb * 16 + r16 < a.w) epi_store<COUT, N>(a, vrow + rb * 16, N * g, bias, aux[rb], val);
+        }
+        const int t = sm;
+        sm = s0;
+        s0 = sp;
+        sp = t;
     }
 }
 
@@ -1651,7 +1731,8 @@ void launch_fwd_t(const ConvArgs &a, hipStream_t st)
         const int lz = (int)std::min<int64_t>(16, std::max<int64_t>(4, cols * a.d / kLdsBlocks));
         const int tz = (a.d + lz - 1) / lz;
         const int64_t tiles = cols * tz;
-        if (a.w >= kLdsX && tiles >= kLdsMinBlocks && g_conv_lds.load()) {
+        // (a plane is one buffer of less than 2 GiB)
+        if (a.w >= kLdsX && tiles >= kLdsMinBlocks && (int64_t)a.h * a.w * CI < ((int64_t)1 << 30) && g_conv_lds.load()) {
             ConvArgs b = a;
             b.nblocks = (tiles + kNumXcd - 1) / kNumXcd * kNumXcd;
             hipLaunchKernelGGL((conv_fwd_lds_kernel<CI, CO>), dim3((unsigned)b.nblocks), dim3(256), 0, st, b, tx, ty,

@@ -974,34 +974,43 @@ hipError_t sum_parts(const float *part0, int64_t n0, float *tmp0, float *out0, c
 
 // ---------------------------------------------------------------------------
 // One-channel layers (the network's input and output): a 1 -> 16 or 16 -> 1
-// convolution is 432 multiply-adds per voxel, too thin for the matrix
-// cores, so one thread computes one voxel on the vector units.  Weights
-// (bfloat16, the packed layout [COUT][27][CIN]) are held in LDS as floats.
+// convolution is 432 multiply-adds per voxel, too thin for the matrix cores,
+// so the vector units compute it, in float32 and in the order of the taps.
+// 8.4 M voxels are 92 us of multiply-adds there and 60 us of traffic; with
+// one voxel per thread, reading weights (1 -> 16) or unpacking activations
+// (16 -> 1) for every multiply-add, they took 274 and 346 us.  A thread
+// computes kThinRows voxels one above the other, which share the weights of
+// a tap and the unpacked activations of a row.
 // ---------------------------------------------------------------------------
 constexpr int kThin = 16;  // channels on the wide side
+constexpr int kThinRows = 4;
 
-__device__ __forceinline__ void thin_decode(int64_t v, int D, int H, int W, int &z, int &y, int &x)
+// Threads of a one-channel convolution: x fastest, then blocks of kThinRows
+// rows, planes, samples.
+__host__ __device__ inline int64_t thin_threads(int64_t nvox, int h, int w)
 {
-    if (v <= 0xffffffffll) {  // 32-bit division, far cheaper than the 64-bit sequence
-        const uint32_t u = (uint32_t)v, t = u / (uint32_t)W, t2 = t / (uint32_t)H;
-        x = (int)(u - t * (uint32_t)W);
-        y = (int)(t - t2 * (uint32_t)H);
-        z = (int)(t2 % (uint32_t)D);
-        return;
-    }
-    const int64_t t = v / W;
-    x = (int)(v - t * W);
-    const int64_t t2 = t / H;
-    y = (int)(t - t2 * H);
-    z = (int)(t2 % D);
+    return nvox / ((int64_t)h * w) * ((h + kThinRows - 1) / kThinRows) * w;
 }
 
-__device__ __forceinline__ bool thin_tap(int tap, int z, int y, int x, int D, int H, int W, int64_t HW,
-                                         int64_t &off)
+// First voxel of thread i (z: plane within its sample).
+__device__ __forceinline__ int64_t thin_decode(int64_t i, int D, int H, int W, int &z, int &y, int &x)
 {
-    const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-    off = dz * HW + (int64_t)dy * W + dx;
-    return (unsigned)(z + dz) < (unsigned)D && (unsigned)(y + dy) < (unsigned)H && (unsigned)(x + dx) < (unsigned)W;
+    const int hb = (H + kThinRows - 1) / kThinRows;
+    int64_t plane;
+    if (i <= 0xffffffffll) {  // 32-bit division, far cheaper than the 64-bit sequence
+        const uint32_t u = (uint32_t)i, t = u / (uint32_t)W, p = t / (uint32_t)hb;
+        x = (int)(u - t * (uint32_t)W);
+        y = (int)(t - p * (uint32_t)hb) * kThinRows;
+        z = (int)(p % (uint32_t)D);
+        plane = p;
+    } else {
+        const int64_t t = i / W;
+        x = (int)(i - t * W);
+        plane = t / hb;
+        y = (int)(t - plane * hb) * kThinRows;
+        z = (int)(plane % D);
+    }
+    return (plane * H + y) * W + x;
 }
 
 // The fused epilogue of conv_fwd_kernel for one voxel and channel.
@@ -1016,153 +1025,208 @@ __device__ __forceinline__ void thin_store(const ConvArgs &a, int64_t v, int co,
 }
 
 // 1 -> 16 channels.  Weights in LDS as [tap][channel] so that one tap's
-// sixteen weights are four 16-byte reads; each channel sums its taps in
-// ascending order.
+// sixteen weights are four 16-byte reads, used for kThinRows voxels; each
+// channel sums its taps in ascending order.
 __global__ __launch_bounds__(256) void conv_thin_in_kernel(ConvArgs a)
 {
+    constexpr int R = kThinRows;
     __shared__ float4 wsh4[27 * kThin / 4];
     float *wsh = reinterpret_cast<float *>(wsh4);
     for (int i = threadIdx.x; i < kThin * 27; i += blockDim.x) wsh[(i % 27) * kThin + i / 27] = bf2f(a.wt[i]);
     __syncthreads();
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = thin_threads(a.nvox, a.h, a.w);
     const int lane = threadIdx.x & 63;
-    const int64_t vbase = v - lane;  // the wavefront's first voxel
     // whole wavefronts only: the stores at the end are shared by its lanes
-    if (vbase >= a.nvox) return;
-    const bool live = v < a.nvox;
+    if (i - lane >= n) return;
     int z, y, x;
-    thin_decode(live ? v : vbase, a.d, a.h, a.w, z, y, x);
+    const int64_t v0 = thin_decode(i < n ? i : i - lane, a.d, a.h, a.w, z, y, x);
+    const int live = i < n ? min(a.h - y, R) : 0;  // rows that this thread stores
     const int64_t HW = (int64_t)a.h * a.w;
-    float acc[kThin];
+    float acc[R][kThin];
 #pragma unroll
-    for (int co = 0; co < kThin; ++co) acc[co] = 0.f;
-#pragma unroll 3
-    for (int t = 0; t < 27; ++t) {
-        int64_t off;
-        const float xt = thin_tap(t, z, y, x, a.d, a.h, a.w, HW, off) && live ? bf2f(a.x[v + off]) : 0.f;
+    for (int j = 0; j < R; ++j)
 #pragma unroll
-        for (int q = 0; q < kThin / 4; ++q) {
-            const float4 w4 = wsh4[t * (kThin / 4) + q];
-            acc[4 * q] = fmaf(w4.x, xt, acc[4 * q]);
-            acc[4 * q + 1] = fmaf(w4.y, xt, acc[4 * q + 1]);
-            acc[4 * q + 2] = fmaf(w4.z, xt, acc[4 * q + 2]);
-            acc[4 * q + 3] = fmaf(w4.w, xt, acc[4 * q + 3]);
+        for (int co = 0; co < kThin; ++co) acc[j][co] = 0.f;
+    const bool left = x > 0, right = x + 1 < a.w;
+#pragma unroll 1
+    for (int dz = -1; dz <= 1; ++dz) {
+        float xt[R + 2][3];
+#pragma unroll
+        for (int r = 0; r < R + 2; ++r) {
+            const bool in = (unsigned)(z + dz) < (unsigned)a.d && (unsigned)(y + r - 1) < (unsigned)a.h;
+            const uint16_t *row = a.x + v0 + dz * HW + (int64_t)(r - 1) * a.w;
+            xt[r][0] = in && left ? bf2f(row[-1]) : 0.f;
+            xt[r][1] = in ? bf2f(row[0]) : 0.f;
+            xt[r][2] = in && right ? bf2f(row[1]) : 0.f;
         }
-    }
-    float val[kThin];
+        const float4 *w = wsh4 + (dz + 1) * 9 * (kThin / 4);
 #pragma unroll
-    for (int co = 0; co < kThin; ++co) {
-        const float t = acc[co] + (a.bias ? a.bias[co] : 0.f);
-        val[co] = a.relu ? fmaxf(t, 0.f) : t;
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int q = 0; q < kThin / 4; ++q) {
+                const float4 w4 = w[t * (kThin / 4) + q];
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const float xv = xt[j + t / 3][t % 3];
+                    acc[j][4 * q] = fmaf(w4.x, xv, acc[j][4 * q]);
+                    acc[j][4 * q + 1] = fmaf(w4.y, xv, acc[j][4 * q + 1]);
+                    acc[j][4 * q + 2] = fmaf(w4.z, xv, acc[j][4 * q + 2]);
+                    acc[j][4 * q + 3] = fmaf(w4.w, xv, acc[j][4 * q + 3]);
+                }
+            }
     }
-    // The epilogue of thin_store for all 16 channels.  Each output goes
-    // through the wavefront's LDS rows (voxel lane, kEpiStride floats) so
-    // that a store instruction writes 1 KB contiguous across the lanes
-    // instead of 16 bytes per lane at a 32- or 64-byte stride.
+    // The epilogue of thin_store for all 16 channels, row by row.  Each output
+    // goes through the wavefront's LDS rows (voxel lane, kEpiStride floats) so
+    // that a store instruction writes whole voxels back to back across the
+    // lanes instead of 16 bytes per lane at a 32- or 64-byte stride: 16-byte
+    // chunk c of a row of the wavefront belongs to the voxel of lane c / 2
+    // (c / 4 for the float output).
     __shared__ __attribute__((aligned(16))) float tscr[4][64 * kEpiStride];
     float *scr = tscr[threadIdx.x >> 6];
-    const int nlive = (int)(a.nvox - vbase < 64 ? a.nvox - vbase : 64);
     auto wave_sync = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    // 16 bfloat16 (two 16-byte chunks) per voxel
-    auto store_bf16 = [&](uint16_t *dst, const uint32_t (&w)[kThin / 2]) {
-        uint4 *row = reinterpret_cast<uint4 *>(scr + lane * kEpiStride);
-        row[0] = make_uint4(w[0], w[1], w[2], w[3]);
-        row[1] = make_uint4(w[4], w[5], w[6], w[7]);
-        wave_sync();
+    int64_t bv[2];  // first voxel and rows of the lanes whose bfloat16 chunks this lane stores
+    int bl[2];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int chunk = k * 64 + lane, vox = chunk >> 1;
-            if (vox < nlive)
-                *reinterpret_cast<uint4 *>(dst + vbase * kThin + chunk * 8) =
-                    *reinterpret_cast<const uint4 *>(scr + vox * kEpiStride + 4 * (chunk & 1));
-        }
-        wave_sync();  // reads done before the rows are written again
-    };
-    if (a.y) {
-        if (a.ych == kThin) {
-            float4 *row = reinterpret_cast<float4 *>(scr + lane * kEpiStride);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) row[q] = make_float4(val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]);
-            wave_sync();
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int chunk = k * 64 + lane, vox = chunk >> 2;
-                if (vox < nlive)
-                    *reinterpret_cast<float4 *>(a.y + vbase * kThin + chunk * 4) =
-                        *reinterpret_cast<const float4 *>(scr + vox * kEpiStride + 4 * (chunk & 3));
-            }
-            wave_sync();
-        } else if (live) {
-#pragma unroll
-            for (int co = 0; co < kThin; ++co)
-                if (co < a.ych) a.y[v * a.ych + co] = val[co];
-        }
+    for (int k = 0; k < 2; ++k) {
+        const int from = (k * 64 + lane) >> 1;
+        bv[k] = __shfl((long long)v0, from);
+        bl[k] = __shfl(live, from);
     }
-    uint32_t rb[kThin / 2], ob[kThin / 2];
 #pragma unroll
-    for (int q = 0; q < kThin / 2; ++q) {
-        rb[q] = (uint32_t)f2bf(val[2 * q]) | ((uint32_t)f2bf(val[2 * q + 1]) << 16);
+    for (int j = 0; j < R; ++j) {
+        // 16 bfloat16 (two 16-byte chunks) per voxel
+        auto store_bf16 = [&](uint16_t *dst, const uint32_t (&w)[kThin / 2]) {
+            uint4 *row = reinterpret_cast<uint4 *>(scr + lane * kEpiStride);
+            row[0] = make_uint4(w[0], w[1], w[2], w[3]);
+            row[1] = make_uint4(w[4], w[5], w[6], w[7]);
+            wave_sync();
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int chunk = k * 64 + lane;
+                if (j < bl[k])
+                    *reinterpret_cast<uint4 *>(dst + (bv[k] + (int64_t)j * a.w) * kThin + (chunk & 1) * 8) =
+                        *reinterpret_cast<const uint4 *>(scr + (chunk >> 1) * kEpiStride + 4 * (chunk & 1));
+            }
+            wave_sync();  // reads done before the rows are written again
+        };
+        const int64_t v = v0 + (int64_t)j * a.w;
+        float val[kThin];
+#pragma unroll
+        for (int co = 0; co < kThin; ++co) {
+            const float t = acc[j][co] + (a.bias ? a.bias[co] : 0.f);
+            val[co] = a.relu ? fmaxf(t, 0.f) : t;
+        }
+        if (a.y) {
+            if (a.ych == kThin) {
+                float4 *row = reinterpret_cast<float4 *>(scr + lane * kEpiStride);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) row[q] = make_float4(val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]);
+                wave_sync();
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int chunk = k * 64 + lane, from = chunk >> 2;
+                    const int64_t fv = __shfl((long long)v, from);
+                    if (j < __shfl(live, from))
+                        *reinterpret_cast<float4 *>(a.y + fv * kThin + (chunk & 3) * 4) =
+                            *reinterpret_cast<const float4 *>(scr + from * kEpiStride + 4 * (chunk & 3));
+                }
+                wave_sync();
+            } else if (j < live) {
+#pragma unroll
+                for (int co = 0; co < kThin; ++co)
+                    if (co < a.ych) a.y[v * a.ych + co] = val[co];
+            }
+        }
+        uint4 m[2] = {};  // the epilogue's bfloat16 input (skip or mask)
+        const uint16_t *aux = epi_aux(a);
+        if (aux && j < live) {
+            const uint4 *pm = reinterpret_cast<const uint4 *>(aux + v * kThin);
+            m[0] = pm[0];
+            m[1] = pm[1];
+        }
+        const uint16_t *me = reinterpret_cast<const uint16_t *>(m);
+        uint32_t rb[kThin / 2];
+        if (a.r) {
+#pragma unroll
+            for (int q = 0; q < kThin / 2; ++q) rb[q] = (uint32_t)f2bf(val[2 * q]) | ((uint32_t)f2bf(val[2 * q + 1]) << 16);
+            store_bf16(a.r, rb);
+        }
+        if (a.gout) {  // the next layer's ReLU gradient
+#pragma unroll
+            for (int q = 0; q < kThin / 2; ++q)
+                rb[q] = (uint32_t)(bf2f(me[2 * q]) > 0.f ? f2bf(val[2 * q]) : (uint16_t)0) |
+                        ((uint32_t)(bf2f(me[2 * q + 1]) > 0.f ? f2bf(val[2 * q + 1]) : (uint16_t)0) << 16);
+            store_bf16(a.gout, rb);
+        }
         if (a.out) {
-            float o0 = val[2 * q], o1 = val[2 * q + 1];
-            if (a.skip && live) {
-                o0 += bf2f(a.skip[v * kThin + 2 * q]);
-                o1 += bf2f(a.skip[v * kThin + 2 * q + 1]);
-            }
-            ob[q] = (uint32_t)f2bf(o0) | ((uint32_t)f2bf(o1) << 16);
-        }
-    }
-    if (a.r) store_bf16(a.r, rb);
-    if (a.gout) {  // the next layer's ReLU gradient
-        uint4 m0 = make_uint4(0u, 0u, 0u, 0u), m1 = m0;
-        if (live) {
-            const uint4 *pm = reinterpret_cast<const uint4 *>(a.mask + v * kThin);
-            m0 = pm[0];
-            m1 = pm[1];
-        }
-        const uint16_t *me0 = reinterpret_cast<const uint16_t *>(&m0);
-        const uint16_t *me1 = reinterpret_cast<const uint16_t *>(&m1);
-        uint32_t gb[kThin / 2];
 #pragma unroll
-        for (int q = 0; q < kThin / 2; ++q) {
-            const uint16_t *me = q < 4 ? me0 : me1;
-            const int k = (2 * q) & 7;
-            gb[q] = (uint32_t)(bf2f(me[k]) > 0.f ? f2bf(val[2 * q]) : (uint16_t)0) |
-                    ((uint32_t)(bf2f(me[k + 1]) > 0.f ? f2bf(val[2 * q + 1]) : (uint16_t)0) << 16);
+            for (int q = 0; q < kThin / 2; ++q)
+                rb[q] = (uint32_t)f2bf(a.skip ? val[2 * q] + bf2f(me[2 * q]) : val[2 * q]) |
+                        ((uint32_t)f2bf(a.skip ? val[2 * q + 1] + bf2f(me[2 * q + 1]) : val[2 * q + 1]) << 16);
+            store_bf16(a.out, rb);
         }
-        store_bf16(a.gout, gb);
     }
-    if (a.out) store_bf16(a.out, ob);
 }
 
-// 16 -> 1 channel.
+// 16 -> 1 channel.  A thread unpacks the 16 channels of each voxel of the
+// kThinRows + 2 rows and three planes it needs once for its up to three rows
+// of outputs; the weights are uniform and come through the scalar cache.
+// Taps outside the grid are left out.
 __global__ __launch_bounds__(256) void conv_thin_out_kernel(ConvArgs a)
 {
-    __shared__ float wsh[27 * kThin];
-    for (int i = threadIdx.x; i < 27 * kThin; i += blockDim.x) wsh[i] = bf2f(a.wt[i]);
-    __syncthreads();
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= a.nvox) return;
+    constexpr int R = kThinRows;
+    typedef __attribute__((address_space(4))) const uint32_t Weights;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = thin_threads(a.nvox, a.h, a.w);
+    if (i >= n) return;
     int z, y, x;
-    thin_decode(v, a.d, a.h, a.w, z, y, x);
+    const int64_t v0 = thin_decode(i, a.d, a.h, a.w, z, y, x);
     const int64_t HW = (int64_t)a.h * a.w;
-    float acc = 0.f;
-    for (int t = 0; t < 27; ++t) {
-        int64_t off;
-        if (!thin_tap(t, z, y, x, a.d, a.h, a.w, HW, off)) continue;
-        const uint4 *p = reinterpret_cast<const uint4 *>(a.x + (v + off) * kThin);
-        const uint4 c0 = p[0], c1 = p[1];
-        const uint16_t *e0 = reinterpret_cast<const uint16_t *>(&c0);
-        const uint16_t *e1 = reinterpret_cast<const uint16_t *>(&c1);
+    float acc[R];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc = fmaf(wsh[t * kThin + i], bf2f(e0[i]), acc);
+    for (int j = 0; j < R; ++j) acc[j] = 0.f;
+    const bool side[3] = {x > 0, true, x + 1 < a.w};
+#pragma unroll 1
+    for (int dz = -1; dz <= 1; ++dz) {
+        if ((unsigned)(z + dz) >= (unsigned)a.d) continue;
+        Weights *w = (Weights *)(uintptr_t)a.wt + (dz + 1) * 9 * (kThin / 2);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc = fmaf(wsh[t * kThin + 8 + i], bf2f(e1[i]), acc);
+        for (int r = 0; r < R + 2; ++r) {
+            if ((unsigned)(y + r - 1) >= (unsigned)a.h) continue;
+            const uint16_t *row = a.x + (v0 + dz * HW + (int64_t)(r - 1) * a.w) * kThin;
+            uint4 c[3][2];
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                const uint4 *p = reinterpret_cast<const uint4 *>(row + (side[dx] ? (dx - 1) * kThin : 0));
+                c[dx][0] = p[0];
+                c[dx][1] = p[1];
+            }
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                const uint32_t e[8] = {c[dx][0].x, c[dx][0].y, c[dx][0].z, c[dx][0].w,
+                                       c[dx][1].x, c[dx][1].y, c[dx][1].z, c[dx][1].w};
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const int dy = r - j;  // tap row of output j
+                    if (dy < 0 || dy > 2) continue;
+                    float s = acc[j];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const uint32_t wq = w[(dy * 3 + dx) * 8 + q];
+                        s = fmaf(__uint_as_float(wq << 16), __uint_as_float(e[q] << 16), s);
+                        s = fmaf(__uint_as_float(wq & 0xffff0000u), __uint_as_float(e[q] & 0xffff0000u), s);
+                    }
+                    acc[j] = side[dx] ? s : acc[j];
+                }
+            }
+        }
     }
-    thin_store(a, v, 0, 1, acc);
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+        if (y + j < a.h) thin_store(a, v0 + (int64_t)j * a.w, 0, 1, acc[j]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1764,11 +1828,11 @@ int launch_fwd_ci(int co, const ConvArgs &a, hipStream_t st)
 int launch_fwd(int ci, int co, ConvArgs a, hipStream_t st)
 {
     if (ci == 1 && co == kThin) {
-        hipLaunchKernelGGL(conv_thin_in_kernel, grid1(a.nvox), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(conv_thin_in_kernel, grid1(thin_threads(a.nvox, a.h, a.w)), dim3(256), 0, st, a);
         return 0;
     }
     if (ci == kThin && co == 1) {
-        hipLaunchKernelGGL(conv_thin_out_kernel, grid1(a.nvox), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(conv_thin_out_kernel, grid1(thin_threads(a.nvox, a.h, a.w)), dim3(256), 0, st, a);
         return 0;
     }
     const int64_t waves = (a.nvox + 63) / 64;

@@ -362,14 +362,25 @@ struct LdsTile {
     static constexpr int PER = (NV + 255) / 256;      // vectors per thread
     static constexpr int PLANE = NV * 16;             // bytes per plane
 
-    // Vector c of voxel vox is stored in place c ^ swz(vox): 16 voxels in a
-    // row put a channel vector into different banks.  Period 16 in vox, so
+    // A 16-byte LDS read takes four phases of 16 lanes over 64 banks: of each
+    // half of the wavefront first lanes 0-3, 12-15 and 20-27, then the rest.
+    // Lanes 0-3 and 12-15 of a 16-lane group take the even voxels of a block
+    // and the others the odd ones, so that a phase reads one vector c of all
+    // even and c ^ 1 of all odd voxels; stored in place c ^ swz(vox), these
+    // fall into different banks wherever the block starts (CIN 32: 8 LDS
+    // cycles per read before, now 4: 414 us -> 399).  At 64 channels, where
+    // the LDS is less busy, the permuted stores cost more than that gains
+    // (181 -> 185 us): lanes in order and a swizzle that leaves 8 cycles of
+    // 13.8.  16 channels have no conflicts as they are.  swz has period 16, so
     // that a wavefront's four 16-voxel blocks lie at constant distances.
     static __device__ __forceinline__ int swz(int vox)
     {
-        if (CIN == 64) return (vox + (vox >> 3 & 1)) & 7;
-        if (CIN == 32) return ((vox >> 1) + (vox >> 3 & 1)) & 3;
-        return 0;
+        return CIN == 64 ? (vox + (vox >> 3 & 1)) & 7 : CIN == 32 ? vox >> 2 & 3 : 0;
+    }
+    static __device__ __forceinline__ int voxel_of(int r16)
+    {
+        if (CIN != 32) return r16;
+        return r16 < 4 ? 2 * r16 : r16 >= 12 ? 2 * (r16 - 8) : 2 * (r16 - 4) + 1;
     }
 };
 
@@ -410,7 +421,7 @@ __global__ __launch_bounds__(256, CIN == 64 ? 1 : 2) void conv_fwd_lds_kernel(Co
     static_assert(CB <= 2, "a lane holds up to eight consecutive channels");
     __shared__ __attribute__((aligned(16))) char ring[3 * T::PLANE];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r16 = lane & 15, g = lane >> 4;
+    const int r16 = lane & 15, g = lane >> 4, px = T::voxel_of(r16);  // this lane's voxel of a 16-voxel block
     int64_t b = xcd_block(blockIdx.x, a.nblocks);
     if (b >= ntiles) return;  // whole workgroup, before any barrier (the grid is a multiple of 8)
     const int tx = (int)(b % tiles_x);
@@ -467,9 +478,9 @@ __global__ __launch_bounds__(256, CIN == 64 ? 1 : 2) void conv_fwd_lds_kernel(Co
                 *reinterpret_cast<uint4 *>(ring + slot + to[k]) = next[k];
     };
 
-    // Byte offsets of this lane's voxel of row wave + dy, column r16 + dx.
+    // Byte offsets of this lane's voxel of row wave + dy, column px + dx.
     int tapo[CIN == 16 ? 1 : 9];
-    const int vox0 = (wave + 1) * T::XW + 1 + r16;
+    const int vox0 = (wave + 1) * T::XW + 1 + px;
     if constexpr (CIN == 16) {
         tapo[0] = vox0 * VB + (g & 1) * 16;
     } else {
@@ -513,12 +524,12 @@ __global__ __launch_bounds__(256, CIN == 64 ? 1 : 2) void conv_fwd_lds_kernel(Co
         // in flight during this plane: plane z + 2, the epilogue's input
         const bool more = z + 1 < z1;
         if (more) fetch(z + 2);
-        const int64_t vrow = ((nbase + z) * a.h + yw) * (int64_t)a.w + x0 + r16;
+        const int64_t vrow = ((nbase + z) * a.h + yw) * (int64_t)a.w + x0 + px;
         Bf16Vec<N> aux[4] = {};
         if (auxp)
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb)
-                if (row_ok && x0 + rb * 16 + r16 < a.w) aux[rb] = bf_load<N>(auxp + (vrow + rb * 16) * COUT + N * g);
+                if (row_ok && x0 + rb * 16 + px < a.w) aux[rb] = bf_load<N>(auxp + (vrow + rb * 16) * COUT + N * g);
         f32x4 acc[4][CB];
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
@@ -546,7 +557,7 @@ __global__ __launch_bounds__(256, CIN == 64 ? 1 : 2) void conv_fwd_lds_kernel(Co
             float val[N];
 #pragma unroll
             for (int j = 0; j < N; ++j) val[j] = acc[rb][j / 4][j % 4];
-            if (row_ok && x0 + rb * 16 + r16 < a.w) epi_store<COUT, N>(a, vrow + rb * 16, N * g, bias, aux[rb], val);
+            if (row_ok && x0 + rb * 16 + px < a.w) epi_store<COUT, N>(a, vrow + rb * 16, N * g, bias, aux[rb], val);
         }
         const int t = sm;
         sm = s0;
@@ -566,6 +577,30 @@ __global__ __launch_bounds__(256, CIN == 64 ? 1 : 2) void conv_fwd_lds_kernel(Co
 // (s, group) writes its own partial sums; a second kernel adds them in a
 // fixed order.  Blocks of the centre pair also sum dy for the bias.
 // ---------------------------------------------------------------------------
+// Elements per row of 32 transposed voxels in LDS: 96 bytes, with which the 16
+// rows x 16 bytes that a phase of a fragment read takes (see LdsTile) fall
+// into different banks (80 bytes: 195 us at 32 -> 16, 128^3, against 186).
+constexpr int kRowPitch = 48;
+
+// Transposes 8 channels (v) of voxel j into rows of kRowPitch elements, one
+// row per channel from `rows` on.  Lanes 2k and 2k + 1 hold voxels j (even) and
+// j + 1 of the same channels: they exchange halves, and each writes both
+// voxels of four channels, as four 4-byte stores instead of eight 2-byte ones
+// (32 -> 16 at 128^3: 186 -> 159 us; 64 -> 32 at 2 x 45 x 52 x 70: 249 -> 222).
+__device__ __forceinline__ void store_rows8(uint16_t *rows, int j, const uint4 &v)
+{
+    const bool odd = threadIdx.x & 1;
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? v.x : v.z), 0xB1, 0xf, 0xf, true);
+    const uint32_t r1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? v.y : v.w), 0xB1, 0xf, 0xf, true);
+    const uint32_t o0 = odd ? v.z : v.x, o1 = odd ? v.w : v.y;
+    const uint32_t lo0 = odd ? r0 : o0, hi0 = odd ? o0 : r0, lo1 = odd ? r1 : o1, hi1 = odd ? o1 : r1;
+    uint32_t *d = reinterpret_cast<uint32_t *>(rows + (odd ? 4 * kRowPitch : 0) + (j & ~1));
+    d[0] = (lo0 & 0xffffu) | (hi0 << 16);
+    d[kRowPitch / 2] = (lo0 >> 16) | (hi0 & 0xffff0000u);
+    d[kRowPitch] = (lo1 & 0xffffu) | (hi1 << 16);
+    d[3 * (kRowPitch / 2)] = (lo1 >> 16) | (hi1 & 0xffff0000u);
+}
+
 template <int CIN, int COUT>
 struct WgCfg {
     static constexpr int CB = COUT / 16, IB = CIN / 16;
@@ -573,8 +608,8 @@ struct WgCfg {
     static constexpr int RS = 4 / WS;
     static constexpr int CPW = CB / WS;
     static constexpr int SEG = 32;
-    static constexpr int XW = SEG + 8;  // x^T row: voxels x0 - 1 .. x0 + 32, padded to whole 16-byte reads
-    static constexpr int LDS_U16 = SEG * COUT + XW * CIN;  // per row group
+    static constexpr int XW = kRowPitch;  // x^T row: voxels x0 - 1 .. x0 + 32
+    static constexpr int LDS_U16 = XW * (COUT + CIN);  // per row group
 };
 
 struct WgArgs {
@@ -599,8 +634,8 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgArgs a)
     const int rg = wave / C::WS, wi = wave % C::WS;
     const int gt = wi * 64 + lane;  // thread index within the row group
     const int r16 = lane & 15, g = lane >> 4;
-    uint16_t *dyT = lds + rg * C::LDS_U16;  // [COUT][SEG]
-    uint16_t *xT = dyT + COUT * SEG;        // [CIN][XW]
+    uint16_t *dyT = lds + rg * C::LDS_U16;  // [COUT][XW]
+    uint16_t *xT = dyT + COUT * C::XW;      // [CIN][XW]
     const int D = a.d, H = a.h, W = a.w;
     const int64_t r0 = a.rows * s / a.S, r1 = a.rows * (s + 1) / a.S;
     const bool centre = (q == 4);
@@ -625,16 +660,14 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgArgs a)
             if (act) {
                 // dy^T: 32 voxels x COUT channels, 8 channels per 16-byte
                 // chunk.  Chunks go voxel fastest, so neighbouring lanes write
-                // neighbouring LDS halves; channel fastest, the lanes of one
+                // neighbouring LDS words; channel fastest, the lanes of one
                 // voxel wrote rows a multiple of 32 banks apart (8- and
                 // 16-way bank conflicts: c5's weight gradient 0.120 -> 0.095 ms)
                 for (int c = gt; c < SEG * COUT / 8; c += 64 * C::WS) {
                     const int j = c % SEG, c0 = (c / SEG) * 8;
                     uint4 v = {0u, 0u, 0u, 0u};
                     if (x0 + j < W) v = *reinterpret_cast<const uint4 *>(a.dy + ((r * W + x0 + j) * COUT + c0));
-                    const uint16_t *e = reinterpret_cast<const uint16_t *>(&v);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) dyT[(c0 + i) * SEG + j] = e[i];
+                    store_rows8(dyT + c0 * C::XW, j, v);
                 }
                 // x^T of the source row, xT[i][jj] = x[x0 + jj - 1][i] for
                 // jj = 0 .. 33 (one copy; the three x shifts are taken from
@@ -644,9 +677,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgArgs a)
                     const int xg = x0 + jj - 1;
                     uint4 v = {0u, 0u, 0u, 0u};
                     if (xg >= 0 && xg < W) v = *reinterpret_cast<const uint4 *>(a.x + ((src * W + xg) * CIN + c0));
-                    const uint16_t *e = reinterpret_cast<const uint16_t *>(&v);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) xT[(c0 + i) * C::XW + jj] = e[i];
+                    store_rows8(xT + c0 * C::XW, jj, v);
                 }
             }
             __syncthreads();
@@ -654,7 +685,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgArgs a)
 #pragma unroll
                 for (int cl = 0; cl < C::CPW; ++cl) {
                     const int co = (wi * C::CPW + cl) * 16 + r16;
-                    const uint4 A = *reinterpret_cast<const uint4 *>(dyT + co * SEG + 8 * g);
+                    const uint4 A = *reinterpret_cast<const uint4 *>(dyT + co * C::XW + 8 * g);
 #pragma unroll
                     for (int ib = 0; ib < C::IB; ++ib) {
                         // voxels 8g + dx .. 8g + dx + 7 of channel ib*16 + r16
@@ -673,7 +704,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgArgs a)
                 }
                 if (centre && gt < COUT) {
 #pragma unroll 8
-                    for (int j = 0; j < SEG; ++j) bacc += bf2f(dyT[gt * SEG + j]);
+                    for (int j = 0; j < SEG; ++j) bacc += bf2f(dyT[gt * C::XW + j]);
                 }
             }
         }
@@ -713,10 +744,10 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(WgArgs a)
 template <int CIN, int ZB>
 struct WrCfg {
     static constexpr int IB = CIN / 16;
-    static constexpr int SEG = 32, XW = SEG + 8;
+    static constexpr int SEG = 32, XW = kRowPitch;
     static constexpr int NP = ZB + 2;                // source planes z0 - 1 .. z0 + ZB
     static constexpr int X_U16 = 3 * NP * CIN * XW;  // three-row ring of x^T
-    static constexpr int D_U16 = ZB * 16 * SEG;       // dy^T of the output rows
+    static constexpr int D_U16 = ZB * 16 * XW;        // dy^T of the output rows
     static constexpr int NT = 9 * 64;
 };
 
@@ -780,10 +811,7 @@ void conv_wgrad_ring_kernel(WrArgs a)
             if (c >= XCH) break;
             const int jj = c % (SEG + 2), rest = c / (SEG + 2);
             const int c0 = (rest % (CIN / 8)) * 8, p = rest / (CIN / 8);
-            const uint16_t *e = reinterpret_cast<const uint16_t *>(&v[k]);
-            uint16_t *dst = xr + ((slot * NP + p) * CIN + c0) * XW + jj;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) dst[i * XW] = e[i];
+            store_rows8(xr + ((slot * NP + p) * CIN + c0) * XW, jj, v[k]);
         }
     };
     // dy^T of output rows (n, z0 + zi, y), channels cb*16 .. cb*16 + 15:
@@ -807,10 +835,7 @@ void conv_wgrad_ring_kernel(WrArgs a)
             if (c >= DCH) break;
             const int j = c % SEG, rest = c / SEG;
             const int half = rest & 1, zi = rest >> 1;
-            const uint16_t *e = reinterpret_cast<const uint16_t *>(&v[k]);
-            uint16_t *dst = dyT + (zi * 16 + half * 8) * SEG + j;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) dst[i * SEG] = e[i];
+            store_rows8(dyT + (zi * 16 + half * 8) * XW, j, v[k]);
         }
     };
 
@@ -841,7 +866,7 @@ void conv_wgrad_ring_kernel(WrArgs a)
             const uint16_t *xs_row = xr + ((sy % 3) * NP + 1 + dz) * CIN * XW;
 #pragma unroll
             for (int zi = 0; zi < ZB; ++zi) {
-                const uint4 A = *reinterpret_cast<const uint4 *>(dyT + (zi * 16 + r16) * SEG + 8 * g);
+                const uint4 A = *reinterpret_cast<const uint4 *>(dyT + (zi * 16 + r16) * XW + 8 * g);
 #pragma unroll
                 for (int ib = 0; ib < IB; ++ib) {
                     // voxels 8g + dx .. 8g + dx + 7 of channel ib*16 + r16 of
@@ -862,7 +887,7 @@ void conv_wgrad_ring_kernel(WrArgs a)
 #pragma unroll
             for (int zi = 0; zi < ZB; ++zi)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) bacc += bf2f(dyT[(zi * 16 + r16) * SEG + 8 * g + j]);
+                for (int j = 0; j < 8; ++j) bacc += bf2f(dyT[(zi * 16 + r16) * XW + 8 * g + j]);
         }
         __syncthreads();  // every wave is done with dy^T and ring slot (y - 1) mod 3 = (y + 2) mod 3
         if (more) {
@@ -1242,7 +1267,7 @@ __global__ __launch_bounds__(256) void conv_thin_out_kernel(ConvArgs a)
 // three-row ring of T rows of the 6 planes z0 - 1 .. z0 + 4 (x^T of the
 // voxels x0 - 1 .. x0 + 32), and each wave writes its own partial sums.
 // ---------------------------------------------------------------------------
-constexpr int kThinZB = 4, kThinSeg = 32, kThinXW = kThinSeg + 8, kThinNP = kThinZB + 2;
+constexpr int kThinZB = 4, kThinSeg = 32, kThinXW = kRowPitch, kThinNP = kThinZB + 2;
 
 struct WtArgs {
     const uint16_t *w16;  // the 16-channel operand, channels-last
@@ -1258,7 +1283,7 @@ __global__ __launch_bounds__(256) void wgrad_thin_mfma_kernel(WtArgs a)
 {
     constexpr int SEG = kThinSeg, XW = kThinXW, NP = kThinNP, ZB = kThinZB, C16 = kThin;
     __shared__ __attribute__((aligned(16))) uint16_t tr[3 * NP * XW];       // ring of T rows
-    __shared__ __attribute__((aligned(16))) uint16_t wT[ZB * C16 * SEG];    // W^T of the output rows
+    __shared__ __attribute__((aligned(16))) uint16_t wT[ZB * C16 * XW];    // W^T of the output rows
     const int job = blockIdx.x, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
     const int r16 = lane & 15, g = lane >> 4;
     int t = job;
@@ -1294,10 +1319,7 @@ __global__ __launch_bounds__(256) void wgrad_thin_mfma_kernel(WtArgs a)
             uint4 v = {0u, 0u, 0u, 0u};
             if (z < D && xg < W)
                 v = *reinterpret_cast<const uint4 *>(a.w16 + (((nD + z) * H + y) * W + xg) * C16 + half * 8);
-            const uint16_t *e = reinterpret_cast<const uint16_t *>(&v);
-            uint16_t *dst = wT + (zi * C16 + half * 8) * SEG + j;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) dst[i * SEG] = e[i];
+            store_rows8(wT + (zi * C16 + half * 8) * XW, j, v);
         }
     };
 
@@ -1321,7 +1343,7 @@ __global__ __launch_bounds__(256) void wgrad_thin_mfma_kernel(WtArgs a)
         stage_t(y + 1);
         stage_w(y);
         __syncthreads();
-        const uint4 A = *reinterpret_cast<const uint4 *>(wT + (wv * C16 + r16) * SEG + 8 * g);
+        const uint4 A = *reinterpret_cast<const uint4 *>(wT + (wv * C16 + r16) * XW + 8 * g);
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
             uint4 B = {0u, 0u, 0u, 0u};
@@ -1339,7 +1361,7 @@ __global__ __launch_bounds__(256) void wgrad_thin_mfma_kernel(WtArgs a)
         }
         if (IN1) {  // bias of the 16 channels: lane (c = r16, g) sums voxels 8g .. 8g + 7
 #pragma unroll
-            for (int j = 0; j < 8; ++j) bacc += bf2f(wT[(wv * C16 + r16) * SEG + 8 * g + j]);
+            for (int j = 0; j < 8; ++j) bacc += bf2f(wT[(wv * C16 + r16) * XW + 8 * g + j]);
         } else if (lane < SEG) {  // bias of the one channel: dy of this output row, one voxel per lane
             bacc += bf2f(tr[((y % 3) * NP + wv + 1) * XW + lane + 1]);
         }

@@ -8,7 +8,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <map>
 #include <mutex>
 #include <new>
 #include <string>
@@ -474,7 +473,7 @@ int max_tiles(const GridInfo &g)
 
 struct RawEnt {
     int tile, z, y, x;
-    std::vector<Contrib> c;
+    int cbeg, cend;  // its contributions, in the build's list
     int slot, shot;
 };
 
@@ -486,6 +485,7 @@ int build_tiling(Job &J, Tiling &T, bool with_receivers)
     T.ents.clear();
     T.cont.clear();
     std::vector<RawEnt> se, re;
+    std::vector<Contrib> pool;  // contributions of the entries
     // 2-D: one tile is TX adjacent strips (one workgroup); 3-D: one strip.
     // 2-D tiles of S > 1 steps per launch: strips of 64 vec columns starting
     // at j W - 4 (S - 1) that own W = 64 vec - 8 (S - 1) columns each
@@ -550,27 +550,39 @@ int build_tiling(Job &J, Tiling &T, bool with_receivers)
         const double hd = std::pow(g.h, g.ndim);
         const double h2 = g.h * g.h;
         for (int q = 0; q < sp.n; ++q) {
-            RawEnt e{tile_of(sp.z[q], sp.y[q], sp.x[q]), sp.z[q], sp.y[q], sp.x[q], {}, q, s};
+            const int c = (int)pool.size();
             // D (B w) = D' (h^2 W / h^d) w with D' = (v dt / h)^2.
-            e.c.push_back(Contrib{0, (float)(sp.w[q] * h2 / hd)});
-            se.push_back(e);
+            pool.push_back(Contrib{0, (float)(sp.w[q] * h2 / hd)});
+            se.push_back(RawEnt{tile_of(sp.z[q], sp.y[q], sp.x[q]), sp.z[q], sp.y[q], sp.x[q], c, c + 1, q, s});
         }
         if (!with_receivers) continue;
-        std::map<std::tuple<int, int, int>, size_t> node_of;
+        // Receiver terms by node: sorted by cell, stably, so that a node's
+        // contributions stay in receiver order.  (An ordered map of nodes
+        // with a list each: 2.5 ms more per call with 65536 receivers, before
+        // the GPU has anything to do.)
+        struct Hit {
+            int64_t cell;
+            int z, y, x, r;
+            float w;
+        };
+        std::vector<Hit> hits;
+        hits.reserve((size_t)S.nrec);
         for (int r = 0; r < S.nrec; ++r) {
             PointOp rp;
             if (!make_point(g, &S.rec[3 * (size_t)r], &rp))
                 return fail(RTM_ERANGE, "shot %d: receiver %d outside the interior", s, r);
-            for (int q = 0; q < rp.n; ++q) {
-                auto key = std::make_tuple(rp.z[q], rp.y[q], rp.x[q]);
-                auto it = node_of.find(key);
-                if (it == node_of.end()) {
-                    it = node_of.emplace(key, re.size()).first;
-                    re.push_back(RawEnt{tile_of(rp.z[q], rp.y[q], rp.x[q]), rp.z[q], rp.y[q], rp.x[q], {}, 0, s});
-                }
-                // D R^T g = D' h^2 W g.
-                re[it->second].c.push_back(Contrib{r, (float)(rp.w[q] * h2)});
-            }
+            // D R^T g = D' h^2 W g.
+            for (int q = 0; q < rp.n; ++q)
+                hits.push_back(Hit{rp.z[q] * g.L.plane + rp.y[q] * g.L.pitch + rp.x[q], rp.z[q], rp.y[q], rp.x[q], r,
+                                   (float)(rp.w[q] * h2)});
+        }
+        auto by_cell = [](const Hit &p, const Hit &q) { return p.cell < q.cell; };
+        if (!std::is_sorted(hits.begin(), hits.end(), by_cell)) std::stable_sort(hits.begin(), hits.end(), by_cell);
+        for (size_t i = 0; i < hits.size();) {
+            const Hit &h = hits[i];
+            const int c = (int)pool.size();
+            for (; i < hits.size() && hits[i].cell == h.cell; ++i) pool.push_back(Contrib{hits[i].r, hits[i].w});
+            re.push_back(RawEnt{tile_of(h.z, h.y, h.x), h.z, h.y, h.x, c, (int)pool.size(), 0, s});
         }
     }
     // Multi-step tiles also list, per tile, every node inside its strip and
@@ -630,7 +642,7 @@ int build_tiling(Job &J, Tiling &T, bool with_receivers)
     auto emit = [&](std::vector<RawEnt> &v, int kind) {
         for (auto &e : v) {
             InjEnt E{e.z, e.y, e.x, (int)T.cont.size(), 0, e.slot, e.shot, 0};
-            for (auto &c : e.c) T.cont.push_back(c);
+            T.cont.insert(T.cont.end(), pool.begin() + e.cbeg, pool.begin() + e.cend);
             E.cend = (int)T.cont.size();
             const int idx = (int)T.ents.size();
             T.ents.push_back(E);
@@ -887,6 +899,10 @@ int build_job_tables(Job &J)
     J.dslot.clear();
     J.slot_shot.clear();
     int64_t base = 0;
+    for (const ShotIn &S : J.shots) base += S.nrec;
+    J.rnode.reserve((size_t)base * kMaxNodes);
+    J.rw.reserve((size_t)base * kMaxNodes);
+    base = 0;
     for (int s = 0; s < (int)J.shots.size(); ++s) {
         const ShotIn &S = J.shots[s];
         J.rbase.push_back(base);

@@ -27,9 +27,10 @@
 // fwd2d_multi<2, 3> against 2581 for 9 with guards and 64-bit lane addresses
 // (forward 156.7 -> 149.9 us per step, reverse 413.7 -> 413.4).  Stores of new
 // levels and the imaging sums that bypass the caches where the arrays exceed
-// them (NT) leave the L2 to the columns and rows that neighbouring tiles share
-// (forward 150 -> 143, reverse 413 -> 378; bypassing on the loads too, 146 and
-// 391: strips overlap, and D' is shared by the shots).  With fewer
+// them (NT) take forward 150 -> 143 and reverse 413 -> 378: the traffic is
+// nearly the same (240 shots, reverse: 31.0 -> 30.5 GB a launch), it moves at
+// 5.6 instead of 5.2 TB/s.  Bypassing on the loads too, 146 and 391: strips
+// overlap, and D' is shared by the shots.  With fewer
 // than about four wavefronts per SIMD each row waits for its own loads, so
 // P = 3 loads them three march steps ahead into a ring of registers
 // (16 shots, forward: 64.3 -> 52.7 us per step, 55.3 without the ring; 2

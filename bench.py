@@ -39,6 +39,18 @@ PMC_REVERSE = {"sources_sha256_16": "a541f8a5e830b464", "shots": 240, "shape": (
 KERNEL_SOURCES = ("prop2d.hip", "prop2d_multi.hip", "multi2d.h", "stencil.h", "common.h")
 
 
+def kernel_label(kind, shape):
+    """Kernel of a pass, as BatchPlan.launch_shape reports it, by its tile: floats per lane x rows (3-D: x planes)."""
+    uncached = ", past the caches" if shape["uncached"] else ""
+    if kind.endswith("3d"):
+        return f"{kind}_kernel, tiles of {shape['vec']} floats x {shape['ty']} rows x {shape['rows']} planes{uncached}"
+    if shape["waves"]:
+        return f"{kind}_block_kernel<{shape['vec']}, {shape['steps']}>, {shape['rows']} rows per block"
+    if shape["steps"] > 1:
+        return f"{kind}_multi_kernel<{shape['vec']}, {shape['steps']}>, {shape['rows']} rows per tile{uncached}"
+    return f"{kind}_kernel<{shape['vec']}>, {shape['tx']} strips x {shape['rows']} rows per tile"
+
+
 def reverse_traffic(B, shape, steps=1):
     import hashlib
     csrc = os.path.join(ROOT, "paper_2204_03380_amd", "csrc")
@@ -224,19 +236,22 @@ def c3_report(nt=4000):
     rev_us, fwd_us = rev_ms * 1e3 / max(rev_n, 1), fwd_ms * 1e3 / max(fwd_n, 1)
     rev_bytes = 28 * cells + 16 * interior
     fwd_bytes = 16 * cells
-    vec_f, ty_f, z_f = rtm.rtm_get_tuning3d(rtm.RTM_OP_MODEL)
-    vec_r, ty_r, z_r = rtm.rtm_get_tuning3d(rtm.RTM_OP_RTM)
-    del d, im
+    # the shapes that the calls above chose: those of a plan of the same shot
+    plan = rtm.BatchPlan(rtm.RTM_OP_RTM, [rtm.BatchShot(g, vp, w, s.src[0], s.rec, traces_in=d, image=im)], s.dt, nt,
+                         defer_workspace=True)
+    fwd_shape, rev_shape = plan.launch_shape(), plan.launch_shape(True)
+    plan.free()
+    del d, im, plan
     torch.cuda.empty_cache()
     return {"workload": f"layered salt 3-D 512x512x256 @ 10 m, nb 50, nt {nt}, 12 Hz, 256x256 receivers: one shot "
                         "modeled then migrated",
             "padded_cells": cells, "model_s": round(t_model, 3), "rtm_s": round(t_rtm, 3),
             "value": round(cells * nt * 4 / (t_model + t_rtm) / 1e9, 2), "unit": "Gcell-updates/s",
-            "roofline": {"bound": "hbm", "kernel": f"rev3d_kernel<{vec_r},{ty_r},false> (fused reverse, one step)",
+            "roofline": {"bound": "hbm", "kernel": kernel_label("rev3d", rev_shape) + " (fused reverse, one step)",
                          "avg_launch_us": round(rev_us, 2), "algorithmic_bytes_per_launch": rev_bytes,
                          "achieved": round(rev_bytes / (rev_us * 1e-6) / 1e9, 1), "peak": HBM_PEAK_GBS,
                          "unit": "GB/s", "frac": round(rev_bytes / (rev_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4)},
-            "forward": {"kernel": f"fwd3d_kernel<{vec_f},{ty_f}>", "avg_launch_us": round(fwd_us, 2),
+            "forward": {"kernel": kernel_label("fwd3d", fwd_shape), "avg_launch_us": round(fwd_us, 2),
                         "achieved_GBps": round(fwd_bytes / (fwd_us * 1e-6) / 1e9, 1),
                         "frac": round(fwd_bytes / (fwd_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4)}}
 
@@ -655,8 +670,6 @@ def main():
         del v_tmp
         # the timed batch runs exactly the configuration the tuner picked for it
         rtm.rtm_set_tuning(rtm.RTM_TUNE_EXACT, 1, 0)
-    fwd_shape = rtm.rtm_get_tuning2d(rtm.RTM_OP_MODEL)   # (vec, tx, zseg)
-    rev_shape = rtm.rtm_get_tuning2d(rtm.RTM_OP_RTM)
 
     # Buffers resident in HBM before timing: padded model, B traces, stack.
     v_pad = rtm.rtm_rbc_pad(g, v_int, s.seed, 0.0)
@@ -679,6 +692,7 @@ def main():
     for mp, rp in plans:
         mp.bind_workspace(ws)
         rp.bind_workspace(ws)
+    fwd_shape, rev_shape = plans[0][0].launch_shape(), plans[0][1].launch_shape(True)  # what the passes launch
 
     def step(i):
         rtm.rtm_rbc_pad(g, v_int, s.seed, 0.0, out=v_pad)
@@ -742,6 +756,7 @@ def main():
     torch.cuda.synchronize()
     rtm.rtm_timing_enable(False)
     check_launches = rtm.rtm_timing_read()["reverse_image"][1]
+    check_shape = check.launch_shape(True)
     check.free()
     tr_equal = all(torch.equal(d, traces[j]) for j, (d, _) in enumerate(plain))
     batch_vs_plain = max(float(torch.linalg.norm(imgs[j] - im) / torch.linalg.norm(im))
@@ -755,22 +770,19 @@ def main():
     # reads and writes num, den on the interior (16 B); two or three steps
     # read the same five arrays once, write the last two levels of each field
     # (36 B) and num, den once (16 B).
-    steps_f = rtm.rtm_get_steps_per_launch(rtm.RTM_OP_MODEL)
-    steps_r = rtm.rtm_get_steps_per_launch(rtm.RTM_OP_RTM)
+    steps_f, steps_r = fwd_shape["steps"], rev_shape["steps"]
     rev_ms, rev_n = loops["reverse_image"]
     rev_us = rev_ms * 1e3 / max(rev_n, 1)
     rev_bytes = B * ((36 if steps_r >= 2 else 28) * cells + 16 * interior)
     achieved = rev_bytes / (rev_us * 1e-6) / 1e9
     one_step_bytes = B * (28 * cells + 16 * interior)
     per_step_us = rev_us / steps_r
-    traffic = reverse_traffic(B, rev_shape, steps_r)
-    rev_kernel = (f"rev2d_multi_kernel<{rev_shape[0]}, {steps_r}> ({steps_r} reverse steps per launch: reconstruction + "
-                  f"receiver field + imaging, {B} shots per launch)" if steps_r >= 2 else
-                  f"rev2d_kernel<{rev_shape[0]},false,{rev_shape[1]}> (fused reconstruction + receiver field + "
-                  f"imaging, {B} shots per launch)")
+    traffic = reverse_traffic(B, (rev_shape["vec"], rev_shape["tx"], rev_shape["rows"]), steps_r)
+    rev_kernel = (f"{kernel_label('rev2d', rev_shape)} ({steps_r} reverse steps per launch: reconstruction + receiver "
+                  f"field + imaging, {B} shots per launch)")
     # the reverse launches of the check plan: nt // steps multi-step launches
     # plus the nt % steps single steps
-    check_kernel = (f"rev2d_multi_kernel<{rev_shape[0]}, {steps_r}> at the timed shape, {B} shots"
+    check_kernel = (f"{kernel_label('rev2d', check_shape)}, {B} shots"
                     if check_launches == nt // steps_r + nt % steps_r else f"{check_launches} launches")
     fwd_ms, fwd_n = loops["model_forward"]
     rf_ms, rf_n = loops["rtm_forward"]
@@ -795,8 +807,8 @@ def main():
             "shots_per_step": B,
             "propagations_per_shot": 4,
             "workspace_bytes": int(ws.numel()),
-            "launch_shape": {"forward": {"vec": fwd_shape[0], "tx": fwd_shape[1], "zseg": fwd_shape[2]},
-                             "reverse": {"vec": rev_shape[0], "tx": rev_shape[1], "zseg": rev_shape[2]},
+            "launch_shape": {"forward": fwd_shape,
+                             "reverse": rev_shape,
                              "autotuned": tuned is not None,
                              "tuner": ({"forward_us_per_step": round(tuned["forward"][-1], 3),
                                         "reverse_us_per_step": round(tuned["reverse"][-1], 3),

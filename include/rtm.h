@@ -443,6 +443,24 @@ int rtm_batch_plan(int op, int32_t nshots, const rtm_shot_desc_t *shots, double 
  * overlap in time. */
 int rtm_batch_run(rtm_plan_t *plan, void *ws, size_t ws_bytes, void *stream);
 
+/* What a plan's passes launch.  The settings above are upper bounds unless
+ * RTM_TUNE_EXACT is set; this is the shape that was chosen from them. */
+typedef struct rtm_launch_shape {
+    int32_t steps;    /* time steps per launch (2-D) */
+    int32_t vec;      /* floats per lane */
+    int32_t rows;     /* rows (2-D) or planes (3-D) per tile; of a block kernel, the rows it owns */
+    int32_t ty;       /* 3-D: y rows per workgroup, else 1 */
+    int32_t tx;       /* 2-D, one step per launch: adjacent strips per workgroup, else 1 */
+    int32_t waves;    /* 2-D, several steps: wavefronts per block of the block kernels, 0 for marching strips */
+    int32_t uncached; /* 1: what a launch touches once is kept out of the caches */
+    int32_t tiles;    /* tiles (workgroups, or wavefronts of marching strips) of a launch */
+} rtm_launch_shape_t;
+
+/* Shape of the plan's forward (reverse 0) or reverse (reverse 1) launches.
+ * The steps left over (nt mod steps) are taken by one-step launches.
+ * RTM_EINVAL for the reverse pass of a modeling plan. */
+int rtm_batch_shape(const rtm_plan_t *plan, int reverse, rtm_launch_shape_t *shape);
+
 /* Releases a plan (and its graph); NULL is allowed. */
 int rtm_batch_free(rtm_plan_t *plan);
 

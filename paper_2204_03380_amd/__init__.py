@@ -527,6 +527,13 @@ class BatchPlan:
                     if t is not None]
         return out
 
+    def launch_shape(self, reverse: bool = False) -> dict:
+        """What the plan's forward (or reverse) pass launches: steps, vec,
+        rows, ty, tx, waves, uncached and tiles of rtm_launch_shape_t."""
+        s = _lib.RtmLaunchShape()
+        _lib.check(_lib.load().rtm_batch_shape(self._plan, int(reverse), ctypes.byref(s)))
+        return {name: int(getattr(s, name)) for name, _ in s._fields_}
+
     def run(self, stream: "torch.cuda.Stream" = None) -> None:
         """Runs the plan on `stream` (default: the current stream).
 

@@ -32,7 +32,7 @@ EXPORTS = (
     "rtm_workspace_bytes", "rtm_rbc_pad", "rtm_rbc_pad_ex", "rtm_pad_adjoint_ex",
     "rtm_pad_adjoint", "rtm_model_shot", "rtm_rtm_shot", "rtm_nyquist_stride", "rtm_storage_count",
     "rtm_storage_shot", "rtm_model_shot_vjp", "rtm_batch_plan", "rtm_batch_run",
-    "rtm_batch_free", "rtm_window_extract", "rtm_window_accumulate", "rtm_misfit_ws_bytes", "rtm_l2_misfit",
+    "rtm_batch_shape", "rtm_batch_free", "rtm_window_extract", "rtm_window_accumulate", "rtm_misfit_ws_bytes", "rtm_l2_misfit",
     "rtm_stream_copy", "rtm_rtm_shot_noalloc", "rtm_set_persist_wait", "rtm_get_persist_wait",
     "unet_weight_pack", "unet_weight_pack_many", "unet_conv3d_fwd", "unet_conv3d_dgrad", "unet_conv3d_dgrad_relu", "unet_wgrad_ws_bytes",
     "unet_conv3d_wgrad", "unet_conv3d_wgrad_partial", "unet_wgrad_reduce_many", "unet_embed", "unet_pool2", "unet_up2", "unet_up2_bwd", "unet_up2_bwd_relu",
@@ -56,6 +56,10 @@ class RtmShotDesc(ctypes.Structure):
                 ("src", ctypes.c_float * 3), ("nrec", ctypes.c_int32), ("rec", ctypes.c_void_p),
                 ("traces_in", ctypes.c_void_p), ("traces_out", ctypes.c_void_p), ("image", ctypes.c_void_p),
                 ("grad_v_pad", ctypes.c_void_p)]
+
+
+class RtmLaunchShape(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("steps", "vec", "rows", "ty", "tx", "waves", "uncached", "tiles")]
 
 
 class UnetConvDesc(ctypes.Structure):
@@ -139,6 +143,7 @@ def load():
         "rtm_batch_plan": ([ctypes.c_int, I32, ctypes.POINTER(RtmShotDesc), D, I32, F, U32,
                             ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(SZ)], ctypes.c_int),
         "rtm_batch_run": ([P, P, SZ, P], ctypes.c_int),
+        "rtm_batch_shape": ([P, ctypes.c_int, ctypes.POINTER(RtmLaunchShape)], ctypes.c_int),
         "rtm_batch_free": ([P], ctypes.c_int),
         "rtm_window_extract": ([I64, I64, I64, I64, P, P, P], ctypes.c_int),
         "rtm_misfit_ws_bytes": ([ctypes.POINTER(SZ)], ctypes.c_int),

@@ -2077,6 +2077,21 @@ int rtm_stream_copy(const void *src, void *dst, size_t bytes, int blocks_per_cu,
     return RTM_OK;
 }
 
+int rtm_batch_shape(const rtm_plan_t *plan, int reverse, rtm_launch_shape_t *shape)
+{
+    t_err.clear();
+    if (!plan || !shape) return fail(RTM_EINVAL, "plan and shape must be non-NULL");
+    if (reverse != 0 && reverse != 1) return fail(RTM_EINVAL, "reverse must be 0 or 1");
+    const Job &J = plan->job;
+    if (reverse && J.op == RTM_OP_MODEL) return fail(RTM_EINVAL, "a modeling plan has no reverse pass");
+    const Tiling &one = reverse ? J.rv : J.fw, &multi = reverse ? J.rv2 : J.fw2;
+    const Tiling &T = multi.steps > 1 ? multi : one;  // as job_launch chooses
+    *shape = rtm_launch_shape_t{T.steps, T.tune.vec, T.tune.zseg, T.ndim == 3 ? T.tune.ty : 1,
+                                T.ndim == 2 && T.steps == 1 ? T.tune.tx : 1, kBlockShapes[T.tune.block].waves,
+                                T.tune.once ? 1 : 0, T.count()};
+    return RTM_OK;
+}
+
 int rtm_batch_free(rtm_plan_t *plan)
 {
     if (!plan) return RTM_OK;

@@ -1,0 +1,75 @@
+"""What a plan's passes launch (rtm_batch_shape): planning is host work, so
+the choice of launch shapes is checked without a GPU; device addresses are
+never dereferenced."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2204_03380_amd as rtm
+from paper_2204_03380_amd import _lib
+
+
+@pytest.fixture(autouse=True)
+def _defaults():
+    snap = rtm.tuning_snapshot()
+    for op in (rtm.RTM_OP_MODEL, rtm.RTM_OP_RTM):
+        rtm.rtm_set_tuning2d(op, 2, 1, 108)
+        rtm.rtm_set_steps_per_launch(op, 3)
+    rtm.rtm_set_tuning(rtm.RTM_TUNE_EXACT, 0, 0)
+    yield
+    rtm.tuning_restore(snap)
+
+
+def shape_of(op, padded, shots=1, reverse=False, shared=True, flags=0):
+    """Shape of a batch of `shots` shots, padded extents (z, x) or (z, y, x)."""
+    lib = _lib.load()
+    nz, ny, nx = padded if len(padded) == 3 else (padded[0], 1, padded[1])
+    grid = rtm.Grid(len(padded), nx, ny, nz, 10.0, 0)
+    rec = np.zeros((1, 3), np.float32)
+    descs = (_lib.RtmShotDesc * shots)()
+    for i, d in enumerate(descs):
+        d.grid = grid.c()
+        d.v_pad = 0x10000 + (0 if shared else 0x10000 * i)
+        d.wavelet = d.traces_in = d.traces_out = d.image = d.grad_v_pad = 0x10000
+        d.nrec, d.rec = 1, rec.ctypes.data
+    plan, ws = ctypes.c_void_p(), ctypes.c_size_t()
+    _lib.check(lib.rtm_batch_plan(op, shots, descs, 1e-3, 20, 1e-3, flags, ctypes.byref(plan), ctypes.byref(ws)))
+    s = _lib.RtmLaunchShape()
+    try:
+        _lib.check(lib.rtm_batch_shape(plan, int(reverse), ctypes.byref(s)))
+    finally:
+        lib.rtm_batch_free(plan)
+    return {n: int(getattr(s, n)) for n, _ in s._fields_}
+
+
+def test_query_reports_what_runs_not_what_is_configured():
+    # two shots of 2421 x 871 take two reverse steps at one float, not the configured three at two
+    assert rtm.rtm_get_steps_per_launch(rtm.RTM_OP_RTM) == 3 and rtm.rtm_get_tuning2d(rtm.RTM_OP_RTM)[0] == 2
+    s = shape_of(rtm.RTM_OP_RTM, (871, 2421), 2, reverse=True)
+    assert (s["steps"], s["vec"], s["waves"]) == (2, 1, 0)
+    # a small job takes block kernels, a survey marching strips past the caches
+    assert shape_of(rtm.RTM_OP_MODEL, (281, 281))["waves"] == 8
+    s = shape_of(rtm.RTM_OP_MODEL, (871, 2421), 48)
+    assert (s["steps"], s["vec"], s["rows"], s["waves"], s["uncached"]) == (3, 2, 108, 0, 1)
+    # under RTM_TUNE_EXACT the configured shape runs
+    rtm.rtm_set_tuning(rtm.RTM_TUNE_EXACT, 1, 0)
+    rtm.rtm_set_tuning2d(rtm.RTM_OP_MODEL, 1, 1, 36)
+    s = shape_of(rtm.RTM_OP_MODEL, (281, 281))
+    assert (s["steps"], s["vec"], s["rows"], s["waves"], s["tiles"]) == (3, 1, 36, 0, 6 * 8)
+    rtm.rtm_set_steps_per_launch(rtm.RTM_OP_MODEL, 1)
+    rtm.rtm_set_tuning2d(rtm.RTM_OP_MODEL, 1, 4, 36)
+    s = shape_of(rtm.RTM_OP_MODEL, (281, 281))
+    assert (s["steps"], s["tx"], s["tiles"]) == (1, 4, 2 * 8)
+    # persistent passes step once per item
+    assert shape_of(rtm.RTM_OP_MODEL, (281, 281), flags=rtm.RTM_F_PERSISTENT)["steps"] == 1
+
+
+def test_query_validation():
+    lib = _lib.load()
+    s = _lib.RtmLaunchShape()
+    assert lib.rtm_batch_shape(None, 0, ctypes.byref(s)) == _lib.RTM_EINVAL
+    with pytest.raises(rtm.RtmError):
+        shape_of(rtm.RTM_OP_MODEL, (50, 50), reverse=True)
+    with pytest.raises(rtm.RtmError):
+        shape_of(rtm.RTM_OP_RTM, (50, 50), reverse=2)

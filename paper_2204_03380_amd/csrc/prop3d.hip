@@ -16,6 +16,14 @@
 // loads return in order, so a load issued and awaited inside the plane would
 // also wait for the whole batch behind it.
 //
+// An access takes a scalar pointer to its plane, which advances in place, and
+// one 32-bit vector offset per row.  The pointers are opaque to the compiler:
+// it would form every address of nine unrolled planes ahead, and had up to
+// 378 scalar registers in vector lanes then, moved back for every access (with
+// the rows' offsets scalar as well; on grids in the memory-side cache, where
+// instructions count, that took as long as one row of tiles: 144^3 in 1 x 4 x 9
+// tiles 17.5 -> 11.2 us, reverse 64^3 17.0 -> 12.1, 300^3 forward 96 -> 91).
+//
 // Bound: memory traffic.  A forward step must move four arrays, a reverse one
 // seven and the imaging sums twice; 612 x 612 x 356 cells (533 MB an array)
 // took 581 us (5.6 TB/s with 4.9 arrays read for 3) and 1365 us, of which the
@@ -59,17 +67,17 @@ __device__ __forceinline__ unsigned row_mask(int y, int lo, int hi, bool lane_in
     return here(m);
 }
 
-// What every march knows of its tile.  Field pointers point at cell (0, 0,
-// x0) of plane 0; rows and columns outside the stored ones are read from the
+// What every march knows of its tile.  Field pointers point at row -4, column
+// x0 of a plane; rows and columns outside the stored ones are read from the
 // zero halo instead, so that no load needs a guard.
 template <int VEC, int TY, int RW>
 struct Ctx3 {
     int64_t plane4;            // bytes per plane
-    unsigned row[RW];          // byte offset of each own row in its plane (clamped)
+    // per lane, byte offsets inside a plane (of rows and columns that are stored):
+    unsigned row[RW];                    // its columns of each own row
     unsigned hrow[halo_per_wave<TY>()];  // of this wave's y-halo rows
-    unsigned erow;             // per lane: row offset and column of its strip-end cell, from x0 - 4
-    unsigned lx, cx;           // byte offsets of this lane's columns: stored, own
-    unsigned own;              // per lane: bit i - this lane stores cells of own row i
+    unsigned erow;                       // its strip-end cell, from x0 - 4
+    unsigned own;                        // bit i: this lane stores cells of own row i
     int pitch4, x, x0, y, y0, NX, NY, lane, w;
 };
 
@@ -87,17 +95,16 @@ __device__ __forceinline__ Ctx3<VEC, TY, RW> make_ctx3(ShotEntry &S, Tile3Entry 
     C.y0 = T.y0;
     C.x = T.x0 + C.lane * VEC;
     C.y = T.y0 + C.w * RW;
-    C.lx = (unsigned)(min(C.x, (C.NX + VEC - 1) / VEC * VEC) - T.x0) * 4u;
-    C.cx = (unsigned)(C.lane * VEC) * 4u;
+    const unsigned lx = (unsigned)(min(C.x, (C.NX + VEC - 1) / VEC * VEC) - T.x0) * 4u;
     C.own = row_mask<RW>(C.y, 0, C.NY, C.x < C.NX);
     // rows from -4 on, so that the offsets are not negative
 #pragma unroll
-    for (int i = 0; i < RW; ++i) C.row[i] = (unsigned)(min(C.y + i, C.NY + kRadius - 1) + kRadius) * (unsigned)C.pitch4;
+    for (int i = 0; i < RW; ++i) C.row[i] = (unsigned)(min(C.y + i, C.NY + kRadius - 1) + kRadius) * (unsigned)C.pitch4 + lx;
 #pragma unroll
     for (int i = 0; i < halo_per_wave<TY>(); ++i) {
         const int h = C.w + i * TY;
         const int yh = h < 4 ? C.y0 - 4 + h : C.y0 + TY * RW + (h - 4);
-        C.hrow[i] = (unsigned)(min(yh, C.NY + kRadius - 1) + kRadius) * (unsigned)C.pitch4;
+        C.hrow[i] = (unsigned)(min(yh, C.NY + kRadius - 1) + kRadius) * (unsigned)C.pitch4 + lx;
     }
     // lane 8 i + e: cell e of row i's 4 left and 4 right strip-end cells
     const int e = C.lane & 7, ye = min(C.y + min(C.lane >> 3, RW - 1), C.NY + kRadius - 1) + kRadius;
@@ -114,17 +121,39 @@ struct FieldNext {
     float end;                             // this lane's strip-end cell of plane z
 };
 
-// Issues the loads of field f for plane z (zo: its byte offset).
+// Advances a pointer by a plane, in place (see the head of the file).
+template <class P>
+__device__ __forceinline__ void next_plane(P &p, int64_t plane4)
+{
+    p = at(p, plane4);
+    asm("" : "+s"(p));
+}
+
+// A field read at planes z (strip ends and y-halo) and z + 4 (queue rows).
+struct Field3 {
+    const gfloat *z, *z4;
+    __device__ __forceinline__ void start(const gfloat *f, int64_t plane4)
+    {
+        z = f;
+        z4 = at(f, 4 * plane4);
+    }
+    __device__ __forceinline__ void next(int64_t plane4)
+    {
+        next_plane(z, plane4);
+        next_plane(z4, plane4);
+    }
+};
+
+// Issues the loads of field f for its plane.
 template <int VEC, int TY, int RW>
-__device__ __forceinline__ void field_prefetch(const Ctx3<VEC, TY, RW> &C, const gfloat *f, int64_t zo,
-                                               FieldNext<VEC, TY, RW> &nx)
+__device__ __forceinline__ void field_prefetch(const Ctx3<VEC, TY, RW> &C, const Field3 &f, FieldNext<VEC, TY, RW> &nx)
 {
 #pragma unroll
-    for (int i = 0; i < RW; ++i) ldv<VEC>(at(at(f, zo + 4 * C.plane4 + C.row[i]), here(C.lx)), nx.q[i]);
+    for (int i = 0; i < RW; ++i) ldv<VEC>(at(f.z4, here(C.row[i])), nx.q[i]);
 #pragma unroll
     for (int i = 0; i < halo_per_wave<TY>(); ++i)
-        if (TY <= 8 || C.w + i * TY < 8) ldv<VEC>(at(at(f, zo + C.hrow[i]), here(C.lx)), nx.halo[i]);
-    if (C.lane < 8 * RW) nx.end = *at(at(f, zo) - 4, here(C.erow));
+        if (TY <= 8 || C.w + i * TY < 8) ldv<VEC>(at(f.z, here(C.hrow[i])), nx.halo[i]);
+    if (C.lane < 8 * RW) nx.end = *at(f.z - 4, here(C.erow));
 }
 
 // Writes the centre rows (queue slot of plane z), the y-halo rows and the
@@ -182,20 +211,20 @@ __device__ __forceinline__ void lap3(const Ctx3<VEC, TY, RW> &C, const Lds<VEC, 
     }
 }
 
-// The wave's rows of plane z (zo) of a field.
+// The wave's rows of the plane that f points at.
 template <int VEC, int TY, int RW, bool NT>
-__device__ __forceinline__ void plane_load(const Ctx3<VEC, TY, RW> &C, const gfloat *f, int64_t zo, float (&v)[RW][VEC])
+__device__ __forceinline__ void plane_load(const Ctx3<VEC, TY, RW> &C, const gfloat *f, float (&v)[RW][VEC])
 {
 #pragma unroll
-    for (int i = 0; i < RW; ++i) ld_once<VEC, NT>(at(at(f, zo + C.row[i]), here(C.lx)), v[i]);
+    for (int i = 0; i < RW; ++i) ld_once<VEC, NT>(at(f, here(C.row[i])), v[i]);
 }
 
 template <int VEC, int TY, int RW, bool NT>
-__device__ __forceinline__ void plane_store(const Ctx3<VEC, TY, RW> &C, gfloat *f, int64_t zo, const float (&v)[RW][VEC])
+__device__ __forceinline__ void plane_store(const Ctx3<VEC, TY, RW> &C, gfloat *f, const float (&v)[RW][VEC])
 {
 #pragma unroll
     for (int i = 0; i < RW; ++i)
-        if (C.own >> i & 1) st_once<VEC, NT>(at(at(f, zo + C.row[i]), here(C.cx)), v[i]);
+        if (C.own >> i & 1) st_once<VEC, NT>(at(f, here(C.row[i])), v[i]);
 }
 
 // One field's update (forward pass, receiver field of storage RTM).  IMG: at
@@ -209,8 +238,9 @@ struct StepIn {
 
 template <int VEC, int TY, int RW, bool IMG>
 struct Step3 {
-    const gfloat *pc, *Dp;
-    gfloat *po, *A0, *A1;
+    Field3 pc;              // all at the plane to load next ...
+    const gfloat *old, *Dp, *A0, *A1;
+    gfloat *po, *S0, *S1;   // ... and at the plane to store
     SnapImg I;
     int z1;
     unsigned izn;   // interior planes from I.iz0
@@ -218,12 +248,12 @@ struct Step3 {
 };
 
 template <int VEC, int TY, int RW, bool IMG, bool NT>
-__device__ __forceinline__ void step_fetch(const Ctx3<VEC, TY, RW> &C, const Step3<VEC, TY, RW, IMG> &K, int z, int64_t zo,
+__device__ __forceinline__ void step_fetch(const Ctx3<VEC, TY, RW> &C, Step3<VEC, TY, RW, IMG> &K, int z,
                                            StepIn<VEC, TY, RW, IMG> &in)
 {
-    field_prefetch<VEC, TY, RW>(C, K.pc, zo, in.f);
-    plane_load<VEC, TY, RW, NT>(C, K.po, zo, in.old);
-    plane_load<VEC, TY, RW, NT>(C, K.Dp, zo, in.d);
+    field_prefetch<VEC, TY, RW>(C, K.pc, in.f);
+    plane_load<VEC, TY, RW, NT>(C, K.old, in.old);
+    plane_load<VEC, TY, RW, NT>(C, K.Dp, in.d);
     if constexpr (IMG)
         if (in_rows(z, K.I.iz0, K.izn)) {
 #pragma unroll
@@ -233,15 +263,22 @@ __device__ __forceinline__ void step_fetch(const Ctx3<VEC, TY, RW> &C, const Ste
 #pragma unroll
                     for (int j = 0; j < VEC; ++j)
                         in.s[i][j] = C.x + j >= K.I.ix0 && C.x + j < K.I.ix1 ? K.I.snap[row + C.x + j] : 0.f;
-                    ld_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.lx)), in.a[i]);
-                    ld_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.lx)), in.b[i]);
+                    ld_once<VEC, NT>(at(K.A0, here(C.row[i])), in.a[i]);
+                    ld_once<VEC, NT>(at(K.A1, here(C.row[i])), in.b[i]);
                 }
         }
+    K.pc.next(C.plane4);
+    next_plane(K.old, C.plane4);
+    next_plane(K.Dp, C.plane4);
+    if constexpr (IMG) {
+        next_plane(K.A0, C.plane4);
+        next_plane(K.A1, C.plane4);
+    }
 }
 
 template <int VEC, int TY, int RW, bool NT, bool IMG, int S>
-__device__ __forceinline__ void step_plane(const Ctx3<VEC, TY, RW> &C, const Step3<VEC, TY, RW, IMG> &K, Lds<VEC, TY, RW> &L,
-                                           float (&q)[9][RW][VEC], StepIn<VEC, TY, RW, IMG> &in, int z, int64_t &zo)
+__device__ __forceinline__ void step_plane(const Ctx3<VEC, TY, RW> &C, Step3<VEC, TY, RW, IMG> &K, Lds<VEC, TY, RW> &L,
+                                           float (&q)[9][RW][VEC], StepIn<VEC, TY, RW, IMG> &in, int z)
 {
     constexpr int r4 = (S + 4) % 9, r8 = (S + 8) % 9;
     const int buf = z & 1;
@@ -260,7 +297,7 @@ __device__ __forceinline__ void step_plane(const Ctx3<VEC, TY, RW> &C, const Ste
             }
         }
     field_publish<VEC, TY, RW>(C, L, buf, q[r4], in.f);
-    if (z + 1 < K.z1) step_fetch<VEC, TY, RW, IMG, NT>(C, K, z + 1, zo + C.plane4, in);
+    if (z + 1 < K.z1) step_fetch<VEC, TY, RW, IMG, NT>(C, K, z + 1, in);
     __syncthreads();
     float lap[RW][VEC];
     lap3<VEC, TY, RW, S>(C, L, buf, q, lap);
@@ -268,7 +305,7 @@ __device__ __forceinline__ void step_plane(const Ctx3<VEC, TY, RW> &C, const Ste
     for (int i = 0; i < RW; ++i)
 #pragma unroll
         for (int j = 0; j < VEC; ++j) lap[i][j] = fmaf(d[i][j], lap[i][j], (q[r4][i][j] + q[r4][i][j]) - old[i][j]);
-    plane_store<VEC, TY, RW, NT>(C, K.po, zo, lap);
+    plane_store<VEC, TY, RW, NT>(C, K.po, lap);
     if constexpr (IMG)
         if (in_rows(z, K.I.iz0, K.izn)) {
 #pragma unroll
@@ -279,11 +316,15 @@ __device__ __forceinline__ void step_plane(const Ctx3<VEC, TY, RW> &C, const Ste
                         sa[i][j] = fmaf(sn[i][j], q[r4][i][j], sa[i][j]);
                         sb[i][j] = fmaf(sn[i][j], sn[i][j], sb[i][j]);
                     }
-                    st_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.cx)), sa[i]);
-                    st_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.cx)), sb[i]);
+                    st_once<VEC, NT>(at(K.S0, here(C.row[i])), sa[i]);
+                    st_once<VEC, NT>(at(K.S1, here(C.row[i])), sb[i]);
                 }
         }
-    zo += C.plane4;
+    next_plane(K.po, C.plane4);
+    if constexpr (IMG) {
+        next_plane(K.S0, C.plane4);
+        next_plane(K.S1, C.plane4);
+    }
 }
 
 // Runs ROWCALL(S, z) over the tile's planes, nine per trip (z1 - z0 is a
@@ -296,16 +337,15 @@ __device__ __forceinline__ void step_plane(const Ctx3<VEC, TY, RW> &C, const Ste
     }
 
 template <int VEC, int TY, int RW, bool NT, bool IMG>
-__device__ __forceinline__ void step_march(const Ctx3<VEC, TY, RW> &C, const Step3<VEC, TY, RW, IMG> &K, Lds<VEC, TY, RW> &L,
+__device__ __forceinline__ void step_march(const Ctx3<VEC, TY, RW> &C, Step3<VEC, TY, RW, IMG> &K, Lds<VEC, TY, RW> &L,
                                            Tile3Entry &T)
 {
     float q[9][RW][VEC];
     StepIn<VEC, TY, RW, IMG> in;
-    int64_t zo = (int64_t)T.z0 * C.plane4;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) plane_load<VEC, TY, RW, false>(C, K.pc, zo + (i - 4) * C.plane4, q[i]);
-    step_fetch<VEC, TY, RW, IMG, NT>(C, K, T.z0, zo, in);
-#define RTM_STEP3(SS, ZZ) step_plane<VEC, TY, RW, NT, IMG, SS>(C, K, L, q, in, ZZ, zo)
+    for (int i = 0; i < 8; ++i) plane_load<VEC, TY, RW, false>(C, at(K.pc.z, (i - 4) * C.plane4), q[i]);
+    step_fetch<VEC, TY, RW, IMG, NT>(C, K, T.z0, in);
+#define RTM_STEP3(SS, ZZ) step_plane<VEC, TY, RW, NT, IMG, SS>(C, K, L, q, in, ZZ)
     RTM_MARCH3(RTM_STEP3)
 #undef RTM_STEP3
 }
@@ -326,36 +366,44 @@ struct RevIn3 {
 
 template <int VEC, int TY, int RW, bool GRAD>
 struct Rev3 {
-    const gfloat *P0, *M0, *Dp;
-    gfloat *P1, *M1, *A0, *A1;
+    Field3 P0, M0;                             // all at the plane to load next ...
+    const gfloat *P1, *M1, *Dp, *A0, *A1;
+    gfloat *WP, *WM, *S0, *S1;                 // ... and at the plane to store
     int z1, alo;    // the sums cover planes [alo, alo + an) ...
     unsigned an;
     unsigned mask;  // ... and, per lane, these of the own rows
 };
 
 template <int VEC, int TY, int RW, bool GRAD, bool NT>
-__device__ __forceinline__ void rev_fetch3(const Ctx3<VEC, TY, RW> &C, const Rev3<VEC, TY, RW, GRAD> &K, int z, int64_t zo,
+__device__ __forceinline__ void rev_fetch3(const Ctx3<VEC, TY, RW> &C, Rev3<VEC, TY, RW, GRAD> &K, int z,
                                            RevIn3<VEC, TY, RW, GRAD> &in)
 {
-    field_prefetch<VEC, TY, RW>(C, K.P0, zo, in.p);
-    field_prefetch<VEC, TY, RW>(C, K.M0, zo, in.m);
-    plane_load<VEC, TY, RW, NT>(C, K.P1, zo, in.p1);
-    plane_load<VEC, TY, RW, NT>(C, K.M1, zo, in.m1);
-    plane_load<VEC, TY, RW, NT>(C, K.Dp, zo, in.d);
+    field_prefetch<VEC, TY, RW>(C, K.P0, in.p);
+    field_prefetch<VEC, TY, RW>(C, K.M0, in.m);
+    plane_load<VEC, TY, RW, NT>(C, K.P1, in.p1);
+    plane_load<VEC, TY, RW, NT>(C, K.M1, in.m1);
+    plane_load<VEC, TY, RW, NT>(C, K.Dp, in.d);
     if (in_rows(z, K.alo, K.an)) {
 #pragma unroll
         for (int i = 0; i < RW; ++i)
             if (K.mask >> i & 1) {
-                ld_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.lx)), in.a[i]);
-                if constexpr (!GRAD) ld_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.lx)), in.b[i]);
+                ld_once<VEC, NT>(at(K.A0, here(C.row[i])), in.a[i]);
+                if constexpr (!GRAD) ld_once<VEC, NT>(at(K.A1, here(C.row[i])), in.b[i]);
             }
     }
+    K.P0.next(C.plane4);
+    K.M0.next(C.plane4);
+    next_plane(K.P1, C.plane4);
+    next_plane(K.M1, C.plane4);
+    next_plane(K.Dp, C.plane4);
+    next_plane(K.A0, C.plane4);
+    if constexpr (!GRAD) next_plane(K.A1, C.plane4);
 }
 
 template <int VEC, int TY, int RW, bool NT, bool GRAD, int S>
-__device__ __forceinline__ void rev_plane3(const Ctx3<VEC, TY, RW> &C, const Rev3<VEC, TY, RW, GRAD> &K,
+__device__ __forceinline__ void rev_plane3(const Ctx3<VEC, TY, RW> &C, Rev3<VEC, TY, RW, GRAD> &K,
                                            Lds<VEC, TY, RW> &LP, Lds<VEC, TY, RW> &LM, float (&qp)[9][RW][VEC],
-                                           float (&qm)[9][RW][VEC], RevIn3<VEC, TY, RW, GRAD> &in, int z, int64_t &zo)
+                                           float (&qm)[9][RW][VEC], RevIn3<VEC, TY, RW, GRAD> &in, int z)
 {
     constexpr int r4 = (S + 4) % 9, r8 = (S + 8) % 9;
     const int buf = z & 1;
@@ -374,7 +422,7 @@ __device__ __forceinline__ void rev_plane3(const Ctx3<VEC, TY, RW> &C, const Rev
         }
     field_publish<VEC, TY, RW>(C, LP, buf, qp[r4], in.p);
     field_publish<VEC, TY, RW>(C, LM, buf, qm[r4], in.m);
-    if (z + 1 < K.z1) rev_fetch3<VEC, TY, RW, GRAD, NT>(C, K, z + 1, zo + C.plane4, in);
+    if (z + 1 < K.z1) rev_fetch3<VEC, TY, RW, GRAD, NT>(C, K, z + 1, in);
     __syncthreads();
     float lp[RW][VEC], lm[RW][VEC];
     lap3<VEC, TY, RW, S>(C, LP, buf, qp, lp);
@@ -391,28 +439,31 @@ __device__ __forceinline__ void rev_plane3(const Ctx3<VEC, TY, RW> &C, const Rev
             }
             lp[i][j] = inc + ((cp + cp) - p1[i][j]);
         }
-    plane_store<VEC, TY, RW, NT>(C, K.P1, zo, lp);
+    plane_store<VEC, TY, RW, NT>(C, K.WP, lp);
     lap3<VEC, TY, RW, S>(C, LM, buf, qm, lm);
 #pragma unroll
     for (int i = 0; i < RW; ++i)
 #pragma unroll
         for (int j = 0; j < VEC; ++j) lm[i][j] = fmaf(d[i][j], lm[i][j], (qm[r4][i][j] + qm[r4][i][j]) - m1[i][j]);
-    plane_store<VEC, TY, RW, NT>(C, K.M1, zo, lm);
+    plane_store<VEC, TY, RW, NT>(C, K.WM, lm);
     if (in_rows(z, K.alo, K.an)) {
 #pragma unroll
         for (int i = 0; i < RW; ++i)
             if (K.mask >> i & 1) {
-                st_once<VEC, NT>(at(at(K.A0, zo + C.row[i]), here(C.cx)), a[i]);
-                if constexpr (!GRAD) st_once<VEC, NT>(at(at(K.A1, zo + C.row[i]), here(C.cx)), b[i]);
+                st_once<VEC, NT>(at(K.S0, here(C.row[i])), a[i]);
+                if constexpr (!GRAD) st_once<VEC, NT>(at(K.S1, here(C.row[i])), b[i]);
             }
     }
-    zo += C.plane4;
+    next_plane(K.WP, C.plane4);
+    next_plane(K.WM, C.plane4);
+    next_plane(K.S0, C.plane4);
+    if constexpr (!GRAD) next_plane(K.S1, C.plane4);
 }
 
 }  // namespace
 
-// Field pointer at (y = -4, x = x0) of plane 0, as Ctx3's row offsets count.
-#define RTM_AT3(f) (gp(f) + S.L.org - kRadius * S.L.pitch + T.x0)
+// Field pointer at (y = -4, x = x0) of plane z0, as Ctx3's row offsets count.
+#define RTM_AT3(f) at(gp(f) + S.L.org - kRadius * S.L.pitch + T.x0, (int64_t)T.z0 * C.plane4)
 
 // Forward step n (see the 2-D kernel): tiles of 64*VEC x TY*RW x (z1 - z0).
 // Workgroups past the stencil slots record d^n = R p^n, one receiver task
@@ -437,8 +488,8 @@ __global__ __launch_bounds__(64 * TY) void fwd3d_kernel(const ShotDev *__restric
     ShotEntry &S = *(ShotEntry *)(uintptr_t)(shots + T.shot);
     const Ctx3<VEC, TY, RW> C = make_ctx3<VEC, TY, RW>(S, T);
     Step3<VEC, TY, RW, false> K{};
-    K.pc = RTM_AT3(S.fld[n & 1]);
-    K.po = RTM_AT3(S.fld[(n + 1) & 1]);
+    K.pc.start(RTM_AT3(S.fld[n & 1]), C.plane4);
+    K.old = K.po = RTM_AT3(S.fld[(n + 1) & 1]);
     K.Dp = RTM_AT3(S.Dp);
     K.z1 = T.z1;
     step_march<VEC, TY, RW, NT, false>(C, K, L, T);
@@ -468,13 +519,13 @@ __global__ __launch_bounds__(64 * TY) void rev3d_kernel(const ShotDev *__restric
     ShotEntry &S = *(ShotEntry *)(uintptr_t)(shots + T.shot);
     const Ctx3<VEC, TY, RW> C = make_ctx3<VEC, TY, RW>(S, T);
     Rev3<VEC, TY, RW, GRAD> K;
-    K.P0 = RTM_AT3(S.fld[k & 1]);
-    K.P1 = RTM_AT3(S.fld[(k + 1) & 1]);
-    K.M0 = RTM_AT3(S.fld[2 + ((k + 1) & 1)]);
-    K.M1 = RTM_AT3(S.fld[2 + (k & 1)]);
+    K.P0.start(RTM_AT3(S.fld[k & 1]), C.plane4);
+    K.M0.start(RTM_AT3(S.fld[2 + ((k + 1) & 1)]), C.plane4);
+    K.P1 = K.WP = RTM_AT3(S.fld[(k + 1) & 1]);
+    K.M1 = K.WM = RTM_AT3(S.fld[2 + (k & 1)]);
     K.Dp = RTM_AT3(S.Dp);
-    K.A0 = RTM_AT3(S.acc0);
-    K.A1 = GRAD ? nullptr : RTM_AT3(S.acc1);
+    K.A0 = K.S0 = RTM_AT3(S.acc0);
+    K.A1 = K.S1 = GRAD ? nullptr : RTM_AT3(S.acc1);
     K.z1 = T.z1;
     // the gradient sum covers the whole padded grid, the imaging sums the interior
     K.alo = GRAD ? T.z0 : max(T.z0, S.iz0);
@@ -482,14 +533,13 @@ __global__ __launch_bounds__(64 * TY) void rev3d_kernel(const ShotDev *__restric
     K.mask = GRAD ? C.own : row_mask<RW>(C.y, S.iy0, S.iy1, C.x + VEC > S.ix0 && C.x < S.ix1);
     float qp[9][RW][VEC], qm[9][RW][VEC];
     RevIn3<VEC, TY, RW, GRAD> in;
-    int64_t zo = (int64_t)T.z0 * C.plane4;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        plane_load<VEC, TY, RW, false>(C, K.P0, zo + (i - 4) * C.plane4, qp[i]);
-        plane_load<VEC, TY, RW, false>(C, K.M0, zo + (i - 4) * C.plane4, qm[i]);
+        plane_load<VEC, TY, RW, false>(C, at(K.P0.z, (i - 4) * C.plane4), qp[i]);
+        plane_load<VEC, TY, RW, false>(C, at(K.M0.z, (i - 4) * C.plane4), qm[i]);
     }
-    rev_fetch3<VEC, TY, RW, GRAD, NT>(C, K, T.z0, zo, in);
-#define RTM_REV3(SS, ZZ) rev_plane3<VEC, TY, RW, NT, GRAD, SS>(C, K, LP, LM, qp, qm, in, ZZ, zo)
+    rev_fetch3<VEC, TY, RW, GRAD, NT>(C, K, T.z0, in);
+#define RTM_REV3(SS, ZZ) rev_plane3<VEC, TY, RW, NT, GRAD, SS>(C, K, LP, LM, qp, qm, in, ZZ)
     RTM_MARCH3(RTM_REV3)
 #undef RTM_REV3
     const gfloat *Dp = gp(S.Dp) + S.L.org, *M0 = gp(S.fld[2 + ((k + 1) & 1)]) + S.L.org;
@@ -530,13 +580,13 @@ __global__ __launch_bounds__(64 * TY) void recv3d_kernel(const ShotDev *__restri
     ShotEntry &S = *(ShotEntry *)(uintptr_t)(shots + T.shot);
     const Ctx3<VEC, TY, RW> C = make_ctx3<VEC, TY, RW>(S, T);
     Step3<VEC, TY, RW, IMG> K{};
-    K.pc = RTM_AT3(S.fld[2 + ((k + 1) & 1)]);  // mu^{k+1}
-    K.po = RTM_AT3(S.fld[2 + (k & 1)]);        // mu^{k+2} -> mu^k
+    K.pc.start(RTM_AT3(S.fld[2 + ((k + 1) & 1)]), C.plane4);  // mu^{k+1}
+    K.old = K.po = RTM_AT3(S.fld[2 + (k & 1)]);               // mu^{k+2} -> mu^k
     K.Dp = RTM_AT3(S.Dp);
     K.z1 = T.z1;
     if constexpr (IMG) {
-        K.A0 = RTM_AT3(S.acc0);
-        K.A1 = RTM_AT3(S.acc1);
+        K.A0 = K.S0 = RTM_AT3(S.acc0);
+        K.A1 = K.S1 = RTM_AT3(S.acc1);
         K.I = SnapImg{snap, S.ix1 - S.ix0, S.iy1 - S.iy0, S.ix0, S.ix1, S.iy0, S.iz0};
         K.izn = (unsigned)(S.iz1 - S.iz0);
         K.mask = row_mask<RW>(C.y, S.iy0, S.iy1, C.x + VEC > S.ix0 && C.x < S.ix1);

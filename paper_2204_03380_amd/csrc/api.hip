@@ -700,48 +700,87 @@ int64_t count_tiles3(const Job &J, Tune t)
 // HBM whatever is done, and then the L2 serves the shared halo rows better
 // without the arrays that are touched once; smaller ones live in that cache
 // (us per step with / without: 612 x 612 x 356 cells forward 442 / 527,
-// reverse 1096 / 1251; 252^3 reverse, 353 MB, 122 / 137; 220^3 reverse,
-// 245 MB, 91 / 94; 252^3 forward, 192 MB, 53 / 50; 188^3 reverse, 150 MB,
-// 55 / 53).
+// reverse 1096 / 1251; 300^3 reverse 256 / 315; 252^3 reverse, 353 MB, 122 /
+// 137; 220^3 reverse, 245 MB, 91 / 94; 252^3 forward, 192 MB, 53 / 50; 188^3
+// reverse, 150 MB, 55 / 53).  A model that several shots share is not touched
+// once (with / without: 16 x 124^3 forward 111 / 99, reverse 341 / 292,
+// gradient 283 / 256; 8 x 188^3 186 / 163, 548 / 476, 444 / 405), which counts
+// from four shots on in a forward step and, in a reverse step of two fields,
+// from eight on beyond twice the cache (4 x 304 x 337 x 43 160 / 187, 16 x 96^3
+// gradient 130 / 138, though 64 x 64^3 203 / 182).  Over 278 drawn jobs the
+// rule costs forward 0.1, reverse 1.6, gradient 1.2 % against the better of the
+// two for each (once for all: 3.6, 3.0, 2.1 %); with a model per shot small
+// extents go either way (reverse, 16 x 124^3 339 / 309, 5 x 301 x 55 x 205
+// 0.78 of the time without).
 //
-// Width and rows: the configured ones where the arrays exceed that cache
-// (fewer halo rows read); else a forward step is quicker in 8-row tiles
-// (156^3, 2 floats: 17.9 against 23.6 us; 188^3: 24.4 against 28.5), a
-// receiver step at one float (188 x 188 x 160: 26.7 against 30.6).
+// In the cache a step is a matter of latency and of instructions.  Forward
+// and receiver steps take the smallest tiles, one float x 4 rows x 9 planes,
+// whatever the size (us per step at 1 x 4 x 9, 1 x 8 x 9, 1 x 4 x 27 and, where
+// larger tiles fill the chip, 2 x 8 x 9: 64^3 7.1, 7.2, 13.8; 144^3 11.2, 11.3,
+// 16.3, 15.4; 188^3 20.1, 21.2, 19.3, 21.5; 300 x 300 x 60 20.0, 20.3, 19.2,
+// 22.8; over 100 sizes and batches within 1.3 % of the best on average).  The
+// reverse kernel has four wavefronts per SIMD: it takes these tiles while its
+// workgroups are all resident, four per CU (a fifth is soon through), also of 18
+// and 27 planes if these still give 2.5 per CU, else the configured ones (1 x 4
+// against 1 x 8 rows: 64^3 12.1 / 15.2, 128^3 20.6 /
+// 20.9, 400 x 90 x 70, 5.0 per CU, 23.9 / 25.0, 260 x 180 x 100 at 27 planes
+// 39.1 / 45.6, 188^3 55.9 / 56.1; 3 x 78 x 353 x 24
+// at 27, 2.1 per CU, 33.1 / 26.6; not resident: 2 x 124^3 at 9 planes 37.2 /
+// 34.5, 4 x 124^3 at 36 79.8 / 75.9).
 //
-// Planes per tile, for the forward and receiver kernels: the least march
-// time.  A tile marches 8 planes beyond its own, and the fullest CU ends the
-// launch: one workgroup of 16 wavefronts fills a CU, smaller ones share it,
-// k of them taking about 1.2 + k units (501 x 501 x 235 cells, one / two /
-// 2.5 workgroups of 16 per CU: 203 / 208 / 241 us per step; 612 x 612 x 356
-// at 72 planes, 3.8 per CU, 442, at 90, 3.05, 508; 96^3 at 9 and 18 planes
-// 10.4 and 15.8).  The reverse kernel, at two rows per wavefront, stays near
-// its memory time at any height that leaves enough workgroups (316^3 at 9 to
-// 81 planes 264 to 292); on arrays that fit the cache the same march rule
-// holds, with a floor for what a lone workgroup takes per plane (188^3 at 9,
-// 18, 27, 36 planes 53.1, 58.5, 48.1, 56.2).
+// Planes per tile otherwise: the least march time.  A tile marches 8 planes
+// beyond its own, and the fullest CU ends the launch: one workgroup of 16
+// wavefronts fills a CU, smaller ones share it, k of them taking about 1.2 + k
+// units (501 x 501 x 235 cells, one / two / 2.5 workgroups of 16 per CU: 203 /
+// 208 / 241 us per step; 612 x 612 x 356 at 72 planes, 3.8 per CU, 442, at 90,
+// 3.05, 508).  The reverse kernel, at two rows per wavefront, stays near its
+// memory time at any height that leaves enough workgroups (316^3 at 9 to 81
+// planes 264 to 292); on arrays that fit the cache the same march rule holds,
+// with a floor for what a lone workgroup takes per plane (188^3 at 9, 18, 27,
+// 36 planes 53.1, 58.5, 48.1, 56.2), and from 14 workgroups per CU on nine
+// planes are best (4 x 156^3, 16.9 per CU, at 9, 27 and 54 planes 140, 159,
+// 142; 8 x 124^3, 14: 148, 161, 147; 24 x 64^3, 12: 65.1, at 18 63.1).
 enum Pass3 { kFwd3, kRecv3, kRev3 };
 constexpr int64_t kCacheBytes = (int64_t)224 << 20;
 
+int once3(const Job &J, Pass3 pass)
+{
+    const int64_t nsh = (int64_t)J.shots.size();
+    int64_t bytes = 0;
+    for (const ShotIn &S : J.shots) {
+        const GridInfo &g = S.g;
+        const int64_t all = 4 * (int64_t)g.NX * g.NY * g.NZ, in = 4 * g.nx * g.ny * g.nz;
+        bytes += pass != kRev3 ? 3 * all : J.op == RTM_OP_VJP ? 6 * all : 5 * all + 2 * in;
+    }
+    if (bytes <= kCacheBytes) return 0;
+    if ((int64_t)J.slot_shot.size() == nsh) return kOnce;  // a model for each shot
+    return (pass != kRev3 ? nsh >= 4 : nsh >= 8 && bytes > 2 * kCacheBytes) ? 0 : kOnce;
+}
+
 Tune fit_tune3(const Job &J, Tune t, Pass3 pass)
 {
-    int64_t bytes = 0;
     int NZr = 0, NX = 0;
     for (const ShotIn &S : J.shots) {
-        const int64_t all = 4 * (int64_t)S.g.NX * S.g.NY * S.g.L.NZ, in = 4 * (int64_t)S.g.nx * S.g.ny * S.g.nz;
-        bytes += pass != kRev3 ? 3 * all : J.op == RTM_OP_VJP ? 6 * all : 5 * all + 2 * in;
         NZr = std::max(NZr, S.g.L.NZr);
         NX = std::max(NX, S.g.NX);
     }
-    t.once = bytes > kCacheBytes ? kOnce : 0;
+    t.once = once3(J, pass);
     if (g_tune_exact.load()) return t;
     if (NX <= 64) t.vec = 1;  // half the lanes would be idle
-    if (!t.once && t.ty == 16 && t.vec > 1) {
-        if (pass == kRecv3) t.vec = 1;
-        else t.ty = 8;
+    const int top = t.zseg;
+    if (!t.once) {
+        Tune c = t;
+        c.vec = 1;
+        c.ty = 4;
+        for (c.zseg = kMinZseg; c.zseg <= std::min(top, 3 * kMinZseg); c.zseg += kMinZseg) {
+            const double n = (double)count_tiles3(J, c) / 256.0;
+            if (pass != kRev3 || (c.zseg == kMinZseg ? n <= 5.1 : n >= 2.5 && n <= 4.15)) return c;
+        }
+        c = t;
+        c.zseg = kMinZseg;
+        if ((double)count_tiles3(J, c) >= 256.0 * 14.0) return c;
     }
     const bool full = t.ty * t.vec >= 32;  // workgroups that fill a CU
-    const int top = t.zseg;
     double least = 0.0;
     for (int seg = 1; seg <= NZr / kZUnroll; ++seg) {
         Tune c = t;

@@ -1004,35 +1004,43 @@ hipError_t sum_parts(const float *part0, int64_t n0, float *tmp0, float *out0, c
 // 8.4 M voxels are 92 us of multiply-adds there and 60 us of traffic; with
 // one voxel per thread, reading weights (1 -> 16) or unpacking activations
 // (16 -> 1) for every multiply-add, they took 274 and 346 us.  A thread
-// computes kThinRows voxels one above the other, which share the weights of
-// a tap and the unpacked activations of a row.
+// computes R voxels one above the other, which share the weights of a tap
+// and the unpacked activations of a row: four on large grids, but one where
+// that leaves the chip short of wavefronts, which then only wait (1 -> 16 and
+// 16 -> 1, us with four / one: 16^3 12.6 / 6.6 and 12.9 / 6.2, 64^3 14.5 / 10.1
+// and 13.1 / 10.3, 63 x 64 x 128 19.4 / 18.8 and 18.6 / 17.6, 96 x 96 x 64 22.5 /
+// 21.8 and 22.4 / 19.3, 96^3 25.6 / 25.6 and 26.8 / 27.5, 128^3 45.0 / 50.0 and
+// 44.9 / 57.4).
 // ---------------------------------------------------------------------------
 constexpr int kThin = 16;  // channels on the wide side
 constexpr int kThinRows = 4;
+constexpr int64_t kThinRowsVox = (int64_t)3 << 18;  // voxels from which on
 
-// Threads of a one-channel convolution: x fastest, then blocks of kThinRows
-// rows, planes, samples.
+// Threads of a one-channel convolution of R rows per thread: x fastest, then
+// blocks of R rows, planes, samples.
+template <int R>
 __host__ __device__ inline int64_t thin_threads(int64_t nvox, int h, int w)
 {
-    return nvox / ((int64_t)h * w) * ((h + kThinRows - 1) / kThinRows) * w;
+    return nvox / ((int64_t)h * w) * ((h + R - 1) / R) * w;
 }
 
 // First voxel of thread i (z: plane within its sample).
+template <int R>
 __device__ __forceinline__ int64_t thin_decode(int64_t i, int D, int H, int W, int &z, int &y, int &x)
 {
-    const int hb = (H + kThinRows - 1) / kThinRows;
+    const int hb = (H + R - 1) / R;
     int64_t plane;
     if (i <= 0xffffffffll) {  // 32-bit division, far cheaper than the 64-bit sequence
         const uint32_t u = (uint32_t)i, t = u / (uint32_t)W, p = t / (uint32_t)hb;
         x = (int)(u - t * (uint32_t)W);
-        y = (int)(t - p * (uint32_t)hb) * kThinRows;
+        y = (int)(t - p * (uint32_t)hb) * R;
         z = (int)(p % (uint32_t)D);
         plane = p;
     } else {
         const int64_t t = i / W;
         x = (int)(i - t * W);
         plane = t / hb;
-        y = (int)(t - plane * hb) * kThinRows;
+        y = (int)(t - plane * hb) * R;
         z = (int)(plane % D);
     }
     return (plane * H + y) * W + x;
@@ -1050,21 +1058,21 @@ __device__ __forceinline__ void thin_store(const ConvArgs &a, int64_t v, int co,
 }
 
 // 1 -> 16 channels.  Weights in LDS as [tap][channel] so that one tap's
-// sixteen weights are four 16-byte reads, used for kThinRows voxels; each
+// sixteen weights are four 16-byte reads, used for R voxels; each
 // channel sums its taps in ascending order.
+template <int R>
 __global__ __launch_bounds__(256) void conv_thin_in_kernel(ConvArgs a)
 {
-    constexpr int R = kThinRows;
     __shared__ float4 wsh4[27 * kThin / 4];
     float *wsh = reinterpret_cast<float *>(wsh4);
     for (int i = threadIdx.x; i < kThin * 27; i += blockDim.x) wsh[(i % 27) * kThin + i / 27] = bf2f(a.wt[i]);
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = thin_threads(a.nvox, a.h, a.w);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = thin_threads<R>(a.nvox, a.h, a.w);
     const int lane = threadIdx.x & 63;
     // whole wavefronts only: the stores at the end are shared by its lanes
     if (i - lane >= n) return;
     int z, y, x;
-    const int64_t v0 = thin_decode(i < n ? i : i - lane, a.d, a.h, a.w, z, y, x);
+    const int64_t v0 = thin_decode<R>(i < n ? i : i - lane, a.d, a.h, a.w, z, y, x);
     const int live = i < n ? min(a.h - y, R) : 0;  // rows that this thread stores
     const int64_t HW = (int64_t)a.h * a.w;
     float acc[R][kThin];
@@ -1197,18 +1205,17 @@ __global__ __launch_bounds__(256) void conv_thin_in_kernel(ConvArgs a)
     }
 }
 
-// 16 -> 1 channel.  A thread unpacks the 16 channels of each voxel of the
-// kThinRows + 2 rows and three planes it needs once for its up to three rows
-// of outputs; the weights are uniform and come through the scalar cache.
+// 16 -> 1 channel.  A thread unpacks the 16 channels of each voxel of the R + 2
+// rows and three planes it needs once for its up to three rows of outputs; the weights are uniform and come through the scalar cache.
 // Taps outside the grid are left out.
+template <int R>
 __global__ __launch_bounds__(256) void conv_thin_out_kernel(ConvArgs a)
 {
-    constexpr int R = kThinRows;
     typedef __attribute__((address_space(4))) const uint32_t Weights;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = thin_threads(a.nvox, a.h, a.w);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = thin_threads<R>(a.nvox, a.h, a.w);
     if (i >= n) return;
     int z, y, x;
-    const int64_t v0 = thin_decode(i, a.d, a.h, a.w, z, y, x);
+    const int64_t v0 = thin_decode<R>(i, a.d, a.h, a.w, z, y, x);
     const int64_t HW = (int64_t)a.h * a.w;
     float acc[R];
 #pragma unroll
@@ -1850,11 +1857,19 @@ int launch_fwd_ci(int co, const ConvArgs &a, hipStream_t st)
 int launch_fwd(int ci, int co, ConvArgs a, hipStream_t st)
 {
     if (ci == 1 && co == kThin) {
-        hipLaunchKernelGGL(conv_thin_in_kernel, grid1(thin_threads(a.nvox, a.h, a.w)), dim3(256), 0, st, a);
+        if (a.nvox >= kThinRowsVox)
+            hipLaunchKernelGGL((conv_thin_in_kernel<kThinRows>), grid1(thin_threads<kThinRows>(a.nvox, a.h, a.w)),
+                               dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((conv_thin_in_kernel<1>), grid1(a.nvox), dim3(256), 0, st, a);
         return 0;
     }
     if (ci == kThin && co == 1) {
-        hipLaunchKernelGGL(conv_thin_out_kernel, grid1(thin_threads(a.nvox, a.h, a.w)), dim3(256), 0, st, a);
+        if (a.nvox >= kThinRowsVox)
+            hipLaunchKernelGGL((conv_thin_out_kernel<kThinRows>), grid1(thin_threads<kThinRows>(a.nvox, a.h, a.w)),
+                               dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((conv_thin_out_kernel<1>), grid1(a.nvox), dim3(256), 0, st, a);
         return 0;
     }
     const int64_t waves = (a.nvox + 63) / 64;

@@ -81,3 +81,31 @@ def test_lds_staged_edges(ci, co, shape):
         assert torch.equal(p, q)
     ref, size = _conv(x, w, shape, b)
     _check(outs[0][0], np.maximum(ref, 0.0), size, ci)
+
+
+# Three samples together (3 x 2^18 voxels and more) take four rows per thread,
+# each alone one row: the same bits, whatever is left of the last four rows.
+@pytest.mark.parametrize("ci,co", [(1, 16), (16, 1)])
+@pytest.mark.parametrize("d,h,w", [(56, 65, 73), (61, 66, 67), (58, 67, 71), (64, 64, 64)])
+def test_one_channel_layers_rows_per_thread(ci, co, d, h, w):
+    n, nv = 3, 3 * d * h * w
+    assert nv // 3 < 3 << 18 <= nv
+    rng, x, _, b, skip, wf, wb = _operands((n, d, h, w), ci, co)
+    x, skip, dy, mask = _bf(x), _bf(skip), _bf(rng.standard_normal((nv, co))), _bf(rng.standard_normal((nv, ci)))
+    bias = torch.from_numpy(b).to(DEV)
+
+    def run(shape, at):
+        k = int(np.prod(shape))
+        y, r = torch.full((k, co), 7.0, device=DEV), torch.full((k, co), 7.0, dtype=torch.bfloat16, device=DEV)
+        out, dx = torch.empty_like(r), torch.full((k, ci), 7.0, device=DEV)
+        part = lambda a: a[at].clone()  # 16-byte aligned
+        N.conv3d_fwd(shape, ci, co, part(x), wf, bias, True, skip=part(skip), y=y, r=r, out=out)
+        N.conv3d_dgrad(shape, ci, co, part(dy), wb, dx)
+        g = [torch.full((k, ci), 7.0, dtype=torch.bfloat16, device=DEV)] if ci == 16 else []
+        for t in g:  # one channel has no fused ReLU gradient
+            N.conv3d_dgrad(shape, ci, co, part(dy), wb, dx, mask=part(mask), g_out=t)
+        return [y, r, out, dx] + g
+
+    each = [run((1, d, h, w), slice(i * nv // n, (i + 1) * nv // n)) for i in range(n)]
+    for k, t in enumerate(run((n, d, h, w), slice(0, nv))):
+        assert torch.isfinite(t.float()).all() and torch.equal(t, torch.cat([e[k] for e in each])), k

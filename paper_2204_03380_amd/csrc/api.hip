@@ -872,7 +872,8 @@ int best_rows(const Job &J, int steps, int vec, int top, int least)
 // 2.5 / 4.9 against 4.0 / 6.9, 300 3.1 / 7.4; 2/16/3 255 2.95 / 6.1 against
 // 4.6 / 8.8, 418 4.1 / 9.9 against 6.4 / 11.9, 616 5.3 / 14.0 against 6.6 /
 // 13.0, 1232 7.9 / 23.3 against 10.8 / 20.8, 3696 20.3 against 22.8, 4928
-// 32.3 against 30.0.
+// 32.3 against 30.0.  Two reverse steps at two floats, where three have too
+// many blocks, keep to them too (432 to 493 blocks 13 to 17 against 16 to 20).
 int fit_block(const Job &J, int steps, bool reverse)
 {
     const int64_t most[] = {0, 512, 256, reverse ? 512 : 3700};
@@ -901,16 +902,20 @@ int once_multi(const Job &J, bool reverse)
     return bytes > ((int64_t)256 << 20) ? kOnce : 0;
 }
 
+Tune block_shape(Tune t)
+{
+    const BlockShape &b = kBlockShapes[t.block];
+    t.once = 0;  // the block kernels have no such form
+    t.vec = b.vec;
+    t.zseg = b.waves * b.rows - 8 * (t.steps - 1);
+    return t;
+}
+
 Tune fit_multi(const Job &J, Tune t, bool reverse)
 {
     if (t.vec < 4) t.once = once_multi(J, reverse);
     if (g_tune_exact.load()) return t;
-    if ((t.block = fit_block(J, t.steps, reverse)) != 0) {
-        const BlockShape &b = kBlockShapes[t.block];
-        t.vec = b.vec;
-        t.zseg = b.waves * b.rows - 8 * (t.steps - 1);
-        return t;
-    }
+    if ((t.block = fit_block(J, t.steps, reverse)) != 0) return block_shape(t);
     const int least = reverse && t.steps == 3 ? 27 : 18;
     if (count_multi(J, t.steps, t.vec, std::min(t.zseg, least)) >= (reverse ? 2048 : 1900)) {
         t.zseg = best_rows(J, t.steps, t.vec, t.zseg, least);
@@ -922,6 +927,7 @@ Tune fit_multi(const Job &J, Tune t, bool reverse)
         t.zseg = best_rows(J, 2, 1, 54, 18);
     } else {
         t.vec = count_multi(J, 2, 2, kMinZseg) >= 1800 ? 2 : 1;
+        if (reverse && t.vec == 2 && (t.block = fit_block(J, 2, true)) != 0) return block_shape(t);
         t.zseg = best_rows(J, 2, t.vec, 18, kMinZseg);
     }
     return t;
@@ -1027,10 +1033,14 @@ int build_job_tables(Job &J)
     // one for imaging and the gradient.  Three steps per launch store the
     // middle level only on the receiver rows, so storage RTM (which copies
     // whole stored levels) takes two.  The gradient pass takes three where
-    // the runtime chooses the shape and two of a configured one: at 209
-    // registers and two floats per lane its triple only pays with few
-    // wavefronts per SIMD (24 windows: 40.8 us per step with three, 46.6
-    // with two).
+    // the runtime chooses the shape and two of a configured one.  Its triple
+    // (209 registers at two floats per lane) pays with many wavefronts, where
+    // it saves traffic, and with few; between them, two steps can be the
+    // quicker (us per step, two / three: 4 windows of 880 x 380 12.7 / 11.1,
+    // 18 39.1 / 33.6, 24 50.1 / 56.2, 48 94 / 93, 96 201 / 162, 192 404 / 285;
+    // 4 shots of 2381 x 831 43.5 / 52.3, 8 86 / 85, 16 175 / 149, 48 516 / 352).
+    // Where it needs two strips for what two steps hold in one it is
+    // slower (60 shots of 117 x 1891 95.5 / 118.5, 200 of 120 x 400 61.5 / 88.1).
     J.fw2 = Tiling{};
     J.rv2 = Tiling{};
     J.fw2.ndim = J.rv2.ndim = ndim;
@@ -1044,7 +1054,9 @@ int build_job_tables(Job &J)
     }
     if ((J.op == RTM_OP_RTM || J.op == RTM_OP_VJP) && conf_r.steps >= 2) {
         Tune t = conf_r;
-        if (J.op == RTM_OP_VJP && g_tune_exact.load()) t.steps = 2;
+        if (J.op == RTM_OP_VJP && t.steps == 3 &&
+            (g_tune_exact.load() || count_multi(J, 3, t.vec, t.zseg) >= 2 * count_multi(J, 2, t.vec, t.zseg)))
+            t.steps = 2;
         J.rv2.tune = fit_multi(J, t, true);
         J.rv2.steps = J.rv2.tune.steps;
         if ((rc = build_tiling(J, J.rv2, true))) return rc;

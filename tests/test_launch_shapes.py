@@ -112,3 +112,17 @@ def test_reverse_steps_in_the_cache_keep_their_workgroups_resident(op, padded, s
     (rtm.RTM_OP_RTM, True, (188, 188, 188), 8, True, 0), (rtm.RTM_OP_RTM, True, (188, 188, 188), 8, False, 1)])
 def test_arrays_kept_out_of_the_cache(op, reverse, padded, shots, shared, uncached):
     assert shape_of(op, padded, shots, reverse, shared)["uncached"] == uncached
+
+
+# Three steps of a strip own 112 columns, two 120: models of 113 to 120 columns
+# would march everything twice (60 shots of 117 x 1891: 118.5 us per step
+# against 95.5, the older kernels 104.5).
+@pytest.mark.parametrize("nx,steps", [(112, 3), (113, 2), (120, 2), (121, 3), (240, 3)])
+def test_gradient_steps_of_narrow_models(nx, steps):
+    assert shape_of(rtm.RTM_OP_VJP, (1891, nx), 60, reverse=True, shared=False)["steps"] == steps
+
+
+def test_two_reverse_steps_take_blocks_before_nine_row_strips():
+    for op in (rtm.RTM_OP_RTM, rtm.RTM_OP_VJP):
+        s = shape_of(op, (1891, 112), 10, reverse=True)
+        assert (s["steps"], s["vec"], s["rows"], s["waves"]) == (2, 2, 40, 16)

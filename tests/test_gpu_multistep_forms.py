@@ -124,3 +124,27 @@ def test_narrow_gradient():
     def check(s):
         assert (s["steps"], s["vec"], s["waves"]) == (2, 2, 0)
     _compare(batch, "vjp", 60, check)
+# The block kernels: 8 wavefronts x 4 rows at one float per lane, 12 x 3 and
+# 16 x 3 at two; one and several shots
+@pytest.mark.parametrize("op", ["model", "rtm", "vjp"])
+@pytest.mark.parametrize("steps,NX,NZ,shots,waves", [(2, 281, 281, 1, 8), (2, 281, 97, 3, 8), (2, 1400, 540, 1, 12),
+                                                     (2, 700, 540, 2, 12), (2, 1574, 540, 1, 16), (3, 281, 281, 1, 8),
+                                                     (3, 900, 540, 1, 12), (3, 880, 270, 2, 12), (3, 1574, 540, 1, 16)])
+def test_blocks(op, steps, NX, NZ, shots, waves):
+    batch = _Batch(NX, NZ)
+    _configure(False, steps, 2, 108)
+
+    def check(s):
+        assert (s["steps"], s["waves"]) == (steps, waves)
+    _compare(batch, op, shots, check)
+
+
+# two reverse steps of a job with too many blocks of three
+@pytest.mark.parametrize("op", ["rtm", "vjp"])
+def test_blocks_of_two_steps_where_three_have_too_many(op):
+    batch = _Batch(700, 380)
+    _configure(False, 3, 2, 108)
+
+    def check(s):
+        assert (s["steps"], s["vec"], s["waves"]) == (2, 2, 16)
+    _compare(batch, op, 8, check)

@@ -278,7 +278,8 @@ PAPER_STORAGE_GB = {"Table 2": 2.638, "Table 4": 132.062}
 PAPER_STRIDE = 10
 
 
-PAPER_3D_SHAPES = tuple((v, y, z, o) for v, y, z in ((1, 4, 18), (1, 8, 18), (2, 8, 18), (1, 4, 36)) for o in (0, 1))
+PAPER_3D_SHAPES = tuple((v, y, z, o) for v, y, z in ((1, 4, 18), (1, 8, 18), (2, 8, 18), (1, 4, 36), (1, 8, 54),
+                                                    (2, 16, 126)) for o in (0, 1))
 
 
 def paper_shapes(nb=50, kinds=("modeling", "rtm", "storage")):
@@ -668,8 +669,6 @@ def main():
         v_tmp = rtm.rtm_rbc_pad(g, v_int, s.seed, 0.0)
         tuned = autotune.tune_batch(g, v_tmp, wav, [s.src[i] for i in range(B)], s.rec, s.dt, nt_probe=90, reps=2)
         del v_tmp
-        # the timed batch runs exactly the configuration the tuner picked for it
-        rtm.rtm_set_tuning(rtm.RTM_TUNE_EXACT, 1, 0)
 
     # Buffers resident in HBM before timing: padded model, B traces, stack.
     v_pad = rtm.rtm_rbc_pad(g, v_int, s.seed, 0.0)
@@ -728,8 +727,6 @@ def main():
     # Plain per-shot calls on the same GPU (modeling + RTM), same shots as
     # the first batch; their images must equal the batched ones bit for bit.
     plain_shots = groups[0][:min(B, args.plain_shots)]
-    exact = rtm.rtm_get_tuning(rtm.RTM_TUNE_EXACT)[0]
-    rtm.rtm_set_tuning(rtm.RTM_TUNE_EXACT, 0, 0)  # single shots take the library's shapes for small jobs
     torch.cuda.synchronize()
     p0 = time.perf_counter()
     plain = []
@@ -738,7 +735,6 @@ def main():
         plain.append((d, rtm.rtm_rtm_shot(g, v_pad, s.dt, wav, s.src[i], s.rec, d, eps_rel=1e-3)["image"]))
     torch.cuda.synchronize()
     plain_s = time.perf_counter() - p0
-    rtm.rtm_set_tuning(rtm.RTM_TUNE_EXACT, exact, 0)
     # The batched side of the comparison is the timed configuration itself:
     # the first group's modeling plan as timed, then an RTM plan of the same
     # B shots at the same launch shape writing one image per shot.  Its launch

@@ -95,3 +95,38 @@ def test_tuner_3d_with_tile_orders():
     d2 = rtm.rtm_model_shot(g, vp, dt, w, src, rec)
     im2 = rtm.rtm_rtm_shot(g, vp, dt, w, src, rec, d2)["image"]
     assert torch.equal(d2, d) and torch.equal(im2, ref)
+
+
+@pytest.mark.parametrize("nx,nz,shots,block", [(181, 181, 1, True), (500, 500, 48, False)])
+def test_what_is_timed_is_what_runs(monkeypatch, nx, nz, shots, block):
+    """Without given shapes the library's own choice takes part, block kernels
+    of a small job included, and the batch tuned for launches the shape that
+    was timed fastest."""
+    s = synth.config_small2d(nx=nx, nz=nz, nb=10, nt=30, seed=12)
+    g = rtm.Grid.for_model(s.v_int, s.h, s.nb)
+    vp = rtm.rtm_rbc_pad(g, torch.from_numpy(s.v_int).to(DEV), s.seed, 0.0)
+    w = torch.from_numpy(s.wavelet).to(DEV)
+    srcs = [np.array([5.5 + (7 * i) % (nx - 12), 0.0, 3.5]) for i in range(shots)]
+
+    def plans():
+        tr = [torch.empty((s.rec.shape[0], s.nt + 1), device=DEV) for _ in srcs]
+        image = torch.zeros(g.interior_shape, device=DEV)
+        mp = rtm.BatchPlan(rtm.RTM_OP_MODEL, [rtm.BatchShot(g, vp, w, x, s.rec, traces_out=t)
+                                              for x, t in zip(srcs, tr)], s.dt, s.nt, defer_workspace=True)
+        rp = rtm.BatchPlan(rtm.RTM_OP_RTM, [rtm.BatchShot(g, vp, w, x, s.rec, traces_in=t, image=image)
+                                            for x, t in zip(srcs, tr)], s.dt, s.nt, defer_workspace=True)
+        return mp.launch_shape(), rp.launch_shape(True)
+
+    automatic = plans()
+    assert all((x["waves"] > 0) == block for x in automatic)
+    times = {}
+    inner = autotune._time_shape
+
+    def record(*args):
+        times["seen"] = args[-1]
+        return inner(*args)
+    monkeypatch.setattr(autotune, "_time_shape", record)
+    res = autotune.tune_batch(g, vp, w, srcs, s.rec, s.dt, nt_probe=30, reps=1)
+    for key, auto, now in zip(("forward", "reverse"), automatic, plans()):
+        assert times["seen"][(key, *auto.values(), ())] == res["table"]["current"][key == "reverse"]
+        assert times["seen"][(key, *now.values(), ())] == res[key][-1] <= res["table"]["current"][key == "reverse"]

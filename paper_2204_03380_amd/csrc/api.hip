@@ -486,6 +486,9 @@ int build_tiling(Job &J, Tiling &T, bool with_receivers)
     T.cont.clear();
     std::vector<RawEnt> se, re;
     std::vector<Contrib> pool;  // contributions of the entries
+    // a march is unrolled by its queue of nine rows (planes) and checks no row of a round by itself
+    if (T.tune.block == 0 && T.tune.zseg % kZUnroll != 0)
+        return fail(RTM_EINVAL, "marching tiles of %d rows or planes, not a multiple of %d", T.tune.zseg, kZUnroll);
     // 2-D: one tile is TX adjacent strips (one workgroup); 3-D: one strip.
     // 2-D tiles of S > 1 steps per launch: strips of 64 vec columns starting
     // at j W - 4 (S - 1) that own W = 64 vec - 8 (S - 1) columns each

@@ -96,9 +96,12 @@ constexpr BlockShape kBlockShapes[] = {{0, 0, 0}, {1, 8, 4}, {2, 12, 3}, {2, 16,
 // launch touches once is better kept out of the caches.
 constexpr int kOnce = 0x10000;
 
-// A 2-D stencil tile: one wavefront marches down rows [z0, z1) of a strip
-// of 64 * VEC columns starting at x0; z1 - z0 is a multiple of kZUnroll
-// (rows at or below NZ are zero halo rows and stay zero).  Injection entries
+// A 2-D stencil tile: rows [z0, z1) of a strip of 64 * VEC columns starting
+// at x0.  A marching tile is one wavefront (tx strips: tx of them) that goes
+// down the rows, and z1 - z0 is a multiple of kZUnroll (rows at or below NZ
+// are zero halo rows and stay zero); a block kernel's tile is a workgroup of
+// several wavefronts that hold waves * rows - 8 (T - 1) rows at once, of any
+// number, and the last of a column may end early.  Injection entries
 // of the tile are ents[sbeg, send) (source, into p) and ents[rbeg, rend)
 // (receivers, into mu).  A tile of T > 1 steps per launch also lists the
 // entries of its whole strip and rows [z0 - 4 (T - 1), z1 + 4 (T - 1)) (where

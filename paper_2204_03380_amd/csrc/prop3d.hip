@@ -597,9 +597,10 @@ __global__ __launch_bounds__(64 * TY) void recv3d_kernel(const ShotDev *__restri
 }
 
 // `code` is floats per lane | kOnce where the arrays of a step exceed the
-// memory-side cache; `ty` rows per tile.  A tile's rows are split over
-// wavefronts by register need: one row each while a workgroup has at most
-// eight (forward) or four (reverse) of them, and at two floats per lane.
+// memory-side cache; `ty` rows per tile.  CALL takes floats per lane,
+// wavefronts and rows per wavefront: one row each, but two of 16 rows at one
+// float per lane and, in the reverse kernels (two fields, twice the
+// registers), of eight rows at one and two floats.
 #define RTM_ONCE3(CALL, V, Y, R) do { if (once) CALL(V, Y, R, true); else CALL(V, Y, R, false); } while (0)
 #define RTM_FWD_SHAPES(CALL)                        \
     switch (vec << 8 | ty) {                        \

@@ -126,3 +126,22 @@ def test_two_reverse_steps_take_blocks_before_nine_row_strips():
     for op in (rtm.RTM_OP_RTM, rtm.RTM_OP_VJP):
         s = shape_of(op, (1891, 112), 10, reverse=True)
         assert (s["steps"], s["vec"], s["rows"], s["waves"]) == (2, 2, 40, 16)
+
+
+# The marches take nine rows (planes) a round without a check of each; only
+# the block kernels' tiles, which hold all their rows at once, have any number.
+@pytest.mark.parametrize("padded", [(9, 5), (201, 201), (434, 1474), (500, 880), (871, 2421), (1891, 117), (64, 64, 64),
+                                    (156, 156, 156), (356, 612, 612)])
+@pytest.mark.parametrize("shots", [1, 3, 12, 48])
+@pytest.mark.parametrize("steps", [1, 2, 3])
+def test_marching_tiles_are_whole_rounds(padded, shots, steps):
+    for op in (rtm.RTM_OP_MODEL, rtm.RTM_OP_RTM):
+        rtm.rtm_set_steps_per_launch(op, steps)
+    for op in (rtm.RTM_OP_MODEL, rtm.RTM_OP_RTM, rtm.RTM_OP_VJP):
+        for reverse in (False, True)[:1 + (op != rtm.RTM_OP_MODEL)]:
+            s = shape_of(op, padded, shots, reverse)
+            if s["waves"] == 0 or len(padded) == 3:
+                assert s["rows"] > 0 and s["rows"] % 9 == 0
+            else:
+                rows = {8: 4, 12: 3, 16: 3}[s["waves"]]
+                assert s["steps"] > 1 and s["rows"] == s["waves"] * rows - 8 * (s["steps"] - 1)

@@ -130,16 +130,18 @@ const char *rtm_last_error(void);
  * autotuner: `op` RTM_OP_MODEL selects the forward kernel, RTM_OP_RTM or
  * RTM_OP_VJP the reverse kernels; vec in {1, 2, 4} floats per lane (strips
  * of 64 * vec columns), zseg rows per tile, a multiple of 9 in [9, 4095]
- * (the march is unrolled by the 9-row register queue).  A job with too few
- * tiles to fill the GPU gets a narrower shape automatically, unless
- * rtm_set_tuning(RTM_TUNE_EXACT, 1, 0) was called (RTM_TUNE_EXACT, 0, 0
- * re-enables narrowing).  Results do not depend on the shape.  Not
- * synchronised with concurrent calls. */
+ * (the march is unrolled by the 9-row register queue).  The setting is where
+ * the library's choice starts from: a job gets the rows, floats per lane and
+ * steps per launch that suit its size, and a small one may run on block
+ * kernels instead, whose shapes are their own and can be wider than the
+ * configured one (rtm_batch_shape tells what a plan launches).
+ * rtm_set_tuning(RTM_TUNE_EXACT, 1, 0) has every job take the configured
+ * shape as it is, RTM_TUNE_EXACT, 0, 0 restores the choice.  Results do not
+ * depend on the shape.  Not synchronised with concurrent calls. */
 #define RTM_TUNE_EXACT 0x100
 int rtm_set_tuning(int op, int vec, int zseg);
 /* Current launch shape for `op` (same selection as rtm_set_tuning);
- * op RTM_TUNE_EXACT returns the no-narrowing setting (0 or 1) in *vec and 0
- * in *zseg. */
+ * op RTM_TUNE_EXACT returns that setting (0 or 1) in *vec and 0 in *zseg. */
 int rtm_get_tuning(int op, int *vec, int *zseg);
 
 /* Full 2-D launch shape: as rtm_set_tuning plus tx in {1, 2, 4}
@@ -162,8 +164,9 @@ int rtm_get_tuning2d(int op, int *vec, int *tx, int *zseg);
  * jobs; storage RTM, which copies whole levels, takes 2 when 3 is set),
  * RTM_OP_RTM for the imaging reverse pass and the gradient pass (which
  * takes at most 2 under RTM_TUNE_EXACT; probed runs take one step per
- * launch; the last nt mod S steps are taken one at a time).  A job too
- * small to fill the GPU may take fewer unless RTM_TUNE_EXACT is set.
+ * launch; the last nt mod S steps are taken one at a time).  A job may take
+ * fewer where that is faster (too small to fill the GPU, or gradients of
+ * models of few columns) unless RTM_TUNE_EXACT is set.
  * Results are bit-identical whatever the setting.
  * Returns RTM_EINVAL for other values. */
 int rtm_set_steps_per_launch(int op, int steps);

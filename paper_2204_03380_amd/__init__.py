@@ -115,7 +115,7 @@ def rtm_get_tuning3d(op: int):
 
 
 def rtm_set_tile_order3d(op: int, z_inner: int) -> None:
-    """3-D tile numbering: 0 y tiles innermost (default), 1 z bands innermost."""
+    """3-D tile numbering: 0 x strips innermost, band by band (default), 1 z bands innermost."""
     _lib.check(_lib.load().rtm_set_tile_order3d(op, int(z_inner)))
 
 
@@ -138,8 +138,8 @@ def rtm_get_tuning2d(op: int):
 
 def rtm_set_steps_per_launch(op: int, steps: int) -> None:
     """Time steps per 2-D launch, 1, 2 or 3: RTM_OP_MODEL for every forward
-    pass, RTM_OP_RTM for the imaging reverse pass.  Results are the same bits
-    whatever the setting; jobs too small to fill the GPU take fewer."""
+    pass, RTM_OP_RTM for the imaging reverse and gradient passes.  Results are
+    the same bits whatever the setting; a job takes fewer where that is faster."""
     _lib.check(_lib.load().rtm_set_steps_per_launch(op, steps))
 
 
@@ -159,7 +159,7 @@ def rtm_get_tuning(op: int):
 
 def tuning_snapshot() -> dict:
     """The process-wide launch settings (2-D and 3-D shapes, the 3-D tile
-    order, 2-D steps per launch, the no-narrowing flag), for tuning_restore."""
+    order, 2-D steps per launch, the RTM_TUNE_EXACT flag), for tuning_restore."""
     snap = {"exact": rtm_get_tuning(RTM_TUNE_EXACT)[0]}
     for op in (RTM_OP_MODEL, RTM_OP_RTM):
         snap[("2d", op)] = rtm_get_tuning2d(op)

@@ -127,8 +127,8 @@ def tune_batch(grid: Grid, v_pad: torch.Tensor, wavelet: torch.Tensor, srcs: Seq
     and stay unless another is faster.  nt_probe should be a multiple of 6 so
     that every steps-per-launch setting divides it.
     Returns {"forward": (*shape, us per step), "reverse": (*shape, us per
-    step), "table": {shape: (forward us, reverse us)}}.  The no-narrowing
-    setting is left as it was."""
+    step), "table": {shape: (forward us, reverse us)}}.  RTM_TUNE_EXACT
+    is left as it was."""
     if shapes is None:
         candidates = [("current", configured(RTM_OP_MODEL, grid.ndim), configured(RTM_OP_RTM, grid.ndim))]
         shapes = DEFAULT_SHAPES_3D if grid.ndim == 3 else DEFAULT_SHAPES

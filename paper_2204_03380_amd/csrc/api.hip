@@ -153,14 +153,14 @@ struct Tune {
 // (232 us per step against 213 at vec 4).
 std::atomic<int> g_tune2d_fwd{(2 << 28) | (1 << 24) | (2 << 16) | 108};
 std::atomic<int> g_tune2d_rev{(2 << 28) | (1 << 24) | (2 << 16) | 108};
-std::atomic<int> g_tune_exact{0};  // 1: never narrow the configured shapes
+std::atomic<int> g_tune_exact{0};  // 1: take the configured shapes as they are
 std::atomic<double> g_persist_wait_ms{4000.0};  // bounded wait of persistent passes
 
 // 3-D shapes: (vec << 24) | (ty << 16) | (z_inner << 15) | zseg: the largest
 // tiles that fit_tune3 chooses from; defaults from sweeps over 64^3 to 512 x
 // 512 x 256 grids (612 x 612 x 356 padded, us per step: forward, 2 floats x
-// 16 rows 442, 2 x 8 466, 1 x 8 485; reverse, 1 x 8 1096, 1 x 16 1108, 2 x 8
-// 1112, 1 x 4 1142).
+// 16 rows 418, 2 x 8 446, 1 x 8 456; reverse, 1 x 8 1096, 1 x 16 1101, 2 x 8
+// 1101, 1 x 4 1108).
 std::atomic<int> g_tune3d_fwd{(2 << 24) | (16 << 16) | 126};
 std::atomic<int> g_tune3d_rev{(1 << 24) | (8 << 16) | 54};
 
@@ -702,10 +702,10 @@ int64_t count_tiles3(const Job &J, Tune t)
 // once: a step's arrays beyond 7/8 of the 256 MiB memory-side cache come from
 // HBM whatever is done, and then the L2 serves the shared halo rows better
 // without the arrays that are touched once; smaller ones live in that cache
-// (us per step with / without: 612 x 612 x 356 cells forward 442 / 527,
-// reverse 1096 / 1251; 300^3 reverse 256 / 315; 252^3 reverse, 353 MB, 122 /
-// 137; 220^3 reverse, 245 MB, 91 / 94; 252^3 forward, 192 MB, 53 / 50; 188^3
-// reverse, 150 MB, 55 / 53).  A model that several shots share is not touched
+// (us per step with / without: 612 x 612 x 356 cells forward 419 / 538,
+// reverse 1096 / 1266; 300^3 reverse 250 / 329; 252^3 reverse, 416 MB, 133 /
+// 157; 220^3 reverse, 276 MB, 99 / 104; 252^3 forward, 192 MB, 47 / 45; 188^3
+// reverse, 171 MB, 61 / 55).  A model that several shots share is not touched
 // once (with / without: 16 x 124^3 forward 111 / 99, reverse 341 / 292,
 // gradient 283 / 256; 8 x 188^3 186 / 163, 548 / 476, 444 / 405), which counts
 // from four shots on in a forward step and, in a reverse step of two fields,
@@ -727,20 +727,20 @@ int64_t count_tiles3(const Job &J, Tune t)
 // and 27 planes if these still give 2.5 per CU, else the configured ones (1 x 4
 // against 1 x 8 rows: 64^3 12.1 / 15.2, 128^3 20.6 /
 // 20.9, 400 x 90 x 70, 5.0 per CU, 23.9 / 25.0, 260 x 180 x 100 at 27 planes
-// 39.1 / 45.6, 188^3 55.9 / 56.1; 3 x 78 x 353 x 24
+// 39.1 / 45.6, 188^3 53.5 / 52.1; 3 x 78 x 353 x 24
 // at 27, 2.1 per CU, 33.1 / 26.6; not resident: 2 x 124^3 at 9 planes 37.2 /
 // 34.5, 4 x 124^3 at 36 79.8 / 75.9).
 //
 // Planes per tile otherwise: the least march time.  A tile marches 8 planes
 // beyond its own, and the fullest CU ends the launch: one workgroup of 16
 // wavefronts fills a CU, smaller ones share it, k of them taking about 1.2 + k
-// units (501 x 501 x 235 cells, one / two / 2.5 workgroups of 16 per CU: 203 /
-// 208 / 241 us per step; 612 x 612 x 356 at 72 planes, 3.8 per CU, 442, at 90,
-// 3.05, 508).  The reverse kernel, at two rows per wavefront, stays near its
+// units (501 x 501 x 235 cells, one / two / 2.5 workgroups of 16 per CU: 164 /
+// 170 / 199 us per step; 612 x 612 x 356 at 72 planes, 3.8 per CU, 418, at 90,
+// 3.05, 477, at 63, 4.6, 444).  The reverse kernel, at two rows per wavefront, stays near its
 // memory time at any height that leaves enough workgroups (316^3 at 9 to 81
-// planes 264 to 292); on arrays that fit the cache the same march rule holds,
+// planes 297 to 325); on arrays that fit the cache the same march rule holds,
 // with a floor for what a lone workgroup takes per plane (188^3 at 9, 18, 27,
-// 36 planes 53.1, 58.5, 48.1, 56.2), and from 14 workgroups per CU on nine
+// 36 planes 55.5, 67.0, 52.1, 56.9), and from 14 workgroups per CU on nine
 // planes are best (4 x 156^3, 16.9 per CU, at 9, 27 and 54 planes 140, 159,
 // 142; 8 x 124^3, 14: 148, 161, 147; 24 x 64^3, 12: 65.1, at 18 63.1).
 enum Pass3 { kFwd3, kRecv3, kRev3 };

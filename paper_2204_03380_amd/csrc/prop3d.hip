@@ -29,9 +29,10 @@
 // took 581 us (5.6 TB/s with 4.9 arrays read for 3) and 1365 us, of which the
 // x-innermost tile order (whole rows of tiles on one XCD) took 25 and 103 us,
 // non-temporal access to what a step touches once 22 and 85, and wider and
-// taller tiles the rest: now 421 and 1095 us at 5.7 and 5.8 TB/s, with 3.5 arrays
-// read for 3 and 8.9 for 6.  501 x 501 x 235: forward 289 -> 203, receiver 325 -> 231; 188^3, in
-// the memory-side cache: 25.8 -> 24.4 and 61.1 -> 48.1 us.  Two rows per
+// taller tiles the rest: now 418 and 1096 us at 5.7 and 5.8 TB/s, with 3.5 arrays
+// read for 3 and 9.0 for 6.  501 x 501 x 235: forward 255 -> 165, reverse 596 ->
+// 473, receiver 270 -> 178; 188^3, in the memory-side cache: forward 24.7 -> 20.4,
+// reverse 65.0 -> 54.3 us.  Two rows per
 // wavefront share y-neighbours and halo loads in the reverse kernel, which is
 // short of registers for more wavefronts (188^3: 8 rows as 4 x 2 49.6, as
 // 8 x 1 57.6 us).

@@ -710,7 +710,11 @@ int64_t count_tiles3(const Job &J, Tune t)
 // gradient 283 / 256; 8 x 188^3 186 / 163, 548 / 476, 444 / 405), which counts
 // from four shots on in a forward step and, in a reverse step of two fields,
 // from eight on beyond twice the cache (4 x 304 x 337 x 43 160 / 187, 16 x 96^3
-// gradient 130 / 138, though 64 x 64^3 203 / 182).  Over 278 drawn jobs the
+// gradient 130 / 138).  Rows of one strip are read whole by their own tiles,
+// and the reverse step of a field narrower than that is better with the caches
+// on all but the gradient with a model per shot (64 x 64^3 203 / 186, 50 x 54 x
+// 324 x 76 1045 / 822, 30 x 56 x 107 x 92 232 / 208; that gradient goes either
+// way, 14 x 38 x 132 x 186 190 / 211, 50 x 50 x 35 x 390 485 / 440).  Over 278 drawn jobs the
 // rule costs forward 0.1, reverse 1.6, gradient 1.2 % against the better of the
 // two for each (once for all: 3.6, 3.0, 2.1 %); with a model per shot small
 // extents go either way (reverse, 16 x 124^3 339 / 309, 5 x 301 x 55 x 205
@@ -742,7 +746,13 @@ int64_t count_tiles3(const Job &J, Tune t)
 // with a floor for what a lone workgroup takes per plane (188^3 at 9, 18, 27,
 // 36 planes 55.5, 67.0, 52.1, 56.9), and from 14 workgroups per CU on nine
 // planes are best (4 x 156^3, 16.9 per CU, at 9, 27 and 54 planes 140, 159,
-// 142; 8 x 124^3, 14: 148, 161, 147; 24 x 64^3, 12: 65.1, at 18 63.1).
+// 142; 8 x 124^3, 14: 148, 161, 147; 24 x 64^3, 12: 65.1, at 18 63.1).  So
+// they are beyond the cache while a band of planes is small, which the next
+// band's workgroups find in the L2 (14 x 125 x 135 x 195 at 9, 27, 54 planes
+// 505, 526, 550; forward, 30 x 38 x 98 x 114 at one float x 16 rows 71, 84, 94;
+// 300^3 258, 262, 289; of 4 rows where 8 compute a tenth more, 28 x 132 x 325
+// 93 / 98, 50 x 50 x 35 x 390 489 / 507; single grids of 420 x 420 cells a plane 345, 339, 350,
+// of 501 x 501 658, 573, 588).
 enum Pass3 { kFwd3, kRecv3, kRev3 };
 constexpr int64_t kCacheBytes = (int64_t)224 << 20;
 
@@ -750,22 +760,29 @@ int once3(const Job &J, Pass3 pass)
 {
     const int64_t nsh = (int64_t)J.shots.size();
     int64_t bytes = 0;
+    int NX = 0;
     for (const ShotIn &S : J.shots) {
         const GridInfo &g = S.g;
+        NX = std::max(NX, g.NX);
         const int64_t all = 4 * (int64_t)g.NX * g.NY * g.NZ, in = 4 * g.nx * g.ny * g.nz;
         bytes += pass != kRev3 ? 3 * all : J.op == RTM_OP_VJP ? 6 * all : 5 * all + 2 * in;
     }
     if (bytes <= kCacheBytes) return 0;
-    if ((int64_t)J.slot_shot.size() == nsh) return kOnce;  // a model for each shot
+    const bool own = (int64_t)J.slot_shot.size() == nsh;  // a model for each shot
+    if (pass == kRev3 && NX <= 64 && !(J.op == RTM_OP_VJP && own)) return 0;
+    if (own) return kOnce;
     return (pass != kRev3 ? nsh >= 4 : nsh >= 8 && bytes > 2 * kCacheBytes) ? 0 : kOnce;
 }
 
 Tune fit_tune3(const Job &J, Tune t, Pass3 pass)
 {
-    int NZr = 0, NX = 0;
+    int NZr = 0, NX = 0, NY = 0;
+    int64_t plane = 0;
     for (const ShotIn &S : J.shots) {
         NZr = std::max(NZr, S.g.L.NZr);
         NX = std::max(NX, S.g.NX);
+        NY = std::max(NY, S.g.NY);
+        plane = std::max(plane, (int64_t)S.g.NX * S.g.NY);
     }
     t.once = once3(J, pass);
     if (g_tune_exact.load()) return t;
@@ -779,11 +796,16 @@ Tune fit_tune3(const Job &J, Tune t, Pass3 pass)
             const double n = (double)count_tiles3(J, c) / 256.0;
             if (pass != kRev3 || (c.zseg == kMinZseg ? n <= 5.1 : n >= 2.5 && n <= 4.15)) return c;
         }
-        c = t;
-        c.zseg = kMinZseg;
-        if ((double)count_tiles3(J, c) >= 256.0 * 14.0) return c;
     }
     const bool full = t.ty * t.vec >= 32;  // workgroups that fill a CU
+    if (!t.once || (!full && plane <= 160000)) {
+        Tune c = t;
+        c.zseg = kMinZseg;
+        if ((double)count_tiles3(J, c) >= 256.0 * 14.0) {
+            if (pass == kRev3 && c.ty == 8 && (NY + 3) / 4 * 40 <= (NY + 7) / 8 * 72) c.ty = 4;
+            return c;
+        }
+    }
     double least = 0.0;
     for (int seg = 1; seg <= NZr / kZUnroll; ++seg) {
         Tune c = t;

@@ -145,3 +145,29 @@ def test_marching_tiles_are_whole_rounds(padded, shots, steps):
             else:
                 rows = {8: 4, 12: 3, 16: 3}[s["waves"]]
                 assert s["steps"] > 1 and s["rows"] == s["waves"] * rows - 8 * (s["steps"] - 1)
+
+
+# us per step: 50 own models of 76 x 324 x 54 imaging 1046 -> 794 (older kernels
+# 850), 30 shots on one model of 92 x 107 x 56 230 -> 186 (210)
+@pytest.mark.parametrize("nx,shared,op,uncached", [
+    (64, False, rtm.RTM_OP_RTM, 0), (65, False, rtm.RTM_OP_RTM, 1), (64, True, rtm.RTM_OP_RTM, 0),
+    (64, True, rtm.RTM_OP_VJP, 0), (64, False, rtm.RTM_OP_VJP, 1), (40, False, rtm.RTM_OP_RTM, 0)])
+def test_reverse_steps_of_one_strip_keep_to_the_caches(nx, shared, op, uncached):
+    s = shape_of(op, (76, 324, nx), 10 if shared else 50, reverse=True, shared=shared)
+    assert (s["uncached"], s["rows"]) == (uncached, 9)
+
+
+@pytest.mark.parametrize("op,reverse,padded,shots,rows", [
+    (rtm.RTM_OP_RTM, True, (195, 135, 125), 14, 9), (rtm.RTM_OP_VJP, True, (195, 135, 125), 14, 9),
+    (rtm.RTM_OP_RTM, True, (200, 380, 380), 1, 9), (rtm.RTM_OP_RTM, True, (235, 501, 501), 1, 27),
+    (rtm.RTM_OP_RTM, True, (356, 612, 612), 1, 54), (rtm.RTM_OP_MODEL, False, (356, 612, 612), 1, 72),
+    (rtm.RTM_OP_MODEL, False, (390, 35, 50), 50, 9), (rtm.RTM_OP_MODEL, False, (76, 324, 54), 50, 9)])
+def test_planes_per_tile_of_many_workgroups(op, reverse, padded, shots, rows):
+    assert shape_of(op, padded, shots, reverse, shared=False)["rows"] == rows
+
+
+@pytest.mark.parametrize("ny,ty", [(35, 4), (36, 4), (37, 8), (40, 8), (44, 8), (4, 4), (9, 4)])
+def test_rows_of_reverse_tiles_on_few_rows(ny, ty):
+    for op in (rtm.RTM_OP_RTM, rtm.RTM_OP_VJP):
+        s = shape_of(op, (390, ny, 200), 50, reverse=True, shared=False)
+        assert (s["ty"], s["rows"]) == (ty, 9)
